@@ -212,7 +212,14 @@ int mhd_restrict(mhd_ctx *fine, mhd_ctx *coarse);
  * along the sweep axis in chunks of `value` cells (value must divide the
  * axis length and be >= 8; 0 restores the built-in choice).  key: MHD_TUNE_
  * CHUNK_Y or MHD_TUNE_CHUNK_Z for the single operators, MHD_TUNE_PAIR_
- * CHUNK_Y or MHD_TUNE_PAIR_CHUNK_Z for the fused reverse-half pairs.
+ * CHUNK_Y or MHD_TUNE_PAIR_CHUNK_Z for the fused reverse-half pairs.  The
+ * built-in choice takes kernels that hold tiles of whole pencils instead of
+ * walking them where pencils are short (up to 64 cells, up to 128 on grids
+ * of a few million cells); a value that is set selects the walk.
+ * mhd_get_launch reports the walk's chunk and, for the next two keys, what
+ * is chosen for the walking kernels: with tiles, MHD_TUNE_REVERSE 0 and
+ * MHD_TUNE_MIDDLE 0 run the reverse pairs, and in FP32 with van Leer's
+ * limiter the middle, as one launch each.
  * key MHD_TUNE_REVERSE: how the reverse-half pairs M_d F_d of a step and of
  * mhd_sweep(3..5) run: 1 = one fused launch per pair (the new faces stay
  * in registers; 9 launches per step), 2 = the two operators in turn (12

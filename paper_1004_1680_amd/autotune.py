@@ -74,14 +74,15 @@ def tune_solver(S, cfl=0.7, steps=4, repeats=2, use_cache=True):
     """Choose the march chunks of a Solver along y and z: those of the single
     operators and, when the reverse-half pairs run fused, those of the fused
     pairs (one parameter at a time, the others held).  Each candidate is
-    timed over `steps` steps, best of `repeats`.  Returns {key: chunk} with
-    keys (kind, axis), kind "op" or "pair"."""
+    timed over `steps` steps, best of `repeats`; 0 stands for the built-in
+    choice, which runs short pencils with the tile kernels.  Returns
+    {key: chunk} with keys (kind, axis), kind "op" or "pair"."""
     fused = S.reverse() == 1
     middle = S.launch(mhd.MHD_TUNE_MIDDLE) == 1
     kinds = ("op", "pair") if fused else ("op",)
     if middle:
         kinds += ("mid",)
-    key = (f"{_device_tag()}:single:{S.n[0]}x{S.n[1]}x{S.n[2]}:"
+    key = (f"{_device_tag()}:single+tiles:{S.n[0]}x{S.n[1]}x{S.n[2]}:"
            f"{'f64' if S.prec == mhd.MHD_F64 else 'f32'}:{'fused' if fused else 'separate'}"
            f"{':middle' if middle else ''}")
     setter = {"op": S.set_chunk, "pair": S.set_pair_chunk,
@@ -111,7 +112,7 @@ def tune_solver(S, cfl=0.7, steps=4, repeats=2, use_cache=True):
     for kind in kinds:
         for axis in ((2,) if kind == "mid" else (1, 2)):
             timings = {}
-            for ch in chunk_candidates(S.n[axis]):
+            for ch in [0] + chunk_candidates(S.n[axis]):
                 setter[kind](axis, ch)
                 timings[ch] = timed()
             best[(kind, axis)] = min(timings, key=timings.get)

@@ -41,6 +41,9 @@ struct LaunchTuning {
     int chunk[3];
     int pair_chunk[3];
     int triple_chunk[3];     // the same for M_d M_d F_d in one launch
+    // chunks the caller set (otherwise the built-in choice, which may be the
+    // tile kernels)
+    bool set_chunk[3], set_pair[3], set_triple[3];
     int wide;                // 1: 64-bit addressing in the marches even where 32-bit offsets fit
     int row_group;           // x sweeps: most rows (along y) in one group of the tile order (0: built-in)
 };
@@ -155,6 +158,10 @@ template <typename T>
 hipError_t launch_fluid(const SweepParams<T>& P, int d, const LaunchTuning& tune, hipStream_t s);
 template <typename T>
 bool fused_cfl_possible(int nx);
+// whether the built-in choice runs op (0 fluid, 1 magnetic, 2 magnetic then
+// fluid, 3 magnetic twice then fluid) along y or z with the tile kernels
+template <typename T>
+bool sweep_uses_tiles(const int n[3], int op, int d, const LaunchTuning& tune);
 template <typename T>
 hipError_t launch_magnetic(const SweepParams<T>& P, int d, const LaunchTuning& tune, hipStream_t s);
 // M_d then F_d in one pass, bitwise the two operators in turn; P.cfl_acc

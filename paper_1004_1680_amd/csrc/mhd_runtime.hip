@@ -126,6 +126,7 @@ static void default_tuning(mhd_ctx* h)
     h->tune.chunk[0] = h->tune.pair_chunk[0] = h->tune.triple_chunk[0] = 0;
     h->tune.wide = 0;
     h->tune.row_group = 0;
+    for (int d = 0; d < 3; ++d) h->tune.set_chunk[d] = h->tune.set_pair[d] = h->tune.set_triple[d] = false;
     for (int d = 1; d < 3; ++d) {
         const long npencil = (long)h->n[0] * h->n[3 - d];
         h->tune.chunk[d] = largest_chunk(h->n[d], npencil, 4);
@@ -608,7 +609,24 @@ static bool pairs_fused(const mhd_ctx* h)
     return h->rev_mode == 1 || (h->rev_mode == 0 && default_rev_fused(h->prec, h->limiter));
 }
 
-static bool mid_fused(const mhd_ctx* h);
+// the built-in choice runs operator o along axis d with the tile kernels
+static bool tiles(const mhd_ctx* h, int o, int d)
+{
+    return h->prec == MHD_F64 ? sweep_uses_tiles<double>(h->n, o, d, h->tune)
+                              : sweep_uses_tiles<float>(h->n, o, d, h->tune);
+}
+
+// the reverse pair along axis d runs as one launch: as pairs_fused says for
+// the marches, and, where the choice is the library's, wherever the tile
+// kernels run it (they spill with no limiter and in neither tier; FP64 64^3:
+// 16.5 us against 11.6 + 8.3 for the two operators)
+static bool pair_fused(const mhd_ctx* h, int d)
+{
+    if (pairs_fused(h)) return true;
+    return h->rev_mode == 0 && h->freeze == MHD_FREEZE_STEP && tiles(h, 2, d);
+}
+
+static bool mid_one_launch(const mhd_ctx* h);
 
 extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
 {
@@ -618,11 +636,11 @@ extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
     h->acc_valid = false;
     if (dim == 7) {
         // the middle of a step: M_z, then the reverse z pair
-        if (mid_fused(h)) {
+        if (mid_one_launch(h)) {
             HIP_TRY(h, op(h, 3, 2, nullptr));
         } else {
             HIP_TRY(h, op(h, 1, 2, nullptr));
-            if (pairs_fused(h)) {
+            if (pair_fused(h, 2)) {
                 HIP_TRY(h, op(h, 2, 2, nullptr));
             } else {
                 HIP_TRY(h, op(h, 1, 2, nullptr));
@@ -635,7 +653,7 @@ extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
         // the reverse x pair with the fused CFL of its result
         unsigned long long* acc = h->fuse_ok ? h->cfl_acc : nullptr;
         if (acc) HIP_TRY(h, launch_clear_acc(acc, h->stream));
-        if (pairs_fused(h)) {
+        if (pair_fused(h, 0)) {
             HIP_TRY(h, op(h, 2, 0, nullptr, acc));
         } else {
             HIP_TRY(h, op(h, 1, 0, nullptr));
@@ -648,7 +666,7 @@ extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
     if (dim < 3) {
         HIP_TRY(h, op(h, 0, d, nullptr));
         HIP_TRY(h, op(h, 1, d, nullptr));
-    } else if (pairs_fused(h)) {
+    } else if (pair_fused(h, d)) {
         HIP_TRY(h, op(h, 2, d, nullptr));
     } else {
         HIP_TRY(h, op(h, 1, d, nullptr));
@@ -670,14 +688,24 @@ static bool mid_fused(const mhd_ctx* h)
     return h->mid_mode == 1;
 }
 
+// the same with the tile kernels counted: where the library chooses and they
+// run the z axis, the middle is one launch at any size (16^3: 7.4 us against
+// 4.7 + 6.6 for M_z and the pair, 128^3: 46.6 against 17.8 + 33)
+static bool mid_one_launch(const mhd_ctx* h)
+{
+    if (mid_fused(h)) return true;
+    return h->mid_mode == 0 && pairs_fused(h) && h->limiter == MHD_LIMITER_VANLEER && h->prec == MHD_F32 &&
+           tiles(h, 3, 2);
+}
+
 // the 12 operators of a full step: x, y, z forward (fluid, magnetic), then
 // z, y, x reverse (magnetic, fluid), each reverse pair in one launch when
-// pairs_fused (9 launches), and M_z with the z pair in one when mid_fused
+// pair_fused (9 launches), and M_z with the z pair in one when mid_one_launch
 // (8 launches).  acc (nullable): the last operator (F_x) also accumulates
 // the CFL maximum of the state it leaves.
 static int enqueue_step_ops(mhd_ctx* h, const int* flag, unsigned long long* acc)
 {
-    const bool mid = mid_fused(h);
+    const bool mid = mid_one_launch(h);
     for (int d = 0; d < 3; ++d) {
         HIP_TRY(h, op(h, 0, d, flag));
         if (d == 2 && mid) {
@@ -687,7 +715,7 @@ static int enqueue_step_ops(mhd_ctx* h, const int* flag, unsigned long long* acc
         HIP_TRY(h, op(h, 1, d, flag));
     }
     for (int d = mid ? 1 : 2; d >= 0; --d) {
-        if (pairs_fused(h)) {
+        if (pair_fused(h, d)) {
             HIP_TRY(h, op(h, 2, d, flag, d == 0 ? acc : nullptr));
         } else {
             HIP_TRY(h, op(h, 1, d, flag));
@@ -903,6 +931,7 @@ extern "C" int mhd_set_launch(mhd_ctx* h, int key, int value)
     if (key != MHD_TUNE_CHUNK_Y && key != MHD_TUNE_CHUNK_Z && !pair && !triple)
         return fail(MHD_EINVAL, "unknown launch key %d", key);
     const int d = triple ? 2 : pair ? key - MHD_TUNE_PAIR_CHUNK_Y + 1 : key;   // axis 1 (y) or 2 (z)
+    bool* set = triple ? &h->tune.set_triple[d] : pair ? &h->tune.set_pair[d] : &h->tune.set_chunk[d];
     int* slot = triple ? &h->tune.triple_chunk[d] : pair ? &h->tune.pair_chunk[d] : &h->tune.chunk[d];
     if (value == 0) {
         const LaunchTuning keep = h->tune;
@@ -910,11 +939,13 @@ extern "C" int mhd_set_launch(mhd_ctx* h, int key, int value)
         const int v = *slot;
         h->tune = keep;
         *slot = v;
+        *set = false;
         return MHD_OK;
     }
     if (value < 8 || h->n[d] % value)
         return fail(MHD_EINVAL, "chunk %d must be >= 8 and divide the axis length %d", value, h->n[d]);
     *slot = value;
+    *set = true;
     return MHD_OK;
 }
 

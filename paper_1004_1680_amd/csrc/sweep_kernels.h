@@ -140,16 +140,80 @@ struct RowThread {
         tnext = inrow ? rloc * tpr + (tr == tpr - 1 ? 0 : tr + 1) : t;
         i0 = 4 * tr;
     }
+    static constexpr unsigned sd = 1;        // stride along the sweep axis
 };
+
+// The same for a tile of pencils along y or z: a workgroup holds tx whole
+// pencils (consecutive in the march kernels' pencil order, so lanes run
+// along x) of tg = nd / 4 threads each; thread t = lx + tx * g owns cells 4 g
+// .. 4 g + 3 of pencil tile * tx + lx.  Offsets are 32-bit element offsets.
+// Idle threads (past the last pencil, or past tx * tg) exchange with
+// themselves.
+template <int D> struct MarchGeom;
+template <int D>
+struct ColThread {
+    int t, tprev, tnext;
+    unsigned i0, inext, sd;  // offsets from the pencil's base: first cell, the cell after the four
+    unsigned pb[5];          // bases of pencils P, P-t1, P+t1, P-t2, P+t2
+    bool active;
+    __device__ __forceinline__ ColThread(int nx, int ny, int nz, int tile, int tx, int tg)
+    {
+        t = threadIdx.x;
+        const int g = t / tx, lx = t - g * tx;
+        const int npencil = nx * (D == 1 ? nz : ny);
+        const int p = tile * tx + lx;
+        const bool in = g < tg;
+        active = in && p < npencil;
+        const MarchGeom<D> G(nx, ny, nz, active ? p : 0);
+        sd = G.sd;
+        pb[0] = G.base; pb[1] = G.b_t1m; pb[2] = G.b_t1p; pb[3] = G.b_t2m; pb[4] = G.b_t2p;
+        tprev = in ? (g == 0 ? lx + tx * (tg - 1) : t - tx) : t;
+        tnext = in ? (g == tg - 1 ? lx : t + tx) : t;
+        i0 = active ? 4u * g * sd : 0u;
+        inext = g == tg - 1 ? 0u : i0 + 4u * sd;
+    }
+};
+
+// Four consecutive cells along the sweep axis d: one vector access along x,
+// four accesses a stride apart along y and z (the lanes of a wave then run
+// along x).  e: element offset of the first cell.
+template <typename T, int D, bool W32>
+struct Cells4 {
+    using RA = RowAddr<T, W32>;
+    using off = typename RA::off;
+    static __device__ __forceinline__ void load(const T* p, off e, unsigned sd, T o[4])
+    {
+        if constexpr (D == 0) vec4<T>::load(RA::at(p, e), o);
+        else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = *RA::at(p, e + (off)k * sd);
+        }
+    }
+    static __device__ __forceinline__ void store(T* p, off e, unsigned sd, const T o[4])
+    {
+        if constexpr (D == 0) vec4<T>::store(RA::at(p, e), o);
+        else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) *RA::at(p, e + (off)k * sd) = o[k];
+        }
+    }
+};
+
+// sweep-local fluid fields (rho, m_n, m_t1, m_t2, e) along axis D
+template <int D>
+__device__ __forceinline__ constexpr int local_field(int q)
+{
+    return q == 0 ? RHO : q == 4 ? EN : MX + (D + q - 1) % 3;
+}
 
 // Freezing speed of the 4 cells of a row thread for one stage (state w,
 // field bb): FRZ_STEP the step's c; FRZ_CELL |v_n| + c_fast of each cell;
 // FRZ_PENCIL the largest of those along the row, an all-reduce over the
 // row's threads by doubling windows in S (blockDim.x values of LDS, free
 // on entry; free again on return).  Every thread of the workgroup calls it.
-template <typename T, int FRZ>
+template <typename T, int FRZ, typename Thread>
 __device__ __forceinline__ void row_stage_speeds(const T (&w)[4][5], const T (&bb)[4][3], T gamma, T c,
-                                                 const RowThread& R, T* const S, T (&cs)[4])
+                                                 const Thread& R, T* const S, T (&cs)[4])
 {
     if constexpr (FRZ == FRZ_STEP) {
 #pragma unroll
@@ -174,15 +238,16 @@ __device__ __forceinline__ void row_stage_speeds(const T (&w)[4][5], const T (&b
     }
 }
 
-// x fluid operator from given inputs: U of the thread's 4 cells, the frozen
-// Bbar, and (CFL) the raw face values (own, next) of b_x, b_y, b_z for the
+// Fluid operator along axis D from given inputs (x: row tiles; y, z: pencil
+// tiles): U of the thread's 4 cells, the frozen Bbar, and (CFL) the raw face values (own, next) of b_x, b_y, b_z for the
 // fused CFL epilogue.  Stores the new U.  A: LDS of 25 values per thread.
 // Every thread of the workgroup calls it (it holds barriers).
 // CFL = true: the FP64 signal speed of every output cell, maximum per wave,
 // atomic maximum into P.cfl_acc; needs full waves (blockDim.x a multiple of
 // 64).
-template <typename T, bool CFL, int LIM = LIM_VANLEER, int FRZ = FRZ_STEP, bool W32 = false>
-__device__ __forceinline__ void fluid_x_core(const SweepParams<T>& P, const RowThread& R,
+template <typename T, int D, bool CFL, int LIM = LIM_VANLEER, int FRZ = FRZ_STEP, bool W32 = false,
+          typename Thread = RowThread>
+__device__ __forceinline__ void fluid_cells_core(const SweepParams<T>& P, const Thread& R,
                                              typename RowAddr<T, W32>::off base,
                                              const T (&u)[4][5], const T (&bb)[4][3],
                                              const T (&fb)[CFL ? 4 : 1][6], T* const A)
@@ -271,7 +336,7 @@ __device__ __forceinline__ void fluid_x_core(const SweepParams<T>& P, const RowT
             T o[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) o[k] = sub_scaled(u[k][q], tau, phi[k][q] - (k > 0 ? phi[k - 1][q] : phiprev));
-            vec4<T>::store(RowAddr<T, W32>::at(P.out[q], base + R.i0), o);
+            Cells4<T, D, W32>::store(P.out[local_field<D>(q)], base + R.i0, R.sd, o);
             if constexpr (CFL)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) onew[k][q] = o[k];
@@ -457,7 +522,7 @@ __device__ __forceinline__ void fluid_x_tile(const SweepParams<T>& P, int tile, 
 #pragma unroll
             for (int k = 0; k < 4; ++k) { fb[k][4] = tmp[k]; fb[k][5] = tmp2[k]; }
     }
-    fluid_x_core<T, CFL, LIM, FRZ, W32>(P, R, base, u, bb, fb, A);
+    fluid_cells_core<T, 0, CFL, LIM, FRZ, W32>(P, R, base, u, bb, fb, A);
 }
 
 template <typename T, bool CFL, int LIM = LIM_VANLEER, int FRZ = FRZ_STEP, bool W32 = false>
@@ -468,75 +533,65 @@ __global__ void __launch_bounds__(256) fluid_x_kernel(SweepParams<T> P, int tpr,
     fluid_x_tile<T, CFL, LIM, FRZ, W32>(P, tile, tpr, rows_per_wg, reinterpret_cast<T*>(smem_raw));
 }
 
-// Magnetic operator along x (e = y then z) of the thread's 4 cells.  For
-// each e two edge-flux chains are evaluated: "own" (edges of this row,
-// velocity from rows P and P-e) and "plus" (edges of row P+e, velocity from
-// rows P+e and P), the latter for the constraint update of b_x; a plus
-// chain is the own chain of the neighbour row, evaluated identically.
-// Gives the new faces nb = (b_y of P, b_y of P+y, b_z of P, b_z of P+z, b_x
-// of P) of the 4 cells; stores nothing.  own (optional): rho and m_x of
-// the thread's 4 cells as loaded.  A: LDS of 16 values per thread.
-// Every thread of the workgroup calls it (it holds barriers).
-template <typename T, int LIM = LIM_VANLEER, bool W32 = false>
-__device__ __forceinline__ void mag_x_core(const SweepParams<T>& P, const RowThread& R, T (&nb)[5][4],
-                                           T* const A, T (*own)[4] = nullptr)
+// Magnetic operator along axis D (e = t1 then t2; y then z for D = x) of the
+// thread's 4 cells.  For each e two edge-flux chains are evaluated: "own"
+// (edges of this pencil, velocity from pencils P and P-e) and "plus" (edges
+// of pencil P+e, velocity from P+e and P), the latter for the constraint
+// update of b_n; a plus chain is the own chain of the neighbour pencil,
+// evaluated identically.  Chains: 0 own-t1, 1 plus-t1, 2 own-t2, 3 plus-t2.
+// Two parts, so that a second operator over the same velocity field can
+// take the first one's edge velocities and new faces:
+//
+// mag_cells_load: the edge velocities a(k+1/2) of the chains, their fields q
+// at the thread's 4 cells and (q4) the next one, b_n of the 4 cells.  pb:
+// offsets of pencils P, P-t1, P+t1, P-t2, P+t2.  own (optional): rho and m_n
+// of the thread's 4 cells as loaded.  A: LDS of 9 values per thread.
+template <typename T, int D, bool W32, typename Thread>
+__device__ __forceinline__ void mag_cells_load(const SweepParams<T>& P, const Thread& R,
+                                               const typename RowAddr<T, W32>::off (&pb)[5], T (&a)[4][4],
+                                               T (&q)[4][5], T* const A, T (*own)[4])
 {
-    using RA = RowAddr<T, W32>;
-    using off = typename RA::off;
-    T* const B = A + 12 * blockDim.x;                       // A: 12, B: 4 values / thread
+    using C = Cells4<T, D, W32>;
+    constexpr int N_ = D, T1 = (D + 1) % 3, T2 = (D + 2) % 3;
     const int nt = blockDim.x;
-    const int nx = P.nx, ny = P.ny, nz = P.nz;
-    const int t = R.t, tprev = R.tprev, tnext = R.tnext, i0 = R.i0, y = R.y, z = R.z;
+    const int t = R.t, tnext = R.tnext;
     const bool active = R.active;
-    auto rbase = [&](int yy, int zz) -> off {
-        return RA::row(nx, ny, wrapi(yy, ny), wrapi(zz, nz));
-    };
-    const off b0 = rbase(y, z);
-    T tau, halftau, cdummy;
-    step_scalars(P, tau, halftau, cdummy);
-
-    // velocity v_x at 5 positions (i0..i0+4) of the rows P, P-y, P+y, P-z, P+z
-    // rows index: 0 P, 1 P-y, 2 P+y, 3 P-z, 4 P+z
+    // velocity v_n at 5 positions of the pencils P, P-t1, P+t1, P-t2, P+t2
     T v[5][5];
-    {
-        const off rb[5] = { b0, rbase(y - 1, z), rbase(y + 1, z), rbase(y, z - 1), rbase(y, z + 1) };
 #pragma unroll
-        for (int r = 0; r < 5; ++r) {
-            T rho[4], m[4];
-            if (active) {
-                vec4<T>::load(RA::at(P.in[RHO], rb[r] + i0), rho);
-                vec4<T>::load(RA::at(P.in[MX], rb[r] + i0), m);
-            } else {
-                rho[0] = rho[1] = rho[2] = rho[3] = T(1);
-                m[0] = m[1] = m[2] = m[3] = T(0);
-            }
+    for (int r = 0; r < 5; ++r) {
+        T rho[4], m[4];
+        if (active) {
+            C::load(P.in[RHO], pb[r] + R.i0, R.sd, rho);
+            C::load(P.in[MX + N_], pb[r] + R.i0, R.sd, m);
+        } else {
+            rho[0] = rho[1] = rho[2] = rho[3] = T(1);
+            m[0] = m[1] = m[2] = m[3] = T(0);
+        }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[r][k] = velocity(m[k], rho[k]);
-            if (r == 0 && own) {                  // rho and m_x of the thread's own cells
+        for (int k = 0; k < 4; ++k) v[r][k] = velocity(m[k], rho[k]);
+        if (r == 0 && own) {                  // rho and m_n of the thread's own cells
 #pragma unroll
-                for (int k = 0; k < 4; ++k) { own[0][k] = rho[k]; own[1][k] = m[k]; }
-            }
+            for (int k = 0; k < 4; ++k) { own[0][k] = rho[k]; own[1][k] = m[k]; }
         }
     }
-    // chains: 0 own-y, 1 plus-y, 2 own-z, 3 plus-z
-    // velocity rows of each chain: (pencil, pencil - e)
+    // velocity pencils of each chain: (pencil, pencil - e)
     const int vr0[4] = { 0, 2, 0, 4 };
     const int vr1[4] = { 1, 0, 3, 0 };
-    T q[4][5];
     {
-        const off qb[4] = { b0, rbase(y + 1, z), b0, rbase(y, z + 1) };
-        const int qf[4] = { BY, BY, BZ, BZ };
+        const int qp[4] = { 0, 2, 0, 4 };
+        const int qf[4] = { BX + T1, BX + T1, BX + T2, BX + T2 };
 #pragma unroll
         for (int ch = 0; ch < 4; ++ch) {
             T tmp[4];
-            if (active) vec4<T>::load(RA::at(P.in[qf[ch]], qb[ch] + i0), tmp);
+            if (active) C::load(P.in[qf[ch]], pb[qp[ch]] + R.i0, R.sd, tmp);
             else tmp[0] = tmp[1] = tmp[2] = tmp[3] = T(0);
 #pragma unroll
             for (int k = 0; k < 4; ++k) q[ch][k] = tmp[k];
         }
     }
     // exchange 0: the next cell's velocities and q (the next thread's first
-    // cell; the row wraps) through LDS rather than loaded and divided again
+    // cell; the pencil wraps) through LDS rather than loaded and divided again
 #pragma unroll
     for (int r = 0; r < 5; ++r) A[r * nt + t] = v[r][0];
 #pragma unroll
@@ -546,18 +601,33 @@ __device__ __forceinline__ void mag_x_core(const SweepParams<T>& P, const RowThr
     for (int r = 0; r < 5; ++r) v[r][4] = A[r * nt + tnext];
 #pragma unroll
     for (int ch = 0; ch < 4; ++ch) q[ch][4] = A[(5 + ch) * nt + tnext];
-    T a[4][4], g[4][4];
 #pragma unroll
     for (int ch = 0; ch < 4; ++ch) {
         T w[5];
 #pragma unroll
         for (int k = 0; k < 5; ++k) w[k] = face_avg(v[vr0[ch]][k], v[vr1[ch]][k]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            a[ch][k] = edge_avg(w[k], w[k + 1]);
-            g[ch][k] = upwind_flux1(a[ch][k], q[ch][k], q[ch][k + 1]);
-        }
+        for (int k = 0; k < 4; ++k) a[ch][k] = edge_avg(w[k], w[k + 1]);
     }
+}
+
+// mag_cells_update: from edge velocities a, chain fields q and bn() (called
+// late: b_n of the 4 cells) the new faces nb = (b_t1 of P, b_t1 of P+t1, b_t2
+// of P, b_t2 of P+t2, b_n of P) of the 4 cells; stores nothing.  A: LDS of
+// 16 values per thread.  Every thread of the workgroup calls both (they hold
+// barriers).
+template <typename T, int LIM, typename Thread, typename Bn>
+__device__ __forceinline__ void mag_cells_update(const Thread& R, T tau, T halftau, const T (&a)[4][4],
+                                                 const T (&q)[4][5], Bn bn, T (&nb)[5][4], T* const A)
+{
+    T* const B = A + 12 * blockDim.x;                       // A: 12, B: 4 values / thread
+    const int nt = blockDim.x;
+    const int t = R.t, tprev = R.tprev, tnext = R.tnext;
+    T g[4][4];
+#pragma unroll
+    for (int ch = 0; ch < 4; ++ch)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) g[ch][k] = upwind_flux1(a[ch][k], q[ch][k], q[ch][k + 1]);
     // exchange 1: last first-order flux -> next thread
 #pragma unroll
     for (int ch = 0; ch < 4; ++ch) B[ch * nt + t] = g[ch][3];
@@ -600,23 +670,53 @@ __device__ __forceinline__ void mag_x_core(const SweepParams<T>& P, const RowThr
     T fprev[4];
 #pragma unroll
     for (int ch = 0; ch < 4; ++ch) fprev[ch] = B[ch * nt + tprev];
-    T bx[4];
-    if (active) vec4<T>::load(RA::at(P.in[BX], b0 + i0), bx);
-    else bx[0] = bx[1] = bx[2] = bx[3] = T(0);
+    T bn4[4];
+    bn(bn4);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const T fo_y = k > 0 ? f[0][k - 1] : fprev[0];
-        const T fp_y = k > 0 ? f[1][k - 1] : fprev[1];
-        const T fo_z = k > 0 ? f[2][k - 1] : fprev[2];
-        const T fp_z = k > 0 ? f[3][k - 1] : fprev[3];
+        const T fo_1 = k > 0 ? f[0][k - 1] : fprev[0];
+        const T fp_1 = k > 0 ? f[1][k - 1] : fprev[1];
+        const T fo_2 = k > 0 ? f[2][k - 1] : fprev[2];
+        const T fp_2 = k > 0 ? f[3][k - 1] : fprev[3];
 #pragma unroll
         for (int ch = 0; ch < 4; ++ch) {
             const T fo = k > 0 ? f[ch][k - 1] : fprev[ch];
             nb[ch][k] = sub_scaled(q[ch][k], tau, f[ch][k] - fo);
         }
-        const T b = add_scaled(bx[k], tau, fp_y - fo_y);
-        nb[4][k] = add_scaled(b, tau, fp_z - fo_z);
+        const T b = add_scaled(bn4[k], tau, fp_1 - fo_1);
+        nb[4][k] = add_scaled(b, tau, fp_2 - fo_2);
     }
+}
+
+// offsets of a row thread's pencils P, P-y, P+y, P-z, P+z
+template <typename T, bool W32>
+__device__ __forceinline__ void row_pencils(const SweepParams<T>& P, const RowThread& R,
+                                            typename RowAddr<T, W32>::off (&pb)[5])
+{
+    using RA = RowAddr<T, W32>;
+    const int ny = P.ny, nz = P.nz, y = R.y, z = R.z;
+    pb[0] = RA::row(P.nx, ny, y, z);
+    pb[1] = RA::row(P.nx, ny, wrapi(y - 1, ny), z);
+    pb[2] = RA::row(P.nx, ny, wrapi(y + 1, ny), z);
+    pb[3] = RA::row(P.nx, ny, y, wrapi(z - 1, nz));
+    pb[4] = RA::row(P.nx, ny, y, wrapi(z + 1, nz));
+}
+
+// Magnetic operator of a row thread's 4 cells (the two parts in turn)
+template <typename T, int LIM = LIM_VANLEER, bool W32 = false>
+__device__ __forceinline__ void mag_x_core(const SweepParams<T>& P, const RowThread& R, T (&nb)[5][4],
+                                           T* const A, T (*own)[4] = nullptr)
+{
+    typename RowAddr<T, W32>::off pb[5];
+    row_pencils<T, W32>(P, R, pb);
+    T tau, halftau, cdummy;
+    step_scalars(P, tau, halftau, cdummy);
+    T a[4][4], q[4][5];
+    mag_cells_load<T, 0, W32>(P, R, pb, a, q, A, own);
+    mag_cells_update<T, LIM>(R, tau, halftau, a, q, [&](T (&bx)[4]) {
+        if (R.active) vec4<T>::load(RowAddr<T, W32>::at(P.in[BX], pb[0] + R.i0), bx);
+        else bx[0] = bx[1] = bx[2] = bx[3] = T(0);
+    }, nb, A);
 }
 
 // One tile of rows_per_wg rows of one grid: magnetic operator M_x.
@@ -723,7 +823,7 @@ __device__ __forceinline__ void magfluid_x_tile(const SweepParams<T>& P, int til
 #pragma unroll
         for (int k = 0; k < 4; ++k) { u[k][0] = own[0][k]; u[k][1] = own[1][k]; }
     }
-    fluid_x_core<T, CFL, LIM, FRZ_STEP, W32>(P, R, base, u, bb, fb, A);
+    fluid_cells_core<T, 0, CFL, LIM, FRZ_STEP, W32>(P, R, base, u, bb, fb, A);
 }
 
 template <typename T, bool CFL, int LIM = LIM_VANLEER, bool W32 = false>
@@ -1521,6 +1621,208 @@ __global__ void __launch_bounds__(256, 1) magmagfluid_march_kernel(SweepParams<T
 }
 
 // ---------------------------------------------------------------------------
+// y and z sweeps of short pencils: tile kernels
+// ---------------------------------------------------------------------------
+// The row kernels' scheme along y and z: a workgroup holds tx whole pencils
+// (ColThread), 4 consecutive cells of a pencil per thread, the stencil
+// neighbours of other threads through LDS.  A march walks a pencil position
+// by position, each one a dependent chain of some hundred instructions
+// behind a load, so on grids that give a SIMD a wave or less its time is
+// (chunk + warm-up) times that latency whatever the grid; here every cell of
+// a pencil is in flight at once.  Same device functions on the same values
+// as the marches, so the results are bitwise theirs.
+
+// b of the thread's 4 cells at pencils P and P+e averaged: Bbar_e
+template <typename T, int D, bool W32>
+__device__ __forceinline__ void face_mean4(const T* b, typename RowAddr<T, W32>::off o0,
+                                           typename RowAddr<T, W32>::off o1, unsigned sd, bool active, T (&m)[4])
+{
+    T lo[4], hi[4];
+    if (active) {
+        Cells4<T, D, W32>::load(b, o0, sd, lo);
+        Cells4<T, D, W32>::load(b, o1, sd, hi);
+    } else lo[0] = lo[1] = lo[2] = lo[3] = hi[0] = hi[1] = hi[2] = hi[3] = T(0);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) m[k] = T(0.5) * (lo[k] + hi[k]);
+}
+
+// the operator skipped under a record: fields [f0, f1) copied
+template <typename T, int D>
+__device__ __forceinline__ void tile_copy(const SweepParams<T>& P, const ColThread<D>& R, int f0, int f1)
+{
+    if (!R.active) return;
+    for (int f = f0; f < f1; ++f) {
+        T v[4];
+        Cells4<T, D, true>::load(P.in[f], R.pb[0] + R.i0, R.sd, v);
+        Cells4<T, D, true>::store(P.out[f], R.pb[0] + R.i0, R.sd, v);
+    }
+}
+
+// U of the thread's 4 cells in sweep-local order, from local field q0 on
+// (inactive threads: ones, a harmless state)
+template <typename T, int D>
+__device__ __forceinline__ void tile_load_u(const SweepParams<T>& P, const ColThread<D>& R, int q0, T (&u)[4][5])
+{
+    T tmp[4];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        if (q < q0) continue;
+        if (R.active) Cells4<T, D, true>::load(P.in[local_field<D>(q)], R.pb[0] + R.i0, R.sd, tmp);
+        else tmp[0] = tmp[1] = tmp[2] = tmp[3] = T(1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) u[k][q] = tmp[k];
+    }
+}
+
+// fluid operator F_d of one tile of pencils; A: LDS of 25 values per thread
+template <typename T, int D, int LIM>
+__device__ __forceinline__ void fluid_tile(const SweepParams<T>& P, int tile, int tx, int tg, T* const A)
+{
+    constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+    const ColThread<D> R(P.nx, P.ny, P.nz, tile, tx, tg);
+    if (P.flag && *P.flag) {
+        tile_copy<T, D>(P, R, RHO, BX);
+        return;
+    }
+    const unsigned o = R.pb[0] + R.i0;
+    T u[4][5], bb[4][3];
+    tile_load_u<T, D>(P, R, 0, u);
+    {
+        T m[4], bn[4], bnn = T(0);
+        if (R.active) {
+            Cells4<T, D, true>::load(P.in[BX + D], o, R.sd, bn);
+            bnn = *RowAddr<T, true>::at(P.in[BX + D], R.pb[0] + R.inext);
+        } else bn[0] = bn[1] = bn[2] = bn[3] = T(0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bb[k][0] = T(0.5) * (bn[k] + (k < 3 ? bn[k + 1] : bnn));
+        face_mean4<T, D, true>(P.in[BX + T1], o, R.pb[2] + R.i0, R.sd, R.active, m);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bb[k][1] = m[k];
+        face_mean4<T, D, true>(P.in[BX + T2], o, R.pb[4] + R.i0, R.sd, R.active, m);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bb[k][2] = m[k];
+    }
+    const T fb[1][6] = {};
+    fluid_cells_core<T, D, false, LIM, FRZ_STEP, true>(P, R, R.pb[0], u, bb, fb, A);
+}
+
+template <typename T, int D>
+__device__ __forceinline__ void tile_store_b(const SweepParams<T>& P, const ColThread<D>& R, const T (&nb)[5][4])
+{
+    constexpr int T1 = (D + 1) % 3, T2 = (D + 2) % 3;
+    if (!R.active) return;
+    const unsigned o = R.pb[0] + R.i0;
+    Cells4<T, D, true>::store(P.out[BX + T1], o, R.sd, nb[0]);
+    Cells4<T, D, true>::store(P.out[BX + T2], o, R.sd, nb[2]);
+    Cells4<T, D, true>::store(P.out[BX + D], o, R.sd, nb[4]);
+}
+
+// Magnetic operator M_d of one tile of pencils, or (TWICE) M_d M_d: the
+// second takes the first one's new faces (P, P+t1, P+t2: everything it reads
+// of b) and edge velocities from registers.  A: LDS of 16 values per thread.
+template <typename T, int D, int LIM, bool TWICE>
+__device__ __forceinline__ void mag_tile_core(const SweepParams<T>& P, const ColThread<D>& R, T (&nb)[5][4],
+                                              T* const A, T (*own)[4])
+{
+    T tau, halftau, cdummy;
+    step_scalars(P, tau, halftau, cdummy);
+    T a[4][4], q[4][5];
+    mag_cells_load<T, D, true>(P, R, R.pb, a, q, A, own);
+    mag_cells_update<T, LIM>(R, tau, halftau, a, q, [&](T (&bn)[4]) {
+        if (R.active) Cells4<T, D, true>::load(P.in[BX + D], R.pb[0] + R.i0, R.sd, bn);
+        else bn[0] = bn[1] = bn[2] = bn[3] = T(0);
+    }, nb, A);
+    if constexpr (TWICE) {
+        const int nt = blockDim.x;
+        T bn1[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            bn1[k] = nb[4][k];
+#pragma unroll
+            for (int ch = 0; ch < 4; ++ch) q[ch][k] = nb[ch][k];
+        }
+        // the next cell's new faces (region A was last read before the
+        // previous barrier; this barrier also separates the reads of region
+        // B from the second operator's writes)
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) A[ch * nt + R.t] = q[ch][0];
+        __syncthreads();
+#pragma unroll
+        for (int ch = 0; ch < 4; ++ch) q[ch][4] = A[ch * nt + R.tnext];
+        mag_cells_update<T, LIM>(R, tau, halftau, a, q, [&](T (&bn)[4]) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) bn[k] = bn1[k];
+        }, nb, A);
+    }
+}
+
+template <typename T, int D, int LIM>
+__device__ __forceinline__ void mag_tile(const SweepParams<T>& P, int tile, int tx, int tg, T* const A)
+{
+    const ColThread<D> R(P.nx, P.ny, P.nz, tile, tx, tg);
+    if (P.flag && *P.flag) {
+        tile_copy<T, D>(P, R, BX, NFIELD);
+        return;
+    }
+    T nb[5][4];
+    mag_tile_core<T, D, LIM, false>(P, R, nb, A, nullptr);
+    tile_store_b<T, D>(P, R, nb);
+}
+
+// M_d (TWICE: M_d M_d) then F_d of one tile of pencils in one pass, as
+// magfluid_x_tile; A: LDS of 25 values per thread
+template <typename T, int D, int LIM, bool TWICE>
+__device__ __forceinline__ void magfluid_tile(const SweepParams<T>& P, int tile, int tx, int tg, T* const A)
+{
+    const ColThread<D> R(P.nx, P.ny, P.nz, tile, tx, tg);
+    if (P.flag && *P.flag) {
+        tile_copy<T, D>(P, R, RHO, NFIELD);
+        return;
+    }
+    T nb[5][4], own[2][4];
+    mag_tile_core<T, D, LIM, TWICE>(P, R, nb, A, own);
+    // new b_n of the first cell -> previous thread
+    T* const X = A + 20 * blockDim.x;
+    X[R.t] = nb[4][0];
+    __syncthreads();
+    const T bnn = X[R.tnext];
+    tile_store_b<T, D>(P, R, nb);
+    T u[4][5], bb[4][3];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        bb[k][0] = T(0.5) * (nb[4][k] + (k < 3 ? nb[4][k + 1] : bnn));
+        bb[k][1] = T(0.5) * (nb[0][k] + nb[1][k]);
+        bb[k][2] = T(0.5) * (nb[2][k] + nb[3][k]);
+    }
+    tile_load_u<T, D>(P, R, 2, u);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { u[k][0] = own[0][k]; u[k][1] = own[1][k]; }
+    const T fb[1][6] = {};
+    fluid_cells_core<T, D, false, LIM, FRZ_STEP, true>(P, R, R.pb[0], u, bb, fb, A);
+}
+
+// op 0 fluid, 1 magnetic, 2 magnetic then fluid, 3 magnetic twice then fluid
+template <typename T, int OP, int D, int LIM>
+__device__ __forceinline__ void sweep_tile(const SweepParams<T>& P, int tile, int tx, int tg, T* const A)
+{
+    if constexpr (OP == 0) fluid_tile<T, D, LIM>(P, tile, tx, tg, A);
+    else if constexpr (OP == 1) mag_tile<T, D, LIM>(P, tile, tx, tg, A);
+    else magfluid_tile<T, D, LIM, OP == 3>(P, tile, tx, tg, A);
+}
+
+constexpr int TILE_THREADS = 512;            // most threads of a tile's workgroup
+
+// FP32: fluid 112 VGPRs (4 waves per SIMD), magnetic 73 (6), pair 127 (4,
+// the march's two windows 2), middle 139 (3, the march's three 1); FP64:
+// fluid 246 (2), magnetic 146 (3), pair 244 (2; the march spills at 1)
+template <typename T, int OP, int D, int LIM>
+__global__ void __launch_bounds__(TILE_THREADS) sweep_tile_kernel(SweepParams<T> P, int tx, int tg)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    sweep_tile<T, OP, D, LIM>(P, xcd_tile(gridDim.x), tx, tg, reinterpret_cast<T*>(smem_raw));
+}
+
+// ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
 
@@ -1548,6 +1850,74 @@ inline bool offsets32(const SweepParams<T>& P, const LaunchTuning& tune)
     return !tune.wide && (unsigned long long)P.nx * P.ny * P.nz * sizeof(T) <= (1ull << 32);
 }
 
+// Shape of a tile launch along axis d: tx pencils of tg = nd / 4 threads, and
+// whether the built-in choice takes it (OP as in sweep_tile) rather than the
+// march.  Measured against the best march chunk (FP32, us, tile / march):
+//   16^3     F 5.1 / 10.8   M 4.7 / 7.5   pair 6.6 / 20   middle 7.4 / 31
+//   64^3     F 8.1 / 17     M 6.8 / 11    pair 10.5 / 29  middle 11.7 / 38
+//   128^3    F 25.5 / 27    M 17.8 / 16.5 pair 33 / 42    middle 46.6 / 57
+//   256x64x256 (y)  F 40 / 48    M 28 / 30   pair 54 / 68
+//   256x128x256 (y) F 112 / 107  M 52 / 47   pair 155 / 136
+// A march costs (chunk + warm-up) positions of latency, so it loses wherever
+// its waves do not fill the SIMDs; past 64 cells per pencil the tile's
+// workgroup is so large that few are resident on a CU, and on grids that
+// stream from HBM that costs more than the march's warm-up.  FP64 windows
+// and tiles hold half the waves per SIMD: the same at 64 cells (F 11.6 / 23,
+// M 8.3 / 15.5, pair 16.5 / 37 at 64^3), 8 pencils (64 bytes) per tile above
+// (128^3: pair 94 / 97, F 55 / 58, M 37 / 37).
+struct TileShape {
+    int tx, tg, threads, grid;
+};
+template <typename T>
+inline bool tile_shape(const int n[3], int op, int d, const LaunchTuning& tune, TileShape& ts)
+{
+    const bool* set = op == 3 ? tune.set_triple : op == 2 ? tune.set_pair : tune.set_chunk;
+    const unsigned long long cells = (unsigned long long)n[0] * n[1] * n[2];
+    if (d == 0 || set[d] || tune.wide || cells * sizeof(T) > (1ull << 32)) return false;
+    const int nd = n[d], npencil = n[0] * n[3 - d];
+    constexpr unsigned long long M = 1ull << 20;
+    const bool f32 = sizeof(T) == 4;
+    const bool use = op == 0 ? nd <= 64 || (f32 && nd <= 128 && cells <= 5 * M / 2)
+                   : op == 1 ? nd <= 64 && cells <= 2 * M
+                             : nd <= 64 || (nd <= 128 && cells <= (f32 ? 9 * M / 2 : 9 * M / 4));
+    if (!use) return false;
+    ts.tg = nd / 4;
+    // 64 bytes of consecutive x per load: 16 pencils (FP64 pencils over 64
+    // cells: 8), more for short pencils so that a workgroup has a full wave,
+    // and 256 threads where a million cells leave enough workgroups (M_y of
+    // 256x32x256: 15.6 us with 32 pencils, 17.8 with 16; 48^3 the other way)
+    ts.tx = !f32 && nd > 64 ? 8 : 16;
+    const int least = cells >= M ? 256 : 64;
+    if (ts.tx * ts.tg < least) ts.tx = least / ts.tg;
+    ts.threads = ts.tx * ts.tg;
+    ts.grid = (npencil + ts.tx - 1) / ts.tx;
+    return ts.threads <= TILE_THREADS;
+}
+template <typename T>
+bool sweep_uses_tiles(const int n[3], int op, int d, const LaunchTuning& tune)
+{
+    TileShape ts;
+    return tile_shape<T>(n, op, d, tune, ts);
+}
+template <typename T>
+inline bool tile_shape(const SweepParams<T>& P, int op, int d, const LaunchTuning& tune, TileShape& ts)
+{
+    const int n[3] = { P.nx, P.ny, P.nz };
+    return tile_shape<T>(n, op, d, tune, ts);
+}
+
+template <typename T, int OP, int LIM>
+inline void launch_tile(const SweepParams<T>& P, int d, const TileShape& ts, hipStream_t s)
+{
+    const size_t lds = sizeof(T) * (OP == 1 ? 16 : 25) * ts.threads;
+    if constexpr (OP != 3) {                 // the middle of a step runs along z
+        if (d == 1) {
+            hipLaunchKernelGGL((sweep_tile_kernel<T, OP, 1, LIM>), dim3(ts.grid), dim3(ts.threads), lds, s, P, ts.tx, ts.tg);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((sweep_tile_kernel<T, OP, 2, LIM>), dim3(ts.grid), dim3(ts.threads), lds, s, P, ts.tx, ts.tg);
+}
 
 template <typename T, int LIM, int FRZ = FRZ_STEP>
 hipError_t launch_fluid_lim(const SweepParams<T>& P, int d, const LaunchTuning& tune, hipStream_t s)
@@ -1578,6 +1948,13 @@ hipError_t launch_fluid_lim(const SweepParams<T>& P, int d, const LaunchTuning& 
         const int nd = d == 1 ? P.ny : P.nz;
         const int npencil = P.nx * (d == 1 ? P.nz : P.ny);
         int chunk = tune.chunk[d];
+        if constexpr (FRZ == FRZ_STEP) {
+            TileShape ts;
+            if (tile_shape(P, 0, d, tune, ts)) {
+                launch_tile<T, 0, LIM>(P, d, ts, s);
+                return hipGetLastError();
+            }
+        }
         // the pencil variant reads its whole pencil twice before marching:
         // one chunk per pencil
         if (chunk <= 0 || nd % chunk || FRZ == FRZ_PENCIL) chunk = nd;
@@ -1612,6 +1989,11 @@ hipError_t launch_magnetic_lim(const SweepParams<T>& P, int d, const LaunchTunin
         const int nd = d == 1 ? P.ny : P.nz;
         const int npencil = P.nx * (d == 1 ? P.nz : P.ny);
         int chunk = tune.chunk[d];
+        TileShape ts;
+        if (tile_shape(P, 1, d, tune, ts)) {
+            launch_tile<T, 1, LIM>(P, d, ts, s);
+            return hipGetLastError();
+        }
         if (chunk <= 0 || nd % chunk) chunk = nd;
         const long lanes = (long)npencil * (nd / chunk);
         const int grid = (int)((lanes + 255) / 256);
@@ -1690,6 +2072,11 @@ hipError_t launch_magfluid_lim(const SweepParams<T>& P, int d, const LaunchTunin
         const int nd = d == 1 ? P.ny : P.nz;
         const int npencil = P.nx * (d == 1 ? P.nz : P.ny);
         int chunk = tune.pair_chunk[d];
+        TileShape ts;
+        if (tile_shape(P, 2, d, tune, ts)) {
+            launch_tile<T, 2, LIM>(P, d, ts, s);
+            return hipGetLastError();
+        }
         if (chunk <= 0 || nd % chunk) chunk = nd;
         const long lanes = (long)npencil * (nd / chunk);
         const int grid = (int)((lanes + 255) / 256);
@@ -1724,6 +2111,13 @@ hipError_t launch_magmagfluid(const SweepParams<T>& P, int d, const LaunchTuning
     const int nd = d == 1 ? P.ny : P.nz;
     const int npencil = P.nx * (d == 1 ? P.nz : P.ny);
     int chunk = tune.triple_chunk[d];
+    if constexpr (sizeof(T) == 4) {          // (the FP64 tile would spill)
+        TileShape ts;
+        if (d == 2 && tile_shape(P, 3, d, tune, ts)) {
+            launch_tile<T, 3, LIM_VANLEER>(P, d, ts, s);
+            return hipGetLastError();
+        }
+    }
     if (chunk <= 0 || nd % chunk) chunk = nd;
     const long lanes = (long)npencil * (nd / chunk);
     const int grid = (int)((lanes + 255) / 256);
