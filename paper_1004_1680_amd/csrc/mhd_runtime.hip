@@ -105,33 +105,48 @@ static void current_fields(mhd_ctx* h, const T* f[8])
     for (int q = 0; q < 8; ++q) f[q] = field_ptr<T>(h, q, h->cur[q]);
 }
 
-static int largest_chunk(int nd, long npencil, int waves_per_simd)
+// Built-in march chunk of a pencil of nd cells: the divisor (>= 8) with the
+// least estimated time.  A lane walks chunk + warm positions (rounded up to
+// the unrolled group); the launch gives each of the 256 CUs at most m
+// workgroups (one wave per SIMD each), `resident` of them at a time, in
+// ceil(m / resident) rounds.  A position costs about m issue slots per SIMD
+// plus half a slot of latency per round (fluid march, cache-resident: 0.63,
+// 1.1, 2.1 us per position at m = 1, 2, 4).  So a chunk that leaves the last
+// round nearly empty, or one whose warm-up outweighs the lanes it adds,
+// loses.  Against the earlier rule (the longest chunk with lanes for every
+// wave slot), us along y: 160^3 fluid 42.5 from 52.2, magnetic 26.5 from
+// 29.7, pair 65 from 102, middle 98 from 119; 192^3 magnetic 41.5 from 48,
+// pair 124 from 143, middle 163 from 224; 256^3 fluid 198 from 218 (z 173
+// from 206), magnetic 131 from 136; 512^3 fluid 1435 from 1537.
+static int march_chunk(int nd, long npencil, int warm, int unroll, int resident)
 {
-    // enough lanes to give every SIMD of the 256 CUs the waves it can hold,
-    // with a chunk no shorter than 16 cells (the warm-up re-reads 6 cells)
-    const long target = 256L * 4 * waves_per_simd * 64;
     int best = nd;
-    for (int ch = nd; ch >= 16; --ch) {
+    double least = 0.0;
+    for (int ch = nd; ch >= 8; --ch) {
         if (nd % ch) continue;
-        best = ch;
-        if (npencil * (nd / ch) >= target) break;
+        const long wgs = (npencil * (nd / ch) + 255) / 256;
+        const long m = (wgs + 255) / 256, rounds = (m + resident - 1) / resident;
+        const int pos = (ch + warm + unroll - 1) / unroll * unroll;
+        const double cost = pos * ((double)m + 0.5 * (double)rounds);
+        if (ch == nd || cost < least) { best = ch; least = cost; }
     }
     return best;
 }
 
 static void default_tuning(mhd_ctx* h)
 {
-    // the fused reverse-pair march holds two register windows: half the
-    // waves per SIMD, so half the lanes fill the device
     h->tune.chunk[0] = h->tune.pair_chunk[0] = h->tune.triple_chunk[0] = 0;
     h->tune.wide = 0;
     h->tune.row_group = 0;
     for (int d = 0; d < 3; ++d) h->tune.set_chunk[d] = h->tune.set_pair[d] = h->tune.set_triple[d] = false;
+    // warm-up positions, unrolled group and waves per SIMD of the marches
+    // (the fluid march's for both single operators)
+    const bool f32 = h->prec == MHD_F32;
     for (int d = 1; d < 3; ++d) {
         const long npencil = (long)h->n[0] * h->n[3 - d];
-        h->tune.chunk[d] = largest_chunk(h->n[d], npencil, 4);
-        h->tune.pair_chunk[d] = largest_chunk(h->n[d], npencil, 2);
-        h->tune.triple_chunk[d] = largest_chunk(h->n[d], npencil, 1);
+        h->tune.chunk[d] = march_chunk(h->n[d], npencil, 6, f32 ? 4 : 2, f32 ? 3 : 2);
+        h->tune.pair_chunk[d] = march_chunk(h->n[d], npencil, 13, f32 ? 4 : 2, f32 ? 2 : 1);
+        h->tune.triple_chunk[d] = march_chunk(h->n[d], npencil, 19, f32 ? 6 : 2, 1);
     }
 }
 
