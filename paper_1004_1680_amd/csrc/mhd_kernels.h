@@ -9,9 +9,8 @@ namespace mhd {
 // relaxation speed, simulated time; and the step counters.
 enum { SCAL_DT = 0, SCAL_C = 1, SCAL_TIME = 2, SCAL_VMAX = 3, SCAL_COUNT = 4 };
 // Device flag block: [0] non-physical state recorded by the device-side
-// CFL of mhd_step_auto, [1] number of such steps that ran, [2] result of the
-// synchronous CFL.
-enum { FLAG_NONPHYS = 0, FLAG_STEPS = 1, FLAG_SYNC = 2, FLAG_COUNT = 4 };
+// CFL of mhd_step_auto, [1] number of such steps that ran.
+enum { FLAG_NONPHYS = 0, FLAG_STEPS = 1, FLAG_COUNT = 4 };
 constexpr int CFL_ACC_SLOTS = 256;     // fused-CFL maximum slots (+1 word for the flag)
 
 template <typename T>
@@ -156,8 +155,6 @@ hipError_t launch_batch_advance(double* scal, int* flag, int nbox, hipStream_t s
 
 template <typename T>
 hipError_t launch_fluid(const SweepParams<T>& P, int d, const LaunchTuning& tune, hipStream_t s);
-template <typename T>
-bool fused_cfl_possible(int nx);
 // whether the built-in choice runs op (0 fluid, 1 magnetic, 2 magnetic then
 // fluid, 3 magnetic twice then fluid) along y or z with the tile kernels
 template <typename T>
@@ -175,17 +172,19 @@ hipError_t launch_magmagfluid(const SweepParams<T>& P, int d, const LaunchTuning
 
 // CFL: per-block maxima of the signal speed into partial[], then a final
 // reduction writes scal[SCAL_VMAX], scal[SCAL_C] = vmax, scal[SCAL_DT] =
-// cfl h / vmax (or, if dt_cap > 0, min(that, dt_cap)), and flags
-// non-physical cells in flag[FLAG_NONPHYS].
+// cfl h / vmax, and flags non-physical cells in flag[FLAG_NONPHYS].  advance:
+// also the time advance of the step it opens.  report (host memory or null):
+// dt, vmax and the record go there instead of the record to the flag.  acc
+// (nullable): the fused CFL's accumulator, cleared.
 template <typename T>
 hipError_t launch_cfl(const T* const f[8], int nx, int ny, int nz, double gamma, double cfl,
-                      double* partial, int* partial_bad, int nblocks, double* scal, int* flag,
-                      hipStream_t s);
+                      double* partial, int* partial_bad, int nblocks, double* scal, int* flag, bool advance,
+                      double* report, unsigned long long* acc, hipStream_t s);
 int cfl_blocks(size_t ncell);
-// CFL from the maximum accumulated by the fused epilogue (then cleared), and
-// clearing the accumulator
-hipError_t launch_cfl_from_acc(unsigned long long* acc, int nx, double cfl, double* scal, int* flag,
-                               hipStream_t s);
+// CFL from the maximum accumulated by the fused epilogue (then cleared, unless
+// keep), and clearing the accumulator
+hipError_t launch_cfl_from_acc(unsigned long long* acc, int nx, double cfl, double* scal, int* flag, bool advance,
+                               double* report, bool keep, hipStream_t s);
 hipError_t launch_clear_acc(unsigned long long* acc, hipStream_t s);
 
 // Diagnostics: 8 field sums (FP64, fixed order), max |div b|, max |b|.
@@ -213,6 +212,7 @@ hipError_t launch_restrict(const T* const fine[8], T* const coarse[8], int nx, i
 // Small scalar kernels (graph-capturable replacements of host writes).
 hipError_t launch_set_scalars(double* scal, double dt, double c, int* flag, int clear_flag,
                               hipStream_t s);
-hipError_t launch_advance_time(double* scal, const int* nonphys, int* steps, hipStream_t s);
+hipError_t launch_begin_step(double* scal, double dt, double c, unsigned long long* acc, hipStream_t s);
+hipError_t launch_reset_scalars(double* scal, int* flag, hipStream_t s);
 
 }  // namespace mhd

@@ -56,8 +56,7 @@ struct mhd_ctx {
     double* partial;        // reduction partials (max of cfl and diag needs)
     int* partial_bad;
     int nblk_cfl, nblk_diag;
-    double* diag_out;       // device 9 doubles
-    double* pinned;         // host pinned scratch (16 doubles)
+    double* pinned;         // host pinned scratch (16 doubles), also written by kernels
     bool have_c;
     double c_host;
     bool scal_known;        // host knows what dt / c the device block holds
@@ -66,7 +65,6 @@ struct mhd_ctx {
     // is still the one it describes
     unsigned long long* cfl_acc;
     bool acc_valid;
-    bool fuse_ok;           // grid shape allows the fused epilogue
     // reverse-half pairs M_d F_d: one fused launch each (true) or the two
     // operators in turn; same result bit for bit
     int rev_mode;           // 0 built-in choice, 1 fused, 2 the two operators
@@ -266,7 +264,6 @@ extern "C" mhd_ctx* mhd_create_ex(int nx, int ny, int nz, double gamma, int prec
               hipMalloc(&h->flag, FLAG_COUNT * sizeof(int)) == hipSuccess &&
               hipMalloc(&h->partial, npart * sizeof(double)) == hipSuccess &&
               hipMalloc(&h->partial_bad, h->nblk_cfl * sizeof(int)) == hipSuccess &&
-              hipMalloc(&h->diag_out, 9 * sizeof(double)) == hipSuccess &&
               hipMalloc(&h->cfl_acc, (CFL_ACC_SLOTS + 1) * sizeof(unsigned long long)) == hipSuccess &&
               hipHostMalloc(&h->pinned, 16 * sizeof(double), hipHostMallocDefault) == hipSuccess;
     if (!ok) {
@@ -288,7 +285,6 @@ extern "C" mhd_ctx* mhd_create_ex(int nx, int ny, int nz, double gamma, int prec
     }
     default_tuning(h);
     h->rev_mode = 0;
-    h->fuse_ok = prec == MHD_F64 ? fused_cfl_possible<double>(nx) : fused_cfl_possible<float>(nx);
     h->acc_valid = false;
     return h;
 }
@@ -310,7 +306,6 @@ extern "C" void mhd_destroy(mhd_ctx* h)
     if (h->flag) (void)hipFree(h->flag);
     if (h->partial) (void)hipFree(h->partial);
     if (h->partial_bad) (void)hipFree(h->partial_bad);
-    if (h->diag_out) (void)hipFree(h->diag_out);
     if (h->cfl_acc) (void)hipFree(h->cfl_acc);
     if (h->pinned) (void)hipHostFree(h->pinned);
     delete h;
@@ -335,8 +330,7 @@ static int reset_after_set(mhd_ctx* h)
     h->have_c = false;
     h->c_host = 0.0;
     h->scal_known = false;
-    HIP_TRY(h, hipMemsetAsync(h->scal, 0, SCAL_COUNT * sizeof(double), h->stream));
-    HIP_TRY(h, hipMemsetAsync(h->flag, 0, FLAG_COUNT * sizeof(int), h->stream));
+    HIP_TRY(h, launch_reset_scalars(h->scal, h->flag, h->stream));
     return MHD_OK;
 }
 
@@ -438,17 +432,19 @@ extern "C" int mhd_get_state_device(mhd_ctx* h, void* dst, size_t n, int prec)
     if (prec != MHD_F32 && prec != MHD_F64) return fail(MHD_EINVAL, "bad precision %d", prec);
     HIP_TRY(h, hipSetDevice(h->device));
     const size_t es = prec == MHD_F64 ? sizeof(double) : sizeof(float);
-    for (int q = 0; q < 8; ++q) {
+    // one copy (or conversion) for each run of fields that share a buffer
+    for (int q = 0, m; q < 8; q += m) {
+        for (m = 1; q + m < 8 && h->cur[q + m] == h->cur[q]; ++m) {}
         char* d = (char*)dst + (size_t)q * h->N * es;
         hipError_t e;
         if (prec == h->prec)
             e = hipMemcpyAsync(d, (char*)h->buf[h->cur[q]] + (size_t)q * h->N * h->esize,
-                               h->N * es, hipMemcpyDeviceToDevice, h->stream);
+                               m * h->N * es, hipMemcpyDeviceToDevice, h->stream);
         else if (prec == MHD_F64)
-            e = launch_cast<float, double>(field_ptr<float>(h, q, h->cur[q]), (double*)d, h->N,
+            e = launch_cast<float, double>(field_ptr<float>(h, q, h->cur[q]), (double*)d, m * h->N,
                                            h->stream);
         else
-            e = launch_cast<double, float>(field_ptr<double>(h, q, h->cur[q]), (float*)d, h->N,
+            e = launch_cast<double, float>(field_ptr<double>(h, q, h->cur[q]), (float*)d, m * h->N,
                                            h->stream);
         HIP_TRY(h, e);
     }
@@ -459,13 +455,26 @@ extern "C" int mhd_get_state_device(mhd_ctx* h, void* dst, size_t n, int prec)
 // CFL and relaxation speed
 // ---------------------------------------------------------------------------
 
+// The CFL of the current state: from the maximum that the last launch of the
+// step before left (the same FP64 expression, the same maximum) where that
+// still describes the state, else a reduction of its own.  step: the CFL of a
+// device-dt step (record in the flag block, time advanced, accumulator left
+// clear); otherwise dt, vmax and the record go to report and a valid
+// accumulator stays valid.
 template <typename T>
-static hipError_t enqueue_cfl(mhd_ctx* h, double cfl, int* flag)
+static hipError_t enqueue_cfl(mhd_ctx* h, double cfl, bool step, double* report)
 {
+    if (h->acc_valid)
+        return launch_cfl_from_acc(h->cfl_acc, h->n[0], cfl, h->scal, h->flag, step, report, !step, h->stream);
     const T* f[8];
     current_fields<T>(h, f);
     return launch_cfl<T>(f, h->n[0], h->n[1], h->n[2], h->gamma, cfl, h->partial, h->partial_bad,
-                         h->nblk_cfl, h->scal, flag, h->stream);
+                         h->nblk_cfl, h->scal, h->flag, step, report, step ? h->cfl_acc : nullptr, h->stream);
+}
+
+static hipError_t enqueue_cfl(mhd_ctx* h, double cfl, bool step, double* report)
+{
+    return h->prec == MHD_F64 ? enqueue_cfl<double>(h, cfl, step, report) : enqueue_cfl<float>(h, cfl, step, report);
 }
 
 extern "C" int mhd_cfl_dt(mhd_ctx* h, double cfl, double* dt_out)
@@ -475,17 +484,10 @@ extern "C" int mhd_cfl_dt(mhd_ctx* h, double cfl, double* dt_out)
     if (!dt_out) return fail(MHD_EINVAL, "null dt pointer");
     if (!(cfl > 0.0) || !isfinite(cfl)) return fail(MHD_EINVAL, "cfl must be > 0 (got %g)", cfl);
     HIP_TRY(h, hipSetDevice(h->device));
-    HIP_TRY(h, hipMemsetAsync(h->flag + FLAG_SYNC, 0, sizeof(int), h->stream));
     h->scal_known = false;
-    HIP_TRY(h, h->prec == MHD_F64 ? enqueue_cfl<double>(h, cfl, h->flag + FLAG_SYNC)
-                                  : enqueue_cfl<float>(h, cfl, h->flag + FLAG_SYNC));
-    HIP_TRY(h, hipMemcpyAsync(h->pinned, h->scal, SCAL_COUNT * sizeof(double),
-                              hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipMemcpyAsync(h->pinned + 8, h->flag + FLAG_SYNC, sizeof(int),
-                              hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(h, enqueue_cfl(h, cfl, false, h->pinned));
     if ((r = sync_stream(h))) return r;
-    int bad;
-    memcpy(&bad, h->pinned + 8, sizeof(int));
+    const int bad = (int)h->pinned[2];
     if (bad == 1) {
         *dt_out = 0.0;
         return fail(MHD_ENONPHYS, "non-physical state: rho <= 0, p < 0 or non-finite value");
@@ -494,8 +496,8 @@ extern "C" int mhd_cfl_dt(mhd_ctx* h, double cfl, double* dt_out)
         *dt_out = 0.0;
         return fail(MHD_EINVAL, "largest signal speed is zero: no CFL time step");
     }
-    *dt_out = h->pinned[SCAL_DT];
-    h->c_host = h->pinned[SCAL_VMAX];
+    *dt_out = h->pinned[0];
+    h->c_host = h->pinned[1];
     h->have_c = true;
     return MHD_OK;
 }
@@ -576,7 +578,10 @@ static int check_dt(double dt)
     return MHD_OK;
 }
 
-static int prepare_host_dt(mhd_ctx* h, double dt, bool need_c)
+// checks of a host-dt call; step: the opening launch of a full step, which
+// sets the scalars in any case (and advances the time, and clears the fused
+// CFL's accumulator)
+static int prepare_host_dt(mhd_ctx* h, double dt, bool need_c, bool step = false)
 {
     int r = check_handle(h);
     if (r) return r;
@@ -588,8 +593,12 @@ static int prepare_host_dt(mhd_ctx* h, double dt, bool need_c)
     HIP_TRY(h, hipSetDevice(h->device));
     // c_host < 0: the speed was set by a device-side CFL and stays there
     const double c = h->have_c ? h->c_host : 0.0;
-    if (h->scal_known && h->scal_dt == dt && (c <= 0.0 || h->scal_c == c)) return MHD_OK;
-    HIP_TRY(h, launch_set_scalars(h->scal, dt, c, h->flag, 0, h->stream));
+    if (step)
+        HIP_TRY(h, launch_begin_step(h->scal, dt, c, h->cfl_acc, h->stream));
+    else if (h->scal_known && h->scal_dt == dt && (c <= 0.0 || h->scal_c == c))
+        return MHD_OK;
+    else
+        HIP_TRY(h, launch_set_scalars(h->scal, dt, c, h->flag, 0, h->stream));
     h->scal_known = c > 0.0;
     h->scal_dt = dt;
     h->scal_c = c;
@@ -666,15 +675,15 @@ extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
     }
     if (dim == 6) {
         // the reverse x pair with the fused CFL of its result
-        unsigned long long* acc = h->fuse_ok ? h->cfl_acc : nullptr;
-        if (acc) HIP_TRY(h, launch_clear_acc(acc, h->stream));
+        unsigned long long* acc = h->cfl_acc;
+        HIP_TRY(h, launch_clear_acc(acc, h->stream));
         if (pair_fused(h, 0)) {
             HIP_TRY(h, op(h, 2, 0, nullptr, acc));
         } else {
             HIP_TRY(h, op(h, 1, 0, nullptr));
             HIP_TRY(h, op(h, 0, 0, nullptr, acc));
         }
-        h->acc_valid = h->fuse_ok;
+        h->acc_valid = true;
         return MHD_OK;
     }
     const int d = dim % 3;
@@ -784,13 +793,11 @@ extern "C" int mhd_get_limiter(const mhd_ctx* h, int* limiter)
 
 extern "C" int mhd_step(mhd_ctx* h, double dt)
 {
-    int r = prepare_host_dt(h, dt, true);
+    int r = prepare_host_dt(h, dt, true, true);
     if (r) return r;
     h->acc_valid = false;
-    if (h->fuse_ok) HIP_TRY(h, launch_clear_acc(h->cfl_acc, h->stream));
-    if ((r = enqueue_step_ops(h, nullptr, h->fuse_ok ? h->cfl_acc : nullptr))) return r;
-    HIP_TRY(h, launch_advance_time(h->scal, nullptr, nullptr, h->stream));
-    h->acc_valid = h->fuse_ok;
+    if ((r = enqueue_step_ops(h, nullptr, h->cfl_acc))) return r;
+    h->acc_valid = true;
     return MHD_OK;
 }
 
@@ -801,19 +808,10 @@ extern "C" int mhd_step_auto(mhd_ctx* h, double cfl)
     if (!(cfl > 0.0) || !isfinite(cfl)) return fail(MHD_EINVAL, "cfl must be > 0 (got %g)", cfl);
     HIP_TRY(h, hipSetDevice(h->device));
     h->scal_known = false;
-    if (h->acc_valid) {
-        // the previous step's last operator already found this state's
-        // largest signal speed (same FP64 expression, same maximum)
-        HIP_TRY(h, launch_cfl_from_acc(h->cfl_acc, h->n[0], cfl, h->scal, h->flag + FLAG_NONPHYS, h->stream));
-    } else {
-        HIP_TRY(h, h->prec == MHD_F64 ? enqueue_cfl<double>(h, cfl, h->flag + FLAG_NONPHYS)
-                                      : enqueue_cfl<float>(h, cfl, h->flag + FLAG_NONPHYS));
-        if (h->fuse_ok) HIP_TRY(h, launch_clear_acc(h->cfl_acc, h->stream));
-    }
+    HIP_TRY(h, enqueue_cfl(h, cfl, true, nullptr));
     h->acc_valid = false;
-    if ((r = enqueue_step_ops(h, h->flag + FLAG_NONPHYS, h->fuse_ok ? h->cfl_acc : nullptr))) return r;
-    h->acc_valid = h->fuse_ok;
-    HIP_TRY(h, launch_advance_time(h->scal, h->flag + FLAG_NONPHYS, h->flag + FLAG_STEPS, h->stream));
+    if ((r = enqueue_step_ops(h, h->flag + FLAG_NONPHYS, h->cfl_acc))) return r;
+    h->acc_valid = true;
     // the device CFL also set the relaxation speed; it stays on the device
     // (c_host < 0 marks that) until read back
     h->have_c = true;
@@ -866,8 +864,7 @@ static hipError_t enqueue_diag(mhd_ctx* h)
 {
     const T* f[8];
     current_fields<T>(h, f);
-    return launch_diag<T>(f, h->n[0], h->n[1], h->n[2], h->partial, h->nblk_diag, h->diag_out,
-                          h->stream);
+    return launch_diag<T>(f, h->n[0], h->n[1], h->n[2], h->partial, h->nblk_diag, h->pinned, h->stream);
 }
 
 extern "C" int mhd_diag(mhd_ctx* h, double out[9])
@@ -877,8 +874,6 @@ extern "C" int mhd_diag(mhd_ctx* h, double out[9])
     if (!out) return fail(MHD_EINVAL, "null output");
     HIP_TRY(h, hipSetDevice(h->device));
     HIP_TRY(h, h->prec == MHD_F64 ? enqueue_diag<double>(h) : enqueue_diag<float>(h));
-    HIP_TRY(h, hipMemcpyAsync(h->pinned, h->diag_out, 9 * sizeof(double), hipMemcpyDeviceToHost,
-                              h->stream));
     if ((r = sync_stream(h))) return r;
     memcpy(out, h->pinned, 9 * sizeof(double));
     return MHD_OK;

@@ -98,7 +98,7 @@ static int enqueue(const void* state, int nx, int ny, int nz, double gamma, doub
     int* flag = reinterpret_cast<int*>(base + OFF_FLAG);
     hipLaunchKernelGGL(noalloc_clear_kernel, dim3(1), dim3(64), 0, s, scal, flag);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = launch_cfl<T>(f, nx, ny, nz, gamma, cfl, partial, bad, nblk, scal, flag, s);
+    if (e == hipSuccess) e = launch_cfl<T>(f, nx, ny, nz, gamma, cfl, partial, bad, nblk, scal, flag, false, nullptr, nullptr, s);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(noalloc_out_kernel, dim3(1), dim3(64), 0, s, scal, flag, out);
         e = hipGetLastError();

@@ -41,7 +41,10 @@ __device__ __forceinline__ double wave_sum(double v)
 
 int cfl_blocks(size_t ncell)
 {
-    size_t b = (ncell + RED_THREADS * 8 - 1) / (RED_THREADS * 8);
+    // two cells per thread until the partials' cap: a thread's cells are one
+    // dependent chain each (loads, FP64 divisions, a square root), so a small
+    // grid wants them spread (16^3: 5.5 us against 9.9 with 8 per thread)
+    size_t b = (ncell + RED_THREADS * 2 - 1) / (RED_THREADS * 2);
     if (b > 4096) b = 4096;
     if (b < 1) b = 1;
     return (int)b;
@@ -50,17 +53,19 @@ int cfl_blocks(size_t ncell)
 // Signal speed max_d |v_d| + sqrt((gamma p + |Bbar|^2)/rho) of cell c of an
 // nx x ny x nz grid in FP64; folds it into vmax, or raises bad for a
 // non-physical cell.
+// (fewer than 2^31 cells: 32-bit indices, whose divisions are far cheaper)
 template <typename T>
-__device__ __forceinline__ void cell_signal_speed(const T* const* f, size_t c, int nx, int ny,
+__device__ __forceinline__ void cell_signal_speed(const T* const* f, unsigned c, int nx, int ny,
                                                   int nz, double gamma, double& vmax, int& bad)
 {
-    const size_t sy = nx, sz = (size_t)nx * ny;
-    const int i = (int)(c % nx);
-    const int j = (int)((c / sy) % ny);
-    const int k = (int)(c / sz);
-    const size_t cx = i + 1 == nx ? c - (nx - 1) : c + 1;
-    const size_t cy = j + 1 == ny ? c - (ny - 1) * sy : c + sy;
-    const size_t cz = k + 1 == nz ? c - (size_t)(nz - 1) * sz : c + sz;
+    const unsigned sy = nx, sz = (unsigned)nx * ny;
+    const unsigned kj = c / sy;
+    const int i = (int)(c - kj * sy);
+    const int k = (int)(kj / (unsigned)ny);
+    const int j = (int)(kj - (unsigned)k * ny);
+    const unsigned cx = i + 1 == nx ? c - (nx - 1) : c + 1;
+    const unsigned cy = j + 1 == ny ? c - (unsigned)(ny - 1) * sy : c + sy;
+    const unsigned cz = k + 1 == nz ? c - (unsigned)(nz - 1) * sz : c + sz;
     signal_speed64((double)f[0][c], (double)f[1][c], (double)f[2][c], (double)f[3][c], (double)f[4][c],
                    (double)f[5][c], (double)f[5][cx], (double)f[6][c], (double)f[6][cy], (double)f[7][c],
                    (double)f[7][cz], gamma, vmax, bad);
@@ -74,12 +79,11 @@ __global__ void __launch_bounds__(RED_THREADS) cfl_partial_kernel(
     const T* __restrict__ by_, const T* __restrict__ bz_, int nx, int ny, int nz, double gamma,
     double* partial, int* partial_bad)
 {
-    const size_t N = (size_t)nx * ny * nz;
+    const unsigned N = (unsigned)nx * ny * nz;
     const T* f[8] = { rho_, mx_, my_, mz_, e_, bx_, by_, bz_ };
     double vmax = 0.0;
     int bad = 0;
-    for (size_t c = (size_t)blockIdx.x * RED_THREADS + threadIdx.x; c < N;
-         c += (size_t)gridDim.x * RED_THREADS)
+    for (unsigned c = blockIdx.x * RED_THREADS + threadIdx.x; c < N; c += gridDim.x * RED_THREADS)
         cell_signal_speed(f, c, nx, ny, nz, gamma, vmax, bad);
     __shared__ double smax[RED_THREADS / 64];
     __shared__ int sbad[RED_THREADS / 64];
@@ -97,18 +101,52 @@ __global__ void __launch_bounds__(RED_THREADS) cfl_partial_kernel(
     }
 }
 
-// One block: final maximum; dt = cfl h / vmax.  A non-physical state
-// raises *flag (never cleared here) and writes dt = 0 without touching the
-// relaxation speed.
+// What a CFL reduction does with its result (one thread): dt = cfl h / vmax
+// and the relaxation speed into scal, or, for a record (1 non-physical, 2
+// zero signal speed), dt = 0 without touching the relaxation speed and the
+// record in *flag (never cleared here).  report (host memory, may be null):
+// dt, vmax and the record go there and *flag stays as it is.  advance: the
+// time advance of the step that this reduction opens, 2 dt and one more step
+// in flag[FLAG_STEPS] unless a record stands; nothing in a step reads them,
+// so they need no launch of their own at its end.
+__device__ __forceinline__ void cfl_finish(double vmax, int record, int nx, double cfl, double* scal, int* flag,
+                                           bool advance, double* report)
+{
+    double dt = 0.0;
+    if (!record && !(vmax > 0.0)) record = 2;
+    if (record) {
+        vmax = 0.0;
+        if (!report) flag[FLAG_NONPHYS] = record;
+    } else {
+        dt = cfl * (1.0 / (double)nx) / vmax;
+        scal[SCAL_C] = vmax;
+    }
+    scal[SCAL_DT] = dt;
+    scal[SCAL_VMAX] = vmax;
+    if (report) { report[0] = dt; report[1] = vmax; report[2] = (double)record; }
+    if (advance && !record && flag[FLAG_NONPHYS] == 0) {
+        scal[SCAL_TIME] += 2.0 * dt;
+        flag[FLAG_STEPS] += 1;
+    }
+}
+
+// One block of CFL_ACC_SLOTS threads: final maximum of the partials; also
+// clears the fused CFL's accumulator (acc, may be null) for the step to come
 __global__ void __launch_bounds__(RED_THREADS) cfl_final_kernel(
     const double* partial, const int* partial_bad, int nblocks, int nx, double cfl, double* scal,
-    int* flag)
+    int* flag, bool advance, double* report, unsigned long long* acc)
 {
+    static_assert(RED_THREADS == CFL_ACC_SLOTS, "one accumulator slot per thread");
     double m = 0.0;
     int bad = 0;
+#pragma unroll 4
     for (int b = threadIdx.x; b < nblocks; b += RED_THREADS) {
         m = fmax(m, partial[b]);
         bad |= partial_bad[b];
+    }
+    if (acc) {
+        acc[threadIdx.x] = 0;
+        if (threadIdx.x == 0) acc[CFL_ACC_SLOTS] = 0;
     }
     __shared__ double smax[RED_THREADS / 64];
     __shared__ int sbad[RED_THREADS / 64];
@@ -121,42 +159,36 @@ __global__ void __launch_bounds__(RED_THREADS) cfl_final_kernel(
         double vmax = smax[0];
         int b = sbad[0];
         for (int q = 1; q < RED_THREADS / 64; ++q) { vmax = fmax(vmax, smax[q]); b |= sbad[q]; }
-        if (b || !(vmax > 0.0)) {
-            scal[SCAL_DT] = 0.0;
-            scal[SCAL_VMAX] = 0.0;
-            flag[0] = b ? 1 : 2;
-        } else {
-            scal[SCAL_DT] = cfl * (1.0 / (double)nx) / vmax;
-            scal[SCAL_VMAX] = vmax;
-            scal[SCAL_C] = vmax;
-        }
+        cfl_finish(vmax, b ? 1 : 0, nx, cfl, scal, flag, advance, report);
     }
 }
 
 template <typename T>
 hipError_t launch_cfl(const T* const f[8], int nx, int ny, int nz, double gamma, double cfl,
-                      double* partial, int* partial_bad, int nblocks, double* scal, int* flag,
-                      hipStream_t s)
+                      double* partial, int* partial_bad, int nblocks, double* scal, int* flag, bool advance,
+                      double* report, unsigned long long* acc, hipStream_t s)
 {
     hipLaunchKernelGGL(cfl_partial_kernel<T>, dim3(nblocks), dim3(RED_THREADS), 0, s, f[0], f[1],
                        f[2], f[3], f[4], f[5], f[6], f[7], nx, ny, nz, gamma, partial, partial_bad);
     hipLaunchKernelGGL(cfl_final_kernel, dim3(1), dim3(RED_THREADS), 0, s, partial, partial_bad,
-                       nblocks, nx, cfl, scal, flag);
+                       nblocks, nx, cfl, scal, flag, advance, report, acc);
     return hipGetLastError();
 }
 
-template hipError_t launch_cfl<float>(const float* const[8], int, int, int, double, double,
-                                      double*, int*, int, double*, int*, hipStream_t);
-template hipError_t launch_cfl<double>(const double* const[8], int, int, int, double, double,
-                                       double*, int*, int, double*, int*, hipStream_t);
+template hipError_t launch_cfl<float>(const float* const[8], int, int, int, double, double, double*, int*, int,
+                                      double*, int*, bool, double*, unsigned long long*, hipStream_t);
+template hipError_t launch_cfl<double>(const double* const[8], int, int, int, double, double, double*, int*, int,
+                                       double*, int*, bool, double*, unsigned long long*, hipStream_t);
 
 // The CFL from the maximum that the fused epilogue of the previous step's
 // last fluid operator accumulated (acc[0 .. CFL_ACC_SLOTS): bits of FP64
 // maxima, acc[CFL_ACC_SLOTS]: non-physical flag); the same dt / relaxation
 // speed / flag rules as cfl_final_kernel.  Clears acc for the next
-// accumulation.  One block of CFL_ACC_SLOTS threads.
+// accumulation unless keep (the state and its maximum stay as they are).
+// One block of CFL_ACC_SLOTS threads.
 __global__ void __launch_bounds__(CFL_ACC_SLOTS) cfl_from_acc_kernel(unsigned long long* acc, int nx, double cfl,
-                                                                     double* scal, int* flag)
+                                                                     double* scal, int* flag, bool advance,
+                                                                     double* report, bool keep)
 {
     double m = __longlong_as_double((long long)acc[threadIdx.x]);
     m = wave_max(m);
@@ -169,24 +201,17 @@ __global__ void __launch_bounds__(CFL_ACC_SLOTS) cfl_from_acc_kernel(unsigned lo
         // bit 0: a non-physical cell (or record); bit 1 alone: a step skipped
         // under a zero-speed record, whose state still has no signal speed
         const int b = (int)acc[CFL_ACC_SLOTS];
-        if (b || !(vmax > 0.0)) {
-            scal[SCAL_DT] = 0.0;
-            scal[SCAL_VMAX] = 0.0;
-            flag[0] = (b & 1) ? 1 : 2;
-        } else {
-            scal[SCAL_DT] = cfl * (1.0 / (double)nx) / vmax;
-            scal[SCAL_VMAX] = vmax;
-            scal[SCAL_C] = vmax;
-        }
-        acc[CFL_ACC_SLOTS] = 0;
+        cfl_finish(vmax, b ? ((b & 1) ? 1 : 2) : 0, nx, cfl, scal, flag, advance, report);
+        if (!keep) acc[CFL_ACC_SLOTS] = 0;
     }
-    acc[threadIdx.x] = 0;
+    if (!keep) acc[threadIdx.x] = 0;
 }
 
-hipError_t launch_cfl_from_acc(unsigned long long* acc, int nx, double cfl, double* scal, int* flag,
-                               hipStream_t s)
+hipError_t launch_cfl_from_acc(unsigned long long* acc, int nx, double cfl, double* scal, int* flag, bool advance,
+                               double* report, bool keep, hipStream_t s)
 {
-    hipLaunchKernelGGL(cfl_from_acc_kernel, dim3(1), dim3(CFL_ACC_SLOTS), 0, s, acc, nx, cfl, scal, flag);
+    hipLaunchKernelGGL(cfl_from_acc_kernel, dim3(1), dim3(CFL_ACC_SLOTS), 0, s, acc, nx, cfl, scal, flag, advance,
+                       report, keep);
     return hipGetLastError();
 }
 
@@ -216,9 +241,9 @@ __global__ void __launch_bounds__(RED_THREADS) batch_cfl_partial_kernel(
     for (int q = 0; q < 8; ++q) f[q] = A.base[q] + bd.off + (size_t)q * bd.ncell;
     double vmax = 0.0;
     int bad = 0;
-    const size_t c0 = (size_t)it.y * CFL_CELLS;
-    const size_t c1 = c0 + CFL_CELLS < bd.ncell ? c0 + CFL_CELLS : bd.ncell;
-    for (size_t c = c0 + threadIdx.x; c < c1; c += RED_THREADS)
+    const unsigned c0 = (unsigned)it.y * CFL_CELLS;
+    const unsigned c1 = c0 + CFL_CELLS < bd.ncell ? c0 + CFL_CELLS : bd.ncell;
+    for (unsigned c = c0 + threadIdx.x; c < c1; c += RED_THREADS)
         cell_signal_speed(f, c, bd.n[0], bd.n[1], bd.n[2], gamma, vmax, bad);
     __shared__ double smax[RED_THREADS / 64];
     __shared__ int sbad[RED_THREADS / 64];
@@ -723,20 +748,37 @@ hipError_t launch_set_scalars(double* scal, double dt, double c, int* flag, int 
     return hipGetLastError();
 }
 
-// Time advance of one full step (2 dt) unless a non-physical state was
-// recorded (nonphys may be null); counts the steps that ran (steps may be
-// null).
-__global__ void advance_time_kernel(double* scal, const int* nonphys, int* steps)
+// Opening of a host-dt step: the time advance of the step (2 dt), the dt and
+// relaxation speed of its operators (c <= 0: keep the device value) and a
+// cleared fused-CFL accumulator (acc, may be null).  One block of
+// CFL_ACC_SLOTS threads.
+__global__ void begin_step_kernel(double* scal, double dt, double c, unsigned long long* acc)
 {
-    if (threadIdx.x == 0 && (nonphys == nullptr || *nonphys == 0)) {
-        scal[SCAL_TIME] += 2.0 * scal[SCAL_DT];
-        if (steps) *steps += 1;
+    if (acc) acc[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        if (acc) acc[CFL_ACC_SLOTS] = 0;
+        scal[SCAL_DT] = dt;
+        if (c > 0.0) scal[SCAL_C] = c;
+        scal[SCAL_TIME] += 2.0 * dt;
     }
 }
 
-hipError_t launch_advance_time(double* scal, const int* nonphys, int* steps, hipStream_t s)
+hipError_t launch_begin_step(double* scal, double dt, double c, unsigned long long* acc, hipStream_t s)
 {
-    hipLaunchKernelGGL(advance_time_kernel, dim3(1), dim3(64), 0, s, scal, nonphys, steps);
+    hipLaunchKernelGGL(begin_step_kernel, dim3(1), dim3(CFL_ACC_SLOTS), 0, s, scal, dt, c, acc);
+    return hipGetLastError();
+}
+
+// scalar and flag blocks of a fresh state (time 0, no record)
+__global__ void reset_scalars_kernel(double* scal, int* flag)
+{
+    if (threadIdx.x < SCAL_COUNT) scal[threadIdx.x] = 0.0;
+    if (threadIdx.x < FLAG_COUNT) flag[threadIdx.x] = 0;
+}
+
+hipError_t launch_reset_scalars(double* scal, int* flag, hipStream_t s)
+{
+    hipLaunchKernelGGL(reset_scalars_kernel, dim3(1), dim3(64), 0, s, scal, flag);
     return hipGetLastError();
 }
 

@@ -4,7 +4,6 @@
 
 namespace mhd {
 template hipError_t launch_fluid<float>(const SweepParams<float>&, int, const LaunchTuning&, hipStream_t);
-template bool fused_cfl_possible<float>(int);
 template bool sweep_uses_tiles<float>(const int[3], int, int, const LaunchTuning&);
 template hipError_t launch_magnetic<float>(const SweepParams<float>&, int, const LaunchTuning&, hipStream_t);
 template hipError_t launch_magfluid<float>(const SweepParams<float>&, int, const LaunchTuning&, hipStream_t);

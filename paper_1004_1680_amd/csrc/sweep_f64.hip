@@ -5,7 +5,6 @@
 
 namespace mhd {
 template hipError_t launch_fluid<double>(const SweepParams<double>&, int, const LaunchTuning&, hipStream_t);
-template bool fused_cfl_possible<double>(int);
 template bool sweep_uses_tiles<double>(const int[3], int, int, const LaunchTuning&);
 template hipError_t launch_magnetic<double>(const SweepParams<double>&, int, const LaunchTuning&, hipStream_t);
 template hipError_t launch_magfluid<double>(const SweepParams<double>&, int, const LaunchTuning&, hipStream_t);

@@ -244,7 +244,7 @@ __device__ __forceinline__ void row_stage_speeds(const T (&w)[4][5], const T (&b
 // Every thread of the workgroup calls it (it holds barriers).
 // CFL = true: the FP64 signal speed of every output cell, maximum per wave,
 // atomic maximum into P.cfl_acc; needs full waves (blockDim.x a multiple of
-// 64).
+// 64, idle threads included).
 template <typename T, int D, bool CFL, int LIM = LIM_VANLEER, int FRZ = FRZ_STEP, bool W32 = false,
           typename Thread = RowThread>
 __device__ __forceinline__ void fluid_cells_core(const SweepParams<T>& P, const Thread& R,
@@ -1834,14 +1834,9 @@ inline void row_shape(int nx, int& tpr, int& rows_per_wg, int& threads)
     threads = rows_per_wg * tpr;
 }
 
-// the fused CFL epilogue needs the x fluid kernel's workgroups to be whole waves
-template <typename T>
-bool fused_cfl_possible(int nx)
-{
-    int tpr, rpw, threads;
-    row_shape<T>(nx, tpr, rpw, threads);
-    return threads % 64 == 0;
-}
+// threads of a workgroup of an x kernel with the fused CFL epilogue, whose
+// wave-wide reductions need whole waves: idle threads fill the last one
+inline int cfl_threads(int threads) { return (threads + 63) / 64 * 64; }
 
 // every byte offset of a field fits in 32 bits (the march kernels' W32 path)
 template <typename T>
@@ -1931,12 +1926,13 @@ hipError_t launch_fluid_lim(const SweepParams<T>& P, int d, const LaunchTuning& 
         const int st = row_group_tiles(P.ny, rpw, tune.row_group);
         const bool fast = offsets32<T>(P, tune);
         if (P.cfl_acc) {
-            if (threads % 64) return hipErrorInvalidValue;      // fused CFL needs full waves
+            const int nt = cfl_threads(threads);
+            const size_t lds = sizeof(T) * 25 * nt;
             if (fast)
-                hipLaunchKernelGGL((fluid_x_kernel<T, true, LIM, FRZ, true>), dim3(grid), dim3(threads), lds, s, P,
+                hipLaunchKernelGGL((fluid_x_kernel<T, true, LIM, FRZ, true>), dim3(grid), dim3(nt), lds, s, P,
                                    tpr, rpw, st);
             else
-                hipLaunchKernelGGL((fluid_x_kernel<T, true, LIM, FRZ>), dim3(grid), dim3(threads), lds, s, P, tpr, rpw, st);
+                hipLaunchKernelGGL((fluid_x_kernel<T, true, LIM, FRZ>), dim3(grid), dim3(nt), lds, s, P, tpr, rpw, st);
         } else {
             if (fast)
                 hipLaunchKernelGGL((fluid_x_kernel<T, false, LIM, FRZ, true>), dim3(grid), dim3(threads), lds, s, P,
@@ -2054,12 +2050,13 @@ hipError_t launch_magfluid_lim(const SweepParams<T>& P, int d, const LaunchTunin
         const int st = row_group_tiles(P.ny, rpw, tune.row_group);
         const bool fast = offsets32<T>(P, tune);
         if (P.cfl_acc) {
-            if (threads % 64) return hipErrorInvalidValue;      // fused CFL needs full waves
+            const int nt = cfl_threads(threads);
+            const size_t lds = sizeof(T) * 25 * nt;
             if (fast)
-                hipLaunchKernelGGL((magfluid_x_kernel<T, true, LIM, true>), dim3(grid), dim3(threads), lds, s, P,
+                hipLaunchKernelGGL((magfluid_x_kernel<T, true, LIM, true>), dim3(grid), dim3(nt), lds, s, P,
                                    tpr, rpw, st);
             else
-                hipLaunchKernelGGL((magfluid_x_kernel<T, true, LIM>), dim3(grid), dim3(threads), lds, s, P, tpr, rpw, st);
+                hipLaunchKernelGGL((magfluid_x_kernel<T, true, LIM>), dim3(grid), dim3(nt), lds, s, P, tpr, rpw, st);
         } else {
             if (fast)
                 hipLaunchKernelGGL((magfluid_x_kernel<T, false, LIM, true>), dim3(grid), dim3(threads), lds, s, P,
