@@ -303,7 +303,12 @@ int mhd_batch_time(mhd_batch *b, double *times);
  * as MHD_TUNE_WIDE_OFFSETS, and MHD_BATCH_MIDDLE as MHD_TUNE_MIDDLE (1: M_z
  * M_z F_z in one launch, on the fused pairs' work list; 2: M_z and the z
  * pair; 0: built-in, 1 where the boxes hold 128^3 cells or more on average,
- * in FP32 with fused pairs and van Leer's limiter).
+ * in FP32 with fused pairs and van Leer's limiter).  Boxes whose pencils
+ * along y or z have at most 64 cells, and are not cut by the chunk target,
+ * run in tiles of whole pencils instead of walking them; where every box's
+ * pairs do, the built-in choices run the pairs, and in FP32 with van Leer's
+ * limiter the middle, as one launch each (the reports are those of the
+ * walking kernels, as for a single grid).
  * Launch-shape parameters, not part of the method. */
 enum { MHD_BATCH_GRID_X = 10, MHD_BATCH_GRID_Y = 11, MHD_BATCH_GRID_Z = 12,
        MHD_BATCH_CHUNK = 13, MHD_BATCH_REVERSE = 14, MHD_BATCH_WIDE_OFFSETS = 15,

@@ -40,10 +40,13 @@ struct mhd_batch {
     int cur[8];
     double* scal;                 // nbox x SCAL_COUNT
     int* flag;                    // nbox x FLAG_COUNT
-    int2* d_items[3];
-    int nitems[3];
-    int2* d_pitems[3];            // work lists of the fused pairs along y, z (x: d_items[0])
-    int npitems[3];
+    // work lists of the single operators [0] and of the fused pairs and the
+    // middle along y, z [1] (x: [0] for both): items of the row and march
+    // kernels, and tile items of the boxes whose pencils run in tiles
+    int2* d_items[2][3];
+    int nitems[2][3];
+    int2* d_titems[2][3];
+    int ntitems[2][3];
     int2* d_cfl_items;
     int n_cfl_items;
     int* d_item_first;
@@ -83,10 +86,12 @@ static int pick_chunk(int n, int target)
 
 static void free_lists(mhd_batch* b)
 {
-    for (int d = 0; d < 3; ++d) {
-        if (b->d_items[d]) { (void)hipFree(b->d_items[d]); b->d_items[d] = nullptr; }
-        if (b->d_pitems[d]) { (void)hipFree(b->d_pitems[d]); b->d_pitems[d] = nullptr; }
-    }
+    for (int p = 0; p < 2; ++p)
+        for (int d = 0; d < 3; ++d) {
+            if (b->d_items[p][d]) { (void)hipFree(b->d_items[p][d]); b->d_items[p][d] = nullptr; }
+            if (b->d_titems[p][d]) { (void)hipFree(b->d_titems[p][d]); b->d_titems[p][d] = nullptr; }
+            b->nitems[p][d] = b->ntitems[p][d] = 0;
+        }
     if (b->d_boxes) { (void)hipFree(b->d_boxes); b->d_boxes = nullptr; }
 }
 
@@ -99,12 +104,32 @@ static void drop_graph(mhd_batch* b)
     b->graph_valid = false;
 }
 
+// Box i runs axis d (y, z) in tiles of whole pencils: up to 64 cells where
+// the chunk target (pair: of the fused pairs) leaves the pencil whole, with
+// 32-bit offsets.  Lines and reasons as for a single grid (tile_shape): at
+// 64 cells tiles win at any number of pencils.  12 boxes of 16 to 48 cells
+// a side, FP32, us per launch: fluid 39 -> 12.5, magnetic 24 -> 12, pair 52
+// -> 20.6, middle 19.3 in place of M_z and the pair.
+static bool box_tiles(const mhd_batch* b, int i, int d, bool pair)
+{
+    const BoxDesc& bd = b->boxes[i];
+    const int target = pair ? b->pair_chunk_target : b->chunk_target;
+    return d > 0 && !b->wide && bd.n[d] <= BATCH_TILE_CELLS && bd.n[d] <= target &&
+           (unsigned long long)bd.ncell * b->esize <= (1ull << 32);
+}
+
+// every box runs the pairs along d in tiles
+static bool all_tiles(const mhd_batch* b, int d)
+{
+    return b->ntitems[1][d] > 0 && b->nitems[1][d] == 0;
+}
+
 // (re)build box shapes and the work lists of the three directions
 static int build_lists(mhd_batch* b)
 {
     free_lists(b);
     drop_graph(b);
-    std::vector<int2> items[3], pitems[3];
+    std::vector<int2> items[2][3], titems[2][3];
     for (int i = 0; i < b->nbox; ++i) {
         BoxDesc& bd = b->boxes[i];
         bd.chunk[0] = bd.pchunk[0] = 0;
@@ -115,39 +140,36 @@ static int build_lists(mhd_batch* b)
         bd.tpr = bd.n[0] / 4;
         bd.rpw = std::max(1, 256 / bd.tpr);
         bd.ntile[0] = (bd.n[1] * bd.n[2] + bd.rpw - 1) / bd.rpw;
-        for (int d = 1; d < 3; ++d) {
-            const long lanes = (long)bd.n[0] * (d == 1 ? bd.n[2] : bd.n[1]) * (bd.n[d] / bd.chunk[d]);
-            bd.ntile[d] = (int)((lanes + 255) / 256);
-        }
         // x tiles in the single-grid visit order (groups of rows along y, one
         // group per z in turn), so the rows z +- 1 a tile reads were read a
         // few items earlier on the same XCD
         const int st = row_group_tiles(bd.n[1], bd.rpw, 0);
         const int ty = bd.n[1] / bd.rpw;
-        for (int t = 0; t < bd.ntile[0]; ++t) items[0].push_back(make_int2(i, row_tile(t, st, ty, bd.n[2])));
-        for (int d = 1; d < 3; ++d)
-            for (int t = 0; t < bd.ntile[d]; ++t) items[d].push_back(make_int2(i, t));
-        for (int d = 1; d < 3; ++d) {
-            const long lanes = (long)bd.n[0] * (d == 1 ? bd.n[2] : bd.n[1]) * (bd.n[d] / bd.pchunk[d]);
-            const int nt = (int)((lanes + 255) / 256);
-            for (int t = 0; t < nt; ++t) pitems[d].push_back(make_int2(i, t));
-        }
+        for (int t = 0; t < bd.ntile[0]; ++t) items[0][0].push_back(make_int2(i, row_tile(t, st, ty, bd.n[2])));
+        for (int p = 0; p < 2; ++p)
+            for (int d = 1; d < 3; ++d) {
+                const long npencil = (long)bd.n[0] * (d == 1 ? bd.n[2] : bd.n[1]);
+                const bool tiled = box_tiles(b, i, d, p == 1);
+                const long per = tiled ? batch_tile_pencils(bd.n[d]) : 256;
+                const long lanes = tiled ? npencil : npencil * (bd.n[d] / (p ? bd.pchunk[d] : bd.chunk[d]));
+                const int nt = (int)((lanes + per - 1) / per);
+                if (p == 0) bd.ntile[d] = nt;
+                for (int t = 0; t < nt; ++t) (tiled ? titems : items)[p][d].push_back(make_int2(i, t));
+            }
     }
     HIP_TRY(b, hipMalloc(&b->d_boxes, sizeof(BoxDesc) * b->nbox));
     HIP_TRY(b, hipMemcpy(b->d_boxes, b->boxes.data(), sizeof(BoxDesc) * b->nbox,
                          hipMemcpyHostToDevice));
-    for (int d = 0; d < 3; ++d) {
-        b->nitems[d] = (int)items[d].size();
-        HIP_TRY(b, hipMalloc(&b->d_items[d], sizeof(int2) * items[d].size()));
-        HIP_TRY(b, hipMemcpy(b->d_items[d], items[d].data(), sizeof(int2) * items[d].size(),
-                             hipMemcpyHostToDevice));
-    }
-    for (int d = 1; d < 3; ++d) {
-        b->npitems[d] = (int)pitems[d].size();
-        HIP_TRY(b, hipMalloc(&b->d_pitems[d], sizeof(int2) * pitems[d].size()));
-        HIP_TRY(b, hipMemcpy(b->d_pitems[d], pitems[d].data(), sizeof(int2) * pitems[d].size(),
-                             hipMemcpyHostToDevice));
-    }
+    for (int p = 0; p < 2; ++p)
+        for (int d = 0; d < 3; ++d)
+            for (int t = 0; t < 2; ++t) {
+                const std::vector<int2>& v = t ? titems[p][d] : items[p][d];
+                int2*& dst = t ? b->d_titems[p][d] : b->d_items[p][d];
+                (t ? b->ntitems : b->nitems)[p][d] = (int)v.size();
+                if (v.empty()) continue;
+                HIP_TRY(b, hipMalloc(&dst, sizeof(int2) * v.size()));
+                HIP_TRY(b, hipMemcpy(dst, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice));
+            }
     return MHD_OK;
 }
 
@@ -206,8 +228,10 @@ extern "C" mhd_batch* mhd_batch_create(int nbox, const int* dims, double gamma, 
     b->wide = false;
     b->d_boxes = nullptr;
     for (int d = 0; d < 3; ++d) {
-        b->d_items[d] = b->d_pitems[d] = nullptr;
-        b->nitems[d] = b->npitems[d] = 0;
+        for (int p = 0; p < 2; ++p) {
+            b->d_items[p][d] = b->d_titems[p][d] = nullptr;
+            b->nitems[p][d] = b->ntitems[p][d] = 0;
+        }
         b->grid[d] = 1024;
     }
     b->buf[0] = b->buf[1] = nullptr;
@@ -409,6 +433,22 @@ static bool batch_mid_fused(const mhd_batch* b)
     return b->mid_mode == 1;
 }
 
+// what a step runs: the reports above are the marches' choice; where every
+// box runs the pairs in tiles and the choice is the library's, the pairs, and
+// in FP32 with van Leer's limiter the middle, are one launch each (the
+// launches of a step flip the fields' buffers, so one choice holds for all
+// boxes)
+static bool run_pairs_fused(const mhd_batch* b)
+{
+    return batch_pairs_fused(b) || (b->rev_mode == 0 && all_tiles(b, 1) && all_tiles(b, 2));
+}
+static bool run_mid_fused(const mhd_batch* b)
+{
+    if (batch_mid_fused(b)) return true;
+    return b->mid_mode == 0 && batch_pairs_fused(b) && b->prec == MHD_F32 && b->limiter == MHD_LIMITER_VANLEER &&
+           all_tiles(b, 2);
+}
+
 template <typename T>
 static int enqueue_batch_step(mhd_batch* b, double cfl)
 {
@@ -421,8 +461,7 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
     } else {
         HIP_TRY(b, launch_batch_cfl<T>(base, b->d_boxes, b->d_cfl_items, b->n_cfl_items,
                                        b->d_item_first, b->nbox, b->gamma, cfl, b->partial,
-                                       b->partial_bad, b->scal, b->flag, b->stream));
-        HIP_TRY(b, launch_batch_clear_acc(b->cfl_acc, b->nbox, b->stream));
+                                       b->partial_bad, b->scal, b->flag, b->cfl_acc, b->stream));
     }
     b->acc_valid = false;
     // (op, d): op 0 fluid, 1 magnetic, 2 the reverse-half pair in one launch
@@ -432,7 +471,7 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
                                      { 2, 2 }, { 2, 1 }, { 2, 0 } };
     // op 3: the middle M_z M_z F_z in one launch
     static const int middle[8][2] = { { 0, 0 }, { 1, 0 }, { 0, 1 }, { 1, 1 }, { 0, 2 }, { 3, 2 }, { 2, 1 }, { 2, 0 } };
-    const bool fz = batch_pairs_fused(b), mid = fz && batch_mid_fused(b);
+    const bool fz = run_pairs_fused(b), mid = fz && run_mid_fused(b);
     const int nops = mid ? 8 : fz ? 9 : 12;
     for (int k = 0; k < nops; ++k) {
         const int op = mid ? middle[k][0] : fz ? fused[k][0] : separate[k][0];
@@ -445,9 +484,7 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
         P.boxes = b->d_boxes;
         // the fused pairs along y and z (and the middle) have work lists of
         // their own chunks
-        const bool pl = (op == 2 || op == 3) && d > 0;
-        P.items = pl ? b->d_pitems[d] : b->d_items[d];
-        P.nitems = pl ? b->npitems[d] : b->nitems[d];
+        const int pl = (op == 2 || op == 3) && d > 0;
         P.gamma = (T)b->gamma;
         P.scal = b->scal;
         P.flag = b->flag;
@@ -458,14 +495,19 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
         P.gamma64 = b->gamma;
         for (const BoxDesc& bd : b->boxes)
             if ((unsigned long long)bd.ncell * (b->prec == MHD_F64 ? 8 : 4) > (1ull << 32)) P.offsets32 = false;
-        const int grid = std::max(8, std::min(b->grid[d], (P.nitems + 7) / 8 * 8));
-        HIP_TRY(b, launch_batch_op<T>(P, op, d, grid, b->stream));
+        for (int t = 0; t < 2; ++t) {
+            P.items = t ? b->d_titems[pl][d] : b->d_items[pl][d];
+            P.nitems = t ? b->ntitems[pl][d] : b->nitems[pl][d];
+            if (!P.nitems) continue;
+            const int grid = std::max(8, std::min(b->grid[d], (P.nitems + 7) / 8 * 8));
+            HIP_TRY(b, t ? launch_batch_tile_op<T>(P, op, d, grid, b->stream)
+                         : launch_batch_op<T>(P, op, d, grid, b->stream));
+        }
         if (op != 1)
             for (int q = 0; q < 5; ++q) b->cur[q] = 1 - b->cur[q];
         if (op != 0)
             for (int q = 5; q < 8; ++q) b->cur[q] = 1 - b->cur[q];
     }
-    HIP_TRY(b, launch_batch_advance(b->scal, b->flag, b->nbox, b->stream));
     b->acc_valid = true;
     return MHD_OK;
 }
@@ -505,7 +547,7 @@ extern "C" int mhd_batch_run(mhd_batch* b, double cfl, int nsteps, int use_graph
     if (nsteps == 0) return MHD_OK;
     // with the fused middle a step moves the face fields to the other
     // buffer: the graph holds two steps and starts from one buffer of them
-    const int gs = batch_mid_fused(b) ? 2 : 1;
+    const int gs = run_mid_fused(b) ? 2 : 1;
     if (b->graph_valid && (b->graph_cfl != cfl || b->graph_steps != gs)) drop_graph(b);
     if (gs == 2 && b->graph_valid && b->cur[5] != b->graph_bpar) {
         if ((r = enqueue_step(b, cfl))) return r;
@@ -594,8 +636,7 @@ extern "C" int mhd_batch_set_launch(mhd_batch* b, int key, int value)
     if (key == MHD_BATCH_WIDE_OFFSETS) {
         if (value < 0 || value > 1) return mhd_fail(MHD_EINVAL, "wide-offset switch must be 0 or 1 (got %d)", value);
         b->wide = value == 1;
-        drop_graph(b);
-        return MHD_OK;
+        return build_lists(b);      // wide offsets run no tiles
     }
     if (key == MHD_BATCH_REVERSE) {
         if (value < 0 || value > 2)

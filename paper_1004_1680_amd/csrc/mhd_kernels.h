@@ -130,6 +130,15 @@ struct BatchParams {
 template <typename T>
 hipError_t launch_batch_op(const BatchParams<T>& B, int op, int d, int grid, hipStream_t s);
 
+// the same for a list of tile items along y or z: item (box, tile), a tile
+// being batch_tile_pencils(n[d]) whole pencils of the box
+template <typename T>
+hipError_t launch_batch_tile_op(const BatchParams<T>& B, int op, int d, int grid, hipStream_t s);
+// longest pencils the ensembles run in tiles, and the pencils of a tile (256
+// threads, 4 cells each)
+constexpr int BATCH_TILE_CELLS = 64;
+__host__ __device__ inline int batch_tile_pencils(int nd) { return 256 / (nd / 4); }
+
 template <typename T>
 struct BatchCflArgs {
     const T* base[8];             // buffer holding the current copy of each field
@@ -141,17 +150,16 @@ struct BatchCflArgs {
 // item_first[b+1]-1 are box b's items
 constexpr int CFL_CELLS = 2048;
 // per box, dt / relaxation speed / non-physical flag from the maxima the
-// fused CFL accumulated (the rules of batch_cfl_final), then clears them
+// fused CFL accumulated (the rules of batch_cfl_final), then clears them.
+// Both also advance the time of the step they open.
 hipError_t launch_batch_cfl_from_acc(unsigned long long* acc, const BoxDesc* boxes, int nbox, double cfl,
                                      double* scal, int* flag, hipStream_t s);
-hipError_t launch_batch_clear_acc(unsigned long long* acc, int nbox, hipStream_t s);
 
 template <typename T>
 hipError_t launch_batch_cfl(const T* const base[8], const BoxDesc* boxes, const int2* items,
                             int nitems, const int* item_first, int nbox, double gamma,
                             double cfl, double* partial, int* partial_bad, double* scal,
-                            int* flag, hipStream_t s);
-hipError_t launch_batch_advance(double* scal, int* flag, int nbox, hipStream_t s);
+                            int* flag, unsigned long long* acc, hipStream_t s);
 
 template <typename T>
 hipError_t launch_fluid(const SweepParams<T>& P, int d, const LaunchTuning& tune, hipStream_t s);

@@ -265,9 +265,12 @@ __global__ void __launch_bounds__(RED_THREADS) batch_cfl_partial_kernel(
 // of the box, or its non-physical flag (then dt = 0)
 __global__ void __launch_bounds__(RED_THREADS) batch_cfl_final_kernel(
     const double* partial, const int* partial_bad, const int* item_first, const BoxDesc* boxes,
-    double cfl, double* scal, int* flag)
+    double cfl, double* scal, int* flag, unsigned long long* acc)
 {
     const int b = blockIdx.x;
+    // the box's fused-CFL accumulator, cleared for the step to come
+    acc[(size_t)b * (CFL_ACC_SLOTS + 1) + threadIdx.x] = 0;
+    if (threadIdx.x == 0) acc[(size_t)b * (CFL_ACC_SLOTS + 1) + CFL_ACC_SLOTS] = 0;
     double m = 0.0;
     int bad = 0;
     for (int i = item_first[b] + threadIdx.x; i < item_first[b + 1]; i += RED_THREADS) {
@@ -285,16 +288,8 @@ __global__ void __launch_bounds__(RED_THREADS) batch_cfl_final_kernel(
         double vmax = smax[0];
         int bb = sbad[0];
         for (int q = 1; q < RED_THREADS / 64; ++q) { vmax = fmax(vmax, smax[q]); bb |= sbad[q]; }
-        double* sc = scal + (size_t)b * SCAL_COUNT;
-        if (bb || !(vmax > 0.0)) {
-            sc[SCAL_DT] = 0.0;
-            sc[SCAL_VMAX] = 0.0;
-            flag[(size_t)b * FLAG_COUNT + FLAG_NONPHYS] = bb ? 1 : 2;
-        } else {
-            sc[SCAL_DT] = cfl * (1.0 / (double)boxes[b].n[0]) / vmax;
-            sc[SCAL_VMAX] = vmax;
-            sc[SCAL_C] = vmax;
-        }
+        cfl_finish(vmax, bb ? 1 : 0, boxes[b].n[0], cfl, scal + (size_t)b * SCAL_COUNT, flag + (size_t)b * FLAG_COUNT,
+                   true, nullptr);
     }
 }
 
@@ -302,7 +297,7 @@ template <typename T>
 hipError_t launch_batch_cfl(const T* const base[8], const BoxDesc* boxes, const int2* items,
                             int nitems, const int* item_first, int nbox, double gamma,
                             double cfl, double* partial, int* partial_bad, double* scal,
-                            int* flag, hipStream_t s)
+                            int* flag, unsigned long long* acc, hipStream_t s)
 {
     BatchCflArgs<T> A;
     for (int q = 0; q < 8; ++q) A.base[q] = base[q];
@@ -311,15 +306,15 @@ hipError_t launch_batch_cfl(const T* const base[8], const BoxDesc* boxes, const 
     hipLaunchKernelGGL(batch_cfl_partial_kernel<T>, dim3(nitems), dim3(RED_THREADS), 0, s, A,
                        gamma, partial, partial_bad);
     hipLaunchKernelGGL(batch_cfl_final_kernel, dim3(nbox), dim3(RED_THREADS), 0, s, partial,
-                       partial_bad, item_first, boxes, cfl, scal, flag);
+                       partial_bad, item_first, boxes, cfl, scal, flag, acc);
     return hipGetLastError();
 }
 template hipError_t launch_batch_cfl<float>(const float* const[8], const BoxDesc*, const int2*,
                                             int, const int*, int, double, double, double*, int*,
-                                            double*, int*, hipStream_t);
+                                            double*, int*, unsigned long long*, hipStream_t);
 template hipError_t launch_batch_cfl<double>(const double* const[8], const BoxDesc*, const int2*,
                                              int, const int*, int, double, double, double*, int*,
-                                             double*, int*, hipStream_t);
+                                             double*, int*, unsigned long long*, hipStream_t);
 
 // box b (one block of CFL_ACC_SLOTS threads per box): the rules of
 // batch_cfl_final_kernel on the maxima the fused CFL accumulated; clears them
@@ -338,16 +333,8 @@ __global__ void __launch_bounds__(CFL_ACC_SLOTS) batch_cfl_from_acc_kernel(unsig
         double vmax = smax[0];
         for (int q = 1; q < CFL_ACC_SLOTS / 64; ++q) vmax = fmax(vmax, smax[q]);
         const int bb = (int)a[CFL_ACC_SLOTS];
-        double* sc = scal + (size_t)b * SCAL_COUNT;
-        if (bb || !(vmax > 0.0)) {
-            sc[SCAL_DT] = 0.0;
-            sc[SCAL_VMAX] = 0.0;
-            flag[(size_t)b * FLAG_COUNT + FLAG_NONPHYS] = (bb & 1) ? 1 : 2;
-        } else {
-            sc[SCAL_DT] = cfl * (1.0 / (double)boxes[b].n[0]) / vmax;
-            sc[SCAL_VMAX] = vmax;
-            sc[SCAL_C] = vmax;
-        }
+        cfl_finish(vmax, bb ? ((bb & 1) ? 1 : 2) : 0, boxes[b].n[0], cfl, scal + (size_t)b * SCAL_COUNT,
+                   flag + (size_t)b * FLAG_COUNT, true, nullptr);
         a[CFL_ACC_SLOTS] = 0;
     }
     a[threadIdx.x] = 0;
@@ -357,35 +344,6 @@ hipError_t launch_batch_cfl_from_acc(unsigned long long* acc, const BoxDesc* box
                                      double* scal, int* flag, hipStream_t s)
 {
     hipLaunchKernelGGL(batch_cfl_from_acc_kernel, dim3(nbox), dim3(CFL_ACC_SLOTS), 0, s, acc, boxes, cfl, scal, flag);
-    return hipGetLastError();
-}
-
-__global__ void batch_clear_acc_kernel(unsigned long long* acc)
-{
-    unsigned long long* a = acc + (size_t)blockIdx.x * (CFL_ACC_SLOTS + 1);
-    a[threadIdx.x] = 0;
-    if (threadIdx.x == 0) a[CFL_ACC_SLOTS] = 0;
-}
-
-hipError_t launch_batch_clear_acc(unsigned long long* acc, int nbox, hipStream_t s)
-{
-    hipLaunchKernelGGL(batch_clear_acc_kernel, dim3(nbox), dim3(CFL_ACC_SLOTS), 0, s, acc);
-    return hipGetLastError();
-}
-
-// per-box time advance (skipped for a box with a non-physical record)
-__global__ void batch_advance_kernel(double* scal, int* flag, int nbox)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b < nbox && flag[(size_t)b * FLAG_COUNT + FLAG_NONPHYS] == 0) {
-        scal[(size_t)b * SCAL_COUNT + SCAL_TIME] += 2.0 * scal[(size_t)b * SCAL_COUNT + SCAL_DT];
-        flag[(size_t)b * FLAG_COUNT + FLAG_STEPS] += 1;
-    }
-}
-
-hipError_t launch_batch_advance(double* scal, int* flag, int nbox, hipStream_t s)
-{
-    hipLaunchKernelGGL(batch_advance_kernel, dim3((nbox + 63) / 64), dim3(64), 0, s, scal, flag, nbox);
     return hipGetLastError();
 }
 

@@ -9,4 +9,5 @@ template hipError_t launch_magnetic<float>(const SweepParams<float>&, int, const
 template hipError_t launch_magfluid<float>(const SweepParams<float>&, int, const LaunchTuning&, hipStream_t);
 template hipError_t launch_magmagfluid<float>(const SweepParams<float>&, int, const LaunchTuning&, hipStream_t);
 template hipError_t launch_batch_op<float>(const BatchParams<float>&, int, int, int, hipStream_t);
+template hipError_t launch_batch_tile_op<float>(const BatchParams<float>&, int, int, int, hipStream_t);
 }  // namespace mhd

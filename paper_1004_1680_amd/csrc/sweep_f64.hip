@@ -10,4 +10,5 @@ template hipError_t launch_magnetic<double>(const SweepParams<double>&, int, con
 template hipError_t launch_magfluid<double>(const SweepParams<double>&, int, const LaunchTuning&, hipStream_t);
 template hipError_t launch_magmagfluid<double>(const SweepParams<double>&, int, const LaunchTuning&, hipStream_t);
 template hipError_t launch_batch_op<double>(const BatchParams<double>&, int, int, int, hipStream_t);
+template hipError_t launch_batch_tile_op<double>(const BatchParams<double>&, int, int, int, hipStream_t);
 }  // namespace mhd

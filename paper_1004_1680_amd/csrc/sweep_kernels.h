@@ -2166,6 +2166,29 @@ constexpr int batch_waves(int d)
     return d == 0 ? 1 : (OP == 3 ? 1 : OP == 2 ? magfluid_waves<T>() : march_waves<T>());
 }
 
+// The tile kernels' form for the boxes of a work list whose pencils along y
+// or z are short and whole (32-bit offsets): bd.n[D] / 4 threads per pencil,
+// as many pencils as 256 threads hold.  The tile functions leave LDS to the
+// next item as they leave it between two operators of one item: every
+// region is rewritten only after a barrier that follows its last read.
+template <typename T, int OP, int D, int LIM>
+__global__ void __launch_bounds__(256, (sizeof(T) == 4 ? 3 : 2)) batch_tile_kernel(BatchParams<T> B)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int g8 = gridDim.x >> 3;
+    const int xcd = blockIdx.x & 7, r = blockIdx.x >> 3;
+    const int per = (B.nitems + 7) >> 3;
+    const int i0 = xcd * per;
+    const int i1 = min(B.nitems, i0 + per);
+    for (int i = i0 + r; i < i1; i += g8) {
+        const int2 it = B.items[i];
+        const BoxDesc bd = B.boxes[it.x];
+        const SweepParams<T> P = box_params(B, it.x, bd);
+        const int tg = bd.n[D] / 4;
+        sweep_tile<T, OP, D, LIM>(P, it.y, batch_tile_pencils(bd.n[D]), tg, reinterpret_cast<T*>(smem_raw));
+    }
+}
+
 // W32: every box's fields have 32-bit byte offsets (see Addr)
 // CFL (x fluid operator or x pair only): also accumulate each box's CFL
 // maximum of the result (B.cfl_acc)
@@ -2184,11 +2207,11 @@ __global__ void __launch_bounds__(256, (batch_waves<T, OP>(D))) batch_sweep_kern
         const SweepParams<T> P = box_params(B, it.x, bd);
         if constexpr (D == 0) {
             if constexpr (OP == 0)
-                fluid_x_tile<T, CFL, LIM>(P, it.y, bd.tpr, bd.rpw, reinterpret_cast<T*>(smem_raw));
+                fluid_x_tile<T, CFL, LIM, FRZ_STEP, W32>(P, it.y, bd.tpr, bd.rpw, reinterpret_cast<T*>(smem_raw));
             else if constexpr (OP == 1)
-                mag_x_tile<T, LIM>(P, it.y, bd.tpr, bd.rpw, reinterpret_cast<T*>(smem_raw));
+                mag_x_tile<T, LIM, W32>(P, it.y, bd.tpr, bd.rpw, reinterpret_cast<T*>(smem_raw));
             else
-                magfluid_x_tile<T, CFL, LIM>(P, it.y, bd.tpr, bd.rpw, reinterpret_cast<T*>(smem_raw));
+                magfluid_x_tile<T, CFL, LIM, W32>(P, it.y, bd.tpr, bd.rpw, reinterpret_cast<T*>(smem_raw));
         } else {
             const long gid = (long)it.y * blockDim.x + threadIdx.x;
             if constexpr (OP == 0)
@@ -2206,16 +2229,18 @@ __global__ void __launch_bounds__(256, (batch_waves<T, OP>(D))) batch_sweep_kern
 template <typename T, int OP, int LIM>
 static void launch_batch_op_dir(const BatchParams<T>& B, int d, int grid, size_t lds, hipStream_t s)
 {
-    // x tiles have no march addressing: one instantiation (two for the
-    // operators that can end a step: with and without the fused CFL)
+    // two instantiations for the x operators that can end a step: with and
+    // without the fused CFL
     if (d == 0) {
         if constexpr (OP != 1) {
             if (B.cfl_acc) {
-                hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 0, true, LIM, true>), dim3(grid), dim3(256), lds, s, B);
+                if (B.offsets32) hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 0, true, LIM, true>), dim3(grid), dim3(256), lds, s, B);
+                else hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 0, false, LIM, true>), dim3(grid), dim3(256), lds, s, B);
                 return;
             }
         }
-        hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 0, true, LIM>), dim3(grid), dim3(256), lds, s, B);
+        if (B.offsets32) hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 0, true, LIM>), dim3(grid), dim3(256), lds, s, B);
+        else hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 0, false, LIM>), dim3(grid), dim3(256), lds, s, B);
     } else if (B.offsets32) {
         if (d == 1) hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 1, true, LIM>), dim3(grid), dim3(256), lds, s, B);
         else hipLaunchKernelGGL((batch_sweep_kernel<T, OP, 2, true, LIM>), dim3(grid), dim3(256), lds, s, B);
@@ -2236,6 +2261,33 @@ static void launch_batch_op_lim(const BatchParams<T>& B, int op, int d, int grid
         if (B.offsets32) hipLaunchKernelGGL((batch_sweep_kernel<T, 3, 2, true, LIM>), dim3(grid), dim3(256), 0, s, B);
         else hipLaunchKernelGGL((batch_sweep_kernel<T, 3, 2, false, LIM>), dim3(grid), dim3(256), 0, s, B);
     }
+}
+
+template <typename T, int LIM>
+static void launch_batch_tile_lim(const BatchParams<T>& B, int op, int d, int grid, hipStream_t s)
+{
+    const size_t lds = sizeof(T) * (op == 1 ? 16 : 25) * 256;
+#define MHD_TILE_LAUNCH(OP, D) hipLaunchKernelGGL((batch_tile_kernel<T, OP, D, LIM>), dim3(grid), dim3(256), lds, s, B)
+    if (op == 0) { if (d == 1) MHD_TILE_LAUNCH(0, 1); else MHD_TILE_LAUNCH(0, 2); }
+    else if (op == 1) { if (d == 1) MHD_TILE_LAUNCH(1, 1); else MHD_TILE_LAUNCH(1, 2); }
+    else if (op == 2) { if (d == 1) MHD_TILE_LAUNCH(2, 1); else MHD_TILE_LAUNCH(2, 2); }
+    else if constexpr (sizeof(T) == 4 && LIM == LIM_VANLEER) MHD_TILE_LAUNCH(3, 2);
+#undef MHD_TILE_LAUNCH
+}
+
+template <typename T>
+hipError_t launch_batch_tile_op(const BatchParams<T>& B, int op, int d, int grid, hipStream_t s)
+{
+    if (d == 0 || B.cfl_acc || !B.offsets32) return hipErrorInvalidValue;
+    if (op == 3 && (d != 2 || sizeof(T) != 4 || B.limiter != LIM_VANLEER)) return hipErrorInvalidValue;
+    switch (B.limiter) {
+    case LIM_VANLEER: launch_batch_tile_lim<T, LIM_VANLEER>(B, op, d, grid, s); break;
+    case LIM_MINMOD: launch_batch_tile_lim<T, LIM_MINMOD>(B, op, d, grid, s); break;
+    case LIM_MC: launch_batch_tile_lim<T, LIM_MC>(B, op, d, grid, s); break;
+    case LIM_SUPERBEE: launch_batch_tile_lim<T, LIM_SUPERBEE>(B, op, d, grid, s); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 template <typename T>

@@ -81,3 +81,33 @@ def test_tiles_keep_a_recorded_state(M, prec):
         S.status()
     assert np.array_equal(S.get_state(), before)
     S.close()
+
+
+@pytest.mark.parametrize("prec,lim", [("f32", 0), ("f32", 2), ("f64", 0)])
+@pytest.mark.parametrize("dims", [[(16, 8, 12), (20, 64, 36), (8, 60, 64)],
+                                  [(16, 12, 8), (20, 64, 68), (24, 72, 64), (36, 132, 8)]])
+def test_ensembles_with_tiles(M, dims, prec, lim):
+    # boxes that run y and z in tiles, in marches, and one axis in each:
+    # every box is the single grid bit for bit, eagerly and from the graph
+    # (odd step counts: with the middle in one launch it holds two steps)
+    say(f"case: ensemble with tiles {dims} {prec} limiter {lim}")
+    states = [smooth_state(n, seed=63 + i) for i, n in enumerate(dims)]
+    for graph in (False, True):
+        B = M.Batch(dims, prec=prec)
+        B.set_limiter(lim)
+        for i, s in enumerate(states):
+            B.set_state(i, s)
+        for k in (1, 3, 2):
+            B.run(k, 0.5, graph=graph)
+        steps, _ = B.status()
+        assert (steps == 6).all()
+        times = B.times()
+        for i, (n, s) in enumerate(zip(dims, states)):
+            S = M.Solver(n, prec=prec)
+            S.set_limiter(lim)
+            S.set_state(s)
+            for _ in range(6):
+                S.step_auto(0.5)
+            assert np.array_equal(B.get_state(i), S.get_state()) and times[i] == S.time(), (i, graph)
+            S.close()
+        B.close()
