@@ -7,9 +7,9 @@
 namespace mhd {
 
 enum {
-    EPI_BIAS_RELU = 0,   // y = relu(acc + bias) -> bf16 (+ channel-major copy)
+    EPI_BIAS_RELU = 0,   // y = relu(acc + bias) -> bf16
     EPI_BIAS_F32 = 1,    // y = acc + bias -> fp32
-    EPI_MASK = 2,        // y = acc * (mask > 0) -> bf16 (+ channel-major copy)
+    EPI_MASK = 2,        // y = acc * (mask > 0) -> bf16
     EPI_F32 = 3          // y = acc -> fp32
 };
 
@@ -21,17 +21,24 @@ struct ConvArgs {
     const uint16_t* mask;   // bf16 [cell][cout] (EPI_MASK)
     float* yf;              // fp32 [cell][cout]
     uint16_t* yb;           // bf16 [cell][cout]
-    uint16_t* ybT;          // bf16 [cout][cell] or null
 };
 
 struct WgradArgs {
     int n[3];
-    const uint16_t* xT;     // bf16 [cin][cell]
-    const uint16_t* dyT;    // bf16 [cout][cell]
-    float* partial;         // [workgroups + 16][27][cin][cout] (partial sums, then the reduction's)
-    int tiles_per_wg;
+    const uint16_t* x;      // bf16 [cell][cin]
+    const uint16_t* dy;     // bf16 [cell][cout]
+    float* partial;         // [workgroups][27][cin][cout]
+    double* bias_partial;   // [workgroups][cout]
 };
 constexpr int WGRAD_MAX_WG = 512;   // persistent workgroups of wgrad (bounds the partial sums)
+// a layer of a reduction of partial sums
+struct WgradLayer {
+    const float* partial;
+    const double* bias_partial;
+    float* dw;              // [27][cin][cout]
+    float* dbias;           // [cout]
+    int count, cout;        // 27 cin cout (a multiple of 64)
+};
 
 // packed size (bf16 elements) of a layer's weights
 inline size_t packed_weight_elems(int cin, int cout)
@@ -41,11 +48,10 @@ inline size_t packed_weight_elems(int cin, int cout)
 
 hipError_t launch_pack_weights(const float* w, int cin, int cout, int flip, uint16_t* wp, hipStream_t s);
 hipError_t launch_conv3d(const ConvArgs& A, int cin, int cout, int epi, hipStream_t s);
-int wgrad_blocks(const int n[3], int& tiles_per_wg);   // workgroups of a wgrad launch
-hipError_t launch_conv3d_wgrad(const WgradArgs& A, int cin, int cout, float* dw, hipStream_t s);
-constexpr int BG_BLOCKS = 64;      // partial sums per channel of the bias gradient (needs BG_BLOCKS * cout doubles)
-hipError_t launch_bias_grad(const uint16_t* dyT, size_t N, int cout, float* dbias, double* partial, hipStream_t s);
-hipError_t launch_to_bf16(const float* src, size_t N, int c, uint16_t* dst, uint16_t* dstT, hipStream_t s);
+int wgrad_blocks(const int n[3]);                       // workgroups of a wgrad launch
+hipError_t launch_conv3d_wgrad(const WgradArgs& A, int cin, int cout, hipStream_t s);
+hipError_t launch_wgrad_reduce(const WgradLayer* layers, int nlayer, int nwg, hipStream_t s);
+hipError_t launch_channel_last(const uint16_t* src, size_t N, int c, uint16_t* dst, hipStream_t s);
 
 // per-channel input normalisation, output and target scales of the closure
 struct ClosureScales {
@@ -53,13 +59,13 @@ struct ClosureScales {
 };
 constexpr int CHSUM_BLOCKS = 512;
 
-hipError_t launch_normalize(const float* u, size_t N, const ClosureScales& sc, uint16_t* x, uint16_t* xT, hipStream_t s);
+hipError_t launch_normalize(const float* u, size_t N, const ClosureScales& sc, uint16_t* x, hipStream_t s);
 hipError_t launch_chsum(const float* a, size_t N, size_t cstride, size_t fstride, int nch, double scale,
                         double* partial, double* out, hipStream_t s);
 hipError_t launch_project(const float* o, const double* mean, const int n[3], const ClosureScales& sc, float* delta,
                           hipStream_t s);
-hipError_t launch_project_T(const float* g, const double* gmean, const int n[3], const ClosureScales& sc, float* go,
-                            hipStream_t s);
+hipError_t launch_project_T(const float* g, const double* gmean, const float* gate, const int n[3],
+                            const ClosureScales& sc, uint16_t* go, hipStream_t s);
 hipError_t launch_loss(const float* delta, const float* target, size_t N, const ClosureScales& sc, float* g,
                        double* partial, double* out, hipStream_t s);
 constexpr int GUARD_LEVELS = 4;     // theta = 1, 1/2, 1/4, 1/8

@@ -11,24 +11,22 @@
 //  * B: activations, channel-last x[cell][CIN]: the 8 K values of a lane are
 //    8 consecutive channels of one shifted cell (one 16-byte load);
 //  * D: 4 consecutive output channels of one cell per lane.
-// A workgroup computes a 16 x 4 x 4 tile of cells x all output channels from
-// an LDS copy of its input halo; each wave one z plane (4 rows of 16 cells).  dgrad is the same kernel on the gradient with the weights
-// flipped (o -> 26 - o) and transposed (ci <-> co), with the ReLU mask of
+// A workgroup computes tiles of cells x all output channels from an LDS copy
+// of the tile's input halo.  dgrad is the same kernel on the gradient with
+// the weights flipped (o -> 26 - o) and transposed (ci <-> co), with the ReLU mask of
 // the forward activation fused in the epilogue.
 //
 // wgrad, dW[o][ci][co] = sum_cell x[cell + d(o)][ci] dy[cell][co], has K =
-// cells: it reads channel-major copies xT[ci][cell], dyT[co][cell] written
-// by the producing kernels, so a lane's 8 K values are 8 consecutive cells
-// of one channel.  A workgroup stages a tile of x with its halo in LDS; each
-// of its 9 waves owns one (dy, dz) pair and builds the dx = -1, 0, +1
-// fragments from three aligned 16-byte reads.  Persistent workgroups write
-// partial sums, which two passes add in a fixed order (deterministic).
+// cells and reads the same channel-last activations through transposing LDS
+// reads.  Persistent workgroups write partial sums, which are added in a
+// fixed order (deterministic).
 //
-// Requirements: nx, ny, nz multiples of 32 (the tiles: 16 x 4 x 4 cells for
-// forward / dgrad, 32 x 4 x 2 for wgrad), fewer than 2^31 cells.
+// Requirements: nx, ny, nz multiples of 32 (the tiles: 16 x 4 x 4 or 8 cells
+// for forward / dgrad, 32 x 4 x 2 for wgrad), fewer than 2^31 cells.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "closure_kernels.h"
 
@@ -37,12 +35,12 @@ namespace mhd {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f4;
 
-__device__ __forceinline__ uint16_t f2bf(float f)
+// bf16 rounding to nearest even (v_cvt_pk_bf16_f32 converts two at a time)
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi)
 {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (uint16_t)((u >> 16) | 0x40);
-    u += 0x7fffu + ((u >> 16) & 1u);          // round to nearest even
-    return (uint16_t)(u >> 16);
+    typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf2;
+    return __builtin_bit_cast(uint32_t, bf2{ (__bf16)lo, (__bf16)hi });
 }
 __device__ __forceinline__ float bf2f(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 
@@ -93,171 +91,360 @@ hipError_t launch_pack_weights(const float* w, int cin, int cout, int flip, uint
 // forward / dgrad convolution
 // ---------------------------------------------------------------------------
 
-// Output tile of a workgroup: 16 (x) x 4 (y) x 4 (z) cells; wave w takes
-// the z plane w, its 4 MFMA column blocks the 4 rows y, lane r the cell x.
-// The input halo (18 x 6 x 6 cells, periodic) is staged once in LDS and
-// every one of the 27 offsets reads its B fragments from there.  A B read
-// has 16 lanes on 16 consecutive cells reading the same 16-byte chunk; with
-// 64-byte cells (CIN = 32) the chunks of cells h and h + 4 would share
-// banks, so chunk q of cell h is stored at position q ^ 2 ((h >> 2) & 1):
-// any 8 consecutive cells then fall on distinct bank groups (measured on
+// Persistent workgroups of 8 waves, one per CU.  A wave keeps its weights in
+// registers for the whole launch (read from L2 once per workgroup, where a
+// workgroup per tile read 55 KiB per wave and tile, as many L1 cycles as MFMA
+// cycles), and the next tile's halo is fetched into registers while the
+// current tile is multiplied from LDS (two buffers, one barrier per tile).
+// A wave takes 16 output channels of one z plane: with 32 output channels two
+// waves share a plane (tile 16 x 4 x 4 cells), with 8 one wave does (16 x 4 x
+// 8).  Its weights are 27 fragments (108 registers) with 32 input channels,
+// one offset per K step, and 7 with 8, four offsets per K step.
+// A wave's 4 MFMA column blocks are the 4 rows y of its plane, lane r the
+// cell x.  The input halo is staged in LDS once per tile, rows of 20 cells.
+// A B read has 16 lanes on 16 consecutive cells reading the same 16-byte
+// chunk; with 64-byte cells (CIN = 32) the chunks of cells h and h + 4 would
+// share banks, so chunk q of cell h is stored at position q ^ 2 ((h >> 2) &
+// 1): any 8 consecutive cells then fall on distinct bank groups (measured on
 // gfx950: a lane stride that is an odd multiple of 32 bytes modulo 256, or
-// this swizzle, is conflict-free; 64 or 80 bytes costs two passes).
-constexpr int CT_X = 16, CT_Y = 4, CT_Z = 4;
-constexpr int CH_X = CT_X + 2, CH_Y = CT_Y + 2, CH_Z = CT_Z + 2, CH_CELLS = CH_X * CH_Y * CH_Z;
+// this swizzle, is conflict-free; 64 or 80 bytes costs two passes).  With
+// rows of 20 cells the swizzle only flips from row to row, so a lane needs
+// two base addresses and every row is an immediate offset.
+constexpr int CT_X = 16, CT_Y = 4;
+constexpr int CH_X = CT_X + 2, CH_Y = CT_Y + 2;
+constexpr int CL_X = 20;         // LDS cells per halo row (18 used)
+constexpr int CONV_WAVES = 8, CONV_THREADS = 64 * CONV_WAVES;
 
-template <int CIN>
-__host__ __device__ constexpr int conv_cell_stride() { return CIN; }
+template <int CIN, int COUT>
+struct ConvShape {
+    static constexpr int MB = (COUT + 15) / 16;            // 16-row blocks of output channels
+    static constexpr int MBW = 1;                          // of them in a wave
+    static constexpr int WM = MB / MBW;                    // waves that share a z plane
+    static constexpr int TZ = CONV_WAVES / WM;             // z planes of a tile
+    static constexpr int CELLS = CH_X * CH_Y * (TZ + 2);   // halo cells
+    static constexpr int LDS = CL_X * CH_Y * (TZ + 2) * CIN;   // bf16 values of a buffer
+    static constexpr int PARTS = CIN / 8;                  // 16-byte pieces per cell
+    static constexpr int KS = (27 * CIN + 31) / 32;
+    static constexpr int FILL = (CELLS * PARTS + CONV_THREADS - 1) / CONV_THREADS;
+};
 // position (in 8-bf16 chunks) of chunk q of halo cell h
 template <int CIN>
 __device__ __forceinline__ int conv_chunk(int h, int q) { return CIN == 32 ? (q ^ (((h >> 2) & 1) << 1)) : q; }
 
-template <int CIN, int COUT, int EPI>
-__global__ void __launch_bounds__(256) conv3d_kernel(ConvArgs A)
+// Visit order of the tiles.  A tile's halo is 2.1 to 2.5 times its cells, so
+// what neighbouring tiles read in common has to come from L2, and each XCD has
+// its own (the hardware deals workgroups round-robin over the 8): XCD k takes
+// the k-th eighth of the visits, which go in columns of CONV_YG tiles along y
+// through z with all x tiles of a z in turn, so that the planes shared with
+// the next z are read again a few dozen visits later.  (Grids are multiples of
+// 32: the number of tiles is a multiple of 16 and ty of 8.)
+constexpr int CONV_YG = 4;
+__device__ __forceinline__ void conv_tile(int o, int tx, int tz, int& x, int& y, int& z)
 {
-    constexpr int KS = (27 * CIN + 31) / 32;
-    constexpr int MB = (COUT + 15) / 16;
-    constexpr int NB = CT_Y;
-    constexpr int CS = conv_cell_stride<CIN>();
-    constexpr int PARTS = CIN / 8;                         // 16-byte pieces per cell
-    __shared__ __align__(16) uint16_t tile[CH_CELLS * CS];
+    x = o % tx;
+    const int q = o / tx, w = q / CONV_YG;
+    y = (w / tz) * CONV_YG + q % CONV_YG;
+    z = w % tz;
+}
+
+// the fragment of cells x from those of x - 1 and x + 1 (16 lanes of a K
+// chunk): lanes 0 - 11 take the next lane's x - 1, lanes 12 - 15 the previous
+// lane's x + 1
+__device__ __forceinline__ bf16x8 between(bf16x8 left, bf16x8 right)
+{
+    typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i4;
+    const i4 l = __builtin_bit_cast(i4, left), r = __builtin_bit_cast(i4, right);
+    i4 o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int a = __builtin_amdgcn_update_dpp(0, l[q], 0x101, 0xf, 0x7, false);        // row_shl:1
+        o[q] = __builtin_amdgcn_update_dpp(a, r[q], 0x111, 0xf, 0x8, false);               // row_shr:1
+    }
+    return __builtin_bit_cast(bf16x8, o);
+}
+
+// two bf16 values, each kept where the mask's value is positive
+__device__ __forceinline__ uint32_t masked2(uint32_t v, uint32_t mk)
+{
+    const uint32_t lo = bf2f((uint16_t)(mk & 0xffff)) > 0.0f ? v & 0xffffu : 0u;
+    const uint32_t hi = bf2f((uint16_t)(mk >> 16)) > 0.0f ? v & 0xffff0000u : 0u;
+    return lo | hi;
+}
+
+template <int CIN, int COUT, int EPI>
+__global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
+{
+    using S = ConvShape<CIN, COUT>;
+    constexpr int MBW = S::MBW, NB = CT_Y, KS = S::KS, FILL = S::FILL, PIECES = S::CELLS * S::PARTS;
+    // 32 output channels in bf16 leave through LDS (two buffers, so that the
+    // barrier of a tile is enough): 4 chunks of 16 bytes per cell, chunk q of
+    // cell c at q ^ ((c >> 2) & 3), which spreads 16 cells over the banks
+    constexpr bool STAGED = COUT == 32 && (EPI == EPI_BIAS_RELU || EPI == EPI_MASK);
+    constexpr int OUT = STAGED ? CT_X * CT_Y * S::TZ * COUT : 8;
+    __shared__ __align__(16) uint16_t tiles[2 * S::LDS];
+    __shared__ __align__(16) uint16_t stage[2 * OUT];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, r = lane & 15;
+    const int m0 = (wave % S::WM) * MBW, wz = wave / S::WM;
     const int nx = A.n[0], ny = A.n[1], nz = A.n[2];
-    const long N = (long)nx * ny * nz;
-    const int tx = nx / CT_X, ty = ny / CT_Y;
-    const int b = blockIdx.x;
-    const int x0 = (b % tx) * CT_X, y0 = ((b / tx) % ty) * CT_Y, z0 = (b / (tx * ty)) * CT_Z;
     const uint16_t* __restrict__ x = A.x;
     const uint4* __restrict__ wp = reinterpret_cast<const uint4*>(A.wp);
 
-    // stage the halo: piece q of halo cell h, consecutive threads on
-    // consecutive pieces (contiguous along x in global memory); all loads
-    // of a thread are issued before its LDS writes
-    constexpr int FILL = (CH_CELLS * PARTS + 255) / 256;
+    bf16x8 a[KS][MBW];
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int m = 0; m < MBW; ++m) a[s][m] = as_bf8(wp[((size_t)s * S::MB + m0 + m) * 64 + lane]);
+    float bias[MBW][4];
+#pragma unroll
+    for (int m = 0; m < MBW; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int co = 16 * (m0 + m) + 4 * g + e;
+            bias[m][e] = (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32) && co < COUT ? A.bias[co] : 0.0f;
+        }
+    // waited for here: in the loop the wait would take in the halo loads that
+    // are to stay in flight over the products
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int m = 0; m < MBW; ++m) asm volatile("" : "+v"(a[s][m]));
+#pragma unroll
+    for (int m = 0; m < MBW; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(bias[m][e]));
+
+    // the offsets within a halo fit in 32 bits (any grid of interest)
+    const bool near = (unsigned long long)nx * ny * (S::TZ + 2) * (CIN * 2) < (1ull << 32);
+
+    // visits o, o + stride, ... below end of this workgroup's XCD
+    const int tx = nx / CT_X, tz = nz / S::TZ, per = (tx * (ny / CT_Y) * tz) >> 3;
+    const int stride = gridDim.x >> 3, end = ((blockIdx.x & 7) + 1) * per;
+    int o = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if (o >= end) return;
+
+    // piece q of halo cell h per thread and round, consecutive threads on
+    // consecutive pieces (contiguous along x in global memory); the cell and
+    // its LDS place, one register per round (opaque below, or the compiler
+    // keeps every derived address across the loop and spills)
+    int place[FILL];                                        // LDS offset / 8, hx, hy, hz
     uint4 fv[FILL];
 #pragma unroll
     for (int f = 0; f < FILL; ++f) {
-        const int t = threadIdx.x + 256 * f;
-        fv[f] = make_uint4(0, 0, 0, 0);
-        if (t < CH_CELLS * PARTS) {
-            const int h = t / PARTS, q = t % PARTS;
-            const int hx = h % CH_X, hy = (h / CH_X) % CH_Y, hz = h / (CH_X * CH_Y);
-            const unsigned src = (unsigned)wrap1(x0 - 1 + hx, nx) +
-                                 (unsigned)nx * ((unsigned)wrap1(y0 - 1 + hy, ny) +
-                                                 (unsigned)ny * (unsigned)wrap1(z0 - 1 + hz, nz));
-            fv[f] = ld16(x + (size_t)src * CIN + 8 * q);
-        }
+        // threads past the last piece repeat the first ones (the same values
+        // to the same place), so that no load sits in a branch
+        int t = threadIdx.x + CONV_THREADS * f;
+        t = t < PIECES ? t : t - PIECES;
+        const int h = t / S::PARTS, q = t % S::PARTS;
+        const int hx = h % CH_X, hy = (h / CH_X) % CH_Y, hz = h / (CH_X * CH_Y);
+        const int hl = (hz * CH_Y + hy) * CL_X + hx;
+        place[f] = (hl * S::PARTS + conv_chunk<CIN>(hl, q)) | hx << 14 | hy << 19 | hz << 22 | q << 26;
     }
+    unsigned delta[FILL];                                   // byte offset from the halo's first cell, unwrapped
 #pragma unroll
-    for (int f = 0; f < FILL; ++f) {
-        const int t = threadIdx.x + 256 * f;
-        if (t < CH_CELLS * PARTS) {
-            const int h = t / PARTS, q = t % PARTS;
-            *reinterpret_cast<uint4*>(tile + h * CS + 8 * conv_chunk<CIN>(h, q)) = fv[f];
+    for (int f = 0; f < FILL; ++f)
+        delta[f] = (unsigned)CIN * 2u * ((unsigned)(place[f] >> 14 & 31) +
+                                         (unsigned)nx * ((unsigned)(place[f] >> 19 & 7) + (unsigned)ny * (unsigned)(place[f] >> 22 & 15))) +
+                   16u * (unsigned)(place[f] >> 26 & 3);
+    auto fetch = [&](int v) {
+        int bx, by, bz;
+        conv_tile(v, tx, tz, bx, by, bz);
+        const int x0 = bx * CT_X - 1, y0 = by * CT_Y - 1, z0 = bz * S::TZ - 1;
+        if (bx > 0 && by > 0 && bz > 0 && bx + 1 < tx && by + 1 < ny / CT_Y && bz + 1 < tz && near) {
+            // a halo that does not wrap: one addition per load
+            const char* const p = reinterpret_cast<const char*>(x + (size_t)CIN * ((size_t)x0 + (size_t)nx * ((size_t)y0 + (size_t)ny * z0)));
+#pragma unroll
+            for (int f = 0; f < FILL; ++f) fv[f] = *reinterpret_cast<const uint4*>(p + delta[f]);
+        } else {
+#pragma unroll
+            for (int f = 0; f < FILL; ++f) {
+                int p = place[f];
+                asm volatile("" : "+v"(p));
+                const unsigned src = (unsigned)wrap1(x0 + (p >> 14 & 31), nx) +
+                                     (unsigned)nx * ((unsigned)wrap1(y0 + (p >> 19 & 7), ny) +
+                                                     (unsigned)ny * (unsigned)wrap1(z0 + (p >> 22 & 15), nz));
+                fv[f] = ld16(x + (size_t)src * CIN + 8 * (p >> 26 & 3));
+            }
         }
-    }
+    };
+    auto fill = [&](uint16_t* tile) {
+#pragma unroll
+        for (int f = 0; f < FILL; ++f) {
+            int p = place[f];
+            asm volatile("" : "+v"(p));
+            *reinterpret_cast<uint4*>(tile + 8 * (p & 0x3fff)) = fv[f];
+        }
+    };
+    // products and epilogue of a visit whose halo is in buffer buf; fetched:
+    // the next halo is in registers and goes to the other buffer (last read
+    // before the previous barrier)
+    auto work = [&](int visit, int buf, auto fetched) {
+        const uint16_t* const tile = tiles + buf * S::LDS;
+        f4 acc[MBW][NB];
+#pragma unroll
+        for (int m = 0; m < MBW; ++m)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) acc[m][nb] = f4{ 0.f, 0.f, 0.f, 0.f };
+        if constexpr (CIN == 32) {
+            // one offset per K step.  Read offset by offset, every row of the
+            // halo would be read from LDS nine times (3 dy, 3 dx), twice the
+            // LDS cycles of the MFMA cycles it feeds; here a row is read twice
+            // (dx = -1, +1; dx = 0 by lane shifts of the two) and feeds the
+            // output rows row - dy of all three dy.  Each accumulator adds its offsets in the order
+            // dz, dy, dx.
+            const uint16_t* const plane = tile + wz * (CH_Y * CL_X * CIN);
+            const uint16_t *leftp[2], *rightp[2];           // lane bases of even and odd rows
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                leftp[p] = plane + r * CIN + 8 * conv_chunk<CIN>(4 * p + r, g);
+                rightp[p] = plane + (r + 2) * CIN + 8 * conv_chunk<CIN>(4 * p + r + 2, g);
+            }
+            auto ld_row = [&](const uint16_t* const (&base)[2], int k) {    // row k of the wave's three planes
+                return as_bf8(*reinterpret_cast<const uint4*>(base[k & 1] + k * (CL_X * CIN)));
+            };
+            bf16x8 left = ld_row(leftp, 0), right = ld_row(rightp, 0);
+#pragma unroll
+            for (int k = 0; k < 3 * CH_Y; ++k) {
+                const int dz = k / CH_Y, row = k % CH_Y;
+                bf16x8 left1 = left, right1 = right;
+                if (k + 1 < 3 * CH_Y) {                     // the next row, ahead of this one's products
+                    left1 = ld_row(leftp, k + 1);
+                    right1 = ld_row(rightp, k + 1);
+                }
+                const bf16x8 b[3] = { left, between(left, right), right };
+                // dx outside: consecutive products go to different accumulators
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy) {
+                        const int nb = row - dy;
+                        if (nb < 0 || nb >= NB) continue;
+#pragma unroll
+                        for (int m = 0; m < MBW; ++m)
+                            acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[dz * 9 + dy * 3 + dx][m], b[dx],
+                                                                                 acc[m][nb], 0, 0, 0);
+                    }
+                left = left1;
+                right = right1;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            // 4 offsets per K step, one per K chunk g (offset 27 is padding)
+            const int hbase = (wz + 1) * (CL_X * CH_Y) + CL_X + (r + 1);
+            auto load_b = [&](int s, bf16x8* bv) {
+                const int of = 4 * s + g;
+                const int dx = of % 3 - 1, dy = (of / 3) % 3 - 1, dz = of / 9 - 1;
+                const int h0 = hbase + dz * (CL_X * CH_Y) + dy * CL_X + dx;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    uint4 v = make_uint4(0, 0, 0, 0);
+                    if (of < 27) v = *reinterpret_cast<const uint4*>(tile + (h0 + nb * CL_X) * CIN);
+                    bv[nb] = as_bf8(v);
+                }
+            };
+            bf16x8 b_cur[NB];
+            load_b(0, b_cur);
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                bf16x8 b_nxt[NB];
+                if (s + 1 < KS) load_b(s + 1, b_nxt);
+#pragma unroll
+                for (int m = 0; m < MBW; ++m)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+                        acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s][m], b_cur[nb], acc[m][nb], 0, 0, 0);
+                if (s + 1 < KS)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) b_cur[nb] = b_nxt[nb];
+            }
+        }
+
+        // epilogue: lane holds channels co = 16 (m0 + m) + 4 g + e of cell
+        // (x0 + r, y0 + nb, z0 + wz).  Stored from there, consecutive lanes
+        // would write 8 or 16 bytes 32 to 64 bytes apart, which the memory
+        // pipe takes lane by lane: 128^3, 32 -> 32 channels 162 us, 58 with
+        // no stores at all; 32 -> 8 93 and 42, 8 -> 32 61 and 14.
+        int bx, by, bz;
+        conv_tile(visit, tx, tz, bx, by, bz);
+        const long c0 = (long)(bx * CT_X) + (long)nx * ((long)(by * CT_Y) + (long)ny * (bz * S::TZ));
+#pragma unroll
+        for (int m = 0; m < MBW; ++m) {
+            const int co0 = 16 * (m0 + m) + 4 * g;
+            if (co0 >= COUT) continue;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                const long c = c0 + r + (long)nx * (nb + (long)ny * wz);
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = acc[m][nb][e];
+                    if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32) v[e] += bias[m][e];
+                    if (EPI == EPI_BIAS_RELU) v[e] = fmaxf(v[e], 0.0f);
+                }
+                if (EPI == EPI_MASK && !STAGED) {
+                    const uint2 mk = *reinterpret_cast<const uint2*>(A.mask + (size_t)c * COUT + co0);
+                    const uint16_t mm[4] = { (uint16_t)(mk.x & 0xffff), (uint16_t)(mk.x >> 16),
+                                             (uint16_t)(mk.y & 0xffff), (uint16_t)(mk.y >> 16) };
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (!(bf2f(mm[e]) > 0.0f)) v[e] = 0.0f;
+                }
+                if (EPI == EPI_BIAS_F32 || EPI == EPI_F32) {
+                    *reinterpret_cast<float4*>(A.yf + (size_t)c * COUT + co0) = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+                    const uint2 w = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+                    if constexpr (STAGED) {
+                        const int cl = (wz * CT_Y + nb) * CT_X + r, q = co0 >> 3;
+                        *reinterpret_cast<uint2*>(stage + buf * OUT + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)) + (co0 & 4)) = w;
+                    } else {
+                        *reinterpret_cast<uint2*>(A.yb + (size_t)c * COUT + co0) = w;
+                    }
+                }
+            }
+        }
+        if constexpr (decltype(fetched)::value) fill(tiles + (buf ^ 1) * S::LDS);
+        if constexpr (STAGED || decltype(fetched)::value) __syncthreads();
+        if constexpr (STAGED) {
+            // consecutive threads store consecutive chunks: 1 KiB per wave and row
+            constexpr int CHUNKS = OUT / 8 / CONV_THREADS;
+#pragma unroll
+            for (int i = 0; i < CHUNKS; ++i) {
+                const int p = threadIdx.x + CONV_THREADS * i;
+                const int cl = p >> 2, q = p & 3;
+                uint4 v = *reinterpret_cast<const uint4*>(stage + buf * OUT + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)));
+                const long c = c0 + cl % CT_X + (long)nx * ((cl / CT_X) % CT_Y + (long)ny * (cl / (CT_X * CT_Y)));
+                if constexpr (EPI == EPI_MASK) {
+                    const uint4 mk = ld16(A.mask + (size_t)c * COUT + 8 * q);
+                    v.x = masked2(v.x, mk.x); v.y = masked2(v.y, mk.y);
+                    v.z = masked2(v.z, mk.z); v.w = masked2(v.w, mk.w);
+                }
+                *reinterpret_cast<uint4*>(A.yb + (size_t)c * COUT + 8 * q) = v;
+            }
+        }
+    };
+    fetch(o);
+    fill(tiles);
     __syncthreads();
-
-    f4 acc[MB][NB];
-#pragma unroll
-    for (int m = 0; m < MB; ++m)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[m][nb] = f4{ 0.f, 0.f, 0.f, 0.f };
-
-    // K step s: weight fragments from global memory (L2), activation
-    // fragments from the LDS halo; the loop is unrolled and the fragments of
-    // step s + 1 are loaded while the MFMAs of step s run
-    const int hbase = (wave + 1) * (CH_X * CH_Y) + CH_X + (r + 1);
-    auto load_a = [&](int s, bf16x8* a) {
-#pragma unroll
-        for (int m = 0; m < MB; ++m) a[m] = as_bf8(wp[((size_t)s * MB + m) * 64 + lane]);
-    };
-    auto load_b = [&](int s, bf16x8* bv) {
-        const int K = 32 * s + 8 * g;
-        const int o = K / CIN, c0 = K % CIN;
-        const int dx = o % 3 - 1, dy = (o / 3) % 3 - 1, dz = o / 9 - 1;
-        const int h0 = hbase + dz * (CH_X * CH_Y) + dy * CH_X + dx;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            uint4 v = make_uint4(0, 0, 0, 0);
-            const int h = h0 + nb * CH_X;
-            if (o < 27) v = *reinterpret_cast<const uint4*>(tile + h * CS + 8 * conv_chunk<CIN>(h, c0 / 8));
-            bv[nb] = as_bf8(v);
-        }
-    };
-    bf16x8 a_cur[MB], b_cur[NB];
-    load_a(0, a_cur);
-    load_b(0, b_cur);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        bf16x8 a_nxt[MB], b_nxt[NB];
-        if (s + 1 < KS) {
-            load_a(s + 1, a_nxt);
-            load_b(s + 1, b_nxt);
-        }
-#pragma unroll
-        for (int m = 0; m < MB; ++m)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_cur[m], b_cur[nb], acc[m][nb], 0, 0, 0);
-        if (s + 1 < KS) {
-#pragma unroll
-            for (int m = 0; m < MB; ++m) a_cur[m] = a_nxt[m];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) b_cur[nb] = b_nxt[nb];
-        }
+    int buf = 0;
+    for (; o + stride < end; o += stride, buf ^= 1) {
+        fetch(o + stride);
+        work(o, buf, std::true_type());
     }
-
-    // epilogue: lane holds channels co = 16 m + 4 g + e of cell (x0 + r, y0 + nb, z0 + wave)
-#pragma unroll
-    for (int m = 0; m < MB; ++m) {
-        const int co0 = 16 * m + 4 * g;
-        if (co0 >= COUT) continue;
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            const long c = (long)(x0 + r) + (long)nx * ((long)(y0 + nb) + (long)ny * (z0 + wave));
-            float v[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[e] = acc[m][nb][e];
-                if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32) v[e] += A.bias[co0 + e];
-                if (EPI == EPI_BIAS_RELU) v[e] = fmaxf(v[e], 0.0f);
-            }
-            if (EPI == EPI_MASK) {
-                const uint2 mk = *reinterpret_cast<const uint2*>(A.mask + (size_t)c * COUT + co0);
-                const uint16_t mm[4] = { (uint16_t)(mk.x & 0xffff), (uint16_t)(mk.x >> 16),
-                                         (uint16_t)(mk.y & 0xffff), (uint16_t)(mk.y >> 16) };
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (!(bf2f(mm[e]) > 0.0f)) v[e] = 0.0f;
-            }
-            if (EPI == EPI_BIAS_F32 || EPI == EPI_F32) {
-                *reinterpret_cast<float4*>(A.yf + (size_t)c * COUT + co0) = make_float4(v[0], v[1], v[2], v[3]);
-            } else {
-                uint16_t bb[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) bb[e] = f2bf(v[e]);
-                *reinterpret_cast<uint2*>(A.yb + (size_t)c * COUT + co0) =
-                    make_uint2((uint32_t)bb[0] | ((uint32_t)bb[1] << 16), (uint32_t)bb[2] | ((uint32_t)bb[3] << 16));
-                if (A.ybT)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) A.ybT[(size_t)(co0 + e) * N + c] = bb[e];
-            }
-        }
-    }
+    work(o, buf, std::false_type());
 }
 
 template <int CIN, int COUT>
 static hipError_t conv_dispatch_epi(const ConvArgs& A, int epi, hipStream_t s)
 {
-    const unsigned grid = (unsigned)((A.n[0] / CT_X) * (A.n[1] / CT_Y) * (A.n[2] / CT_Z));
+    const int ntiles = (A.n[0] / CT_X) * (A.n[1] / CT_Y) * (A.n[2] / ConvShape<CIN, COUT>::TZ);
+    constexpr int resident = 256;
+    const unsigned grid = (unsigned)(ntiles < resident ? ntiles : resident);      // multiples of 8
     switch (epi) {
-    case EPI_BIAS_RELU: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_RELU>), dim3(grid), dim3(256), 0, s, A); break;
-    case EPI_BIAS_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_F32>), dim3(grid), dim3(256), 0, s, A); break;
-    case EPI_MASK: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_MASK>), dim3(grid), dim3(256), 0, s, A); break;
-    case EPI_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_F32>), dim3(grid), dim3(256), 0, s, A); break;
+    case EPI_BIAS_RELU: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_RELU>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
+    case EPI_BIAS_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_F32>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
+    case EPI_MASK: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_MASK>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
+    case EPI_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_F32>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -276,317 +463,270 @@ hipError_t launch_conv3d(const ConvArgs& A, int cin, int cout, int epi, hipStrea
 // wgrad
 // ---------------------------------------------------------------------------
 
-// 8 consecutive bf16 starting one element after (dx = +1) or before
-// (dx = -1) the aligned group c, from the aligned groups around it
-__device__ __forceinline__ uint4 shift_right1(uint4 c, uint4 n)    // elements c[1..7], n[0]
-{
-    return make_uint4((c.x >> 16) | (c.y << 16), (c.y >> 16) | (c.z << 16), (c.z >> 16) | (c.w << 16),
-                      (c.w >> 16) | (n.x << 16));
-}
-__device__ __forceinline__ uint4 shift_left1(uint4 p, uint4 c)     // elements p[7], c[0..6]
-{
-    return make_uint4((p.w >> 16) | (c.x << 16), (c.x >> 16) | (c.y << 16), (c.y >> 16) | (c.z << 16),
-                      (c.z >> 16) | (c.w << 16));
-}
-
-// Tile of wgrad: 32 (x) x 4 (y) x 2 (z) cells = 8 K steps of 32 cells (one
-// row segment each).
+// dW[o][ci][co] = sum_c x[c + d(o)][ci] dy[c][co] as MFMA products with M =
+// co, N = ci, K = cells.  Both operands are staged as they lie in memory,
+// channel-last; the fragments, whose lanes want 8 consecutive cells of one
+// channel, come from ds_read_b64_tr_b16: in each group of 16 lanes, lane i
+// gives the address of 4 channels (4 (i % 4) ..) of cell i / 4 and receives
+// channel i of the 4 cells.  An offset d(o) is then only another address, with
+// no shifting and no channel-major copy of any activation (the form before
+// read such copies, which the producing kernels wrote 2 bytes at a time).
+//
+// Tile: 32 (x) x 4 (y) x 2 (z) cells, x with a one-cell halo.  Six waves: wave
+// w has the offsets with dz = w / 2 - 1 and half of the blocks (32 -> 32: 16
+// of the ci; 8 -> 32: 16 of the co; 32 -> 8: 16 of the ci).  A row of x is
+// read once per dx and multiplies the rows y - dy of dy of all three dy, kept
+// in registers: 52 reads of 512 bytes feed 72 products per plane.  Two
+// workgroups fit on a CU, so that one's products cover the other's staging.
+// Where one side has 8 channels the 16 rows (columns) of a block hold two
+// offsets: for 8 input channels columns 8 .. 15 read the next cell (dx + 1),
+// for 8 output channels rows 8 .. 15 read the cell before of dy, which turns
+// dx into dx + 1.  Two blocks then make the three dx.
+//
+// Persistent over tiles (XCD k takes the k-th eighth, so that halos shared by
+// neighbouring tiles meet in its L2); each workgroup writes its partial sums
+// of dW and, in FP64, of the bias gradient, wgrad_reduce_kernel adds them in a
+// fixed order.
 constexpr int WT_X = 32, WT_Y = 4, WT_Z = 2;
-constexpr int WL_Y = WT_Y + 2, WL_Z = WT_Z + 2;          // x rows with their y / z halo
-
-// wgrad: dW[o][ci][co] = sum_c x[c + d(o)][ci] dy[c][co]
-//                     = sum_c dy[c - dx][co] x[c + (0, dy, dz)][ci]
-// (the x offset moved onto dy), with M = co (A = dy shifted along x), N = ci
-// (B = x rows, aligned: no shifting), K = cells.  Three waves per
-// workgroup; wave w owns the offsets with dz = w - 1 and all nine (dx, dy),
-// so an A fragment feeds 3 x NBI and a B fragment 3 x MB products.  LDS:
-// x without an x halo, [ci][hz][hy][32], and dy with one, [co][ks][48],
-// channel strides padded by 16 bf16 (75 KB for 32 -> 32 channels).  The
-// elements one before and after a lane's 8 dy values come from the lanes
-// 16 below and above (ds_bpermute) or, at the segment's ends, from the
-// halo.  With 8 channels on one side a 16-row (16-column) block carries two
-// offsets.  Persistent over tiles; each workgroup writes its partial sums,
-// wgrad_reduce adds them in a fixed order.  (A first form shifted x and ran
-// nine waves of three offsets each: it read x with halo in all three axes
-// and the dword reads of each shifted fragment's edge elements conflicted
-// in the LDS banks; 315, 271 and 130 us against 236, 110 and 100 us for
-// 32 -> 32, 32 -> 8 and 8 -> 32 channels at 128^3.)
-constexpr int WG_WAVES = 3;
+constexpr int WL_X = WT_X + 2, WL_Y = WT_Y + 2, WL_Z = WT_Z + 2;
 
 template <int CI, int CO>
-__global__ void __launch_bounds__(64 * WG_WAVES, (CI * CO > 256 ? 1 : 2)) conv3d_wgrad_kernel(WgradArgs A)
+struct WgradShape {
+    static constexpr bool FM = CO == 8 && CI == 32;        // rows hold two offsets
+    static constexpr bool FN = CI == 8;                    // columns do
+    static constexpr int WAVES = CI == 8 && CO == 8 ? 3 : 6;
+    static constexpr int HALVES = WAVES / 3;
+    static constexpr int ND = FM || FN ? 2 : 3;            // x blocks (dx) per row of x and wave
+    static constexpr int MB = CI == 32 && CO == 32 ? 2 : 1;     // dy blocks per row of dy and wave
+    static constexpr int DX = FM ? WT_X + 1 : WT_X;        // dy cells per row (FM: one before)
+    static constexpr int XS = WL_Z * WL_Y * WL_X * CI, DS = WT_Z * WT_Y * DX * CO;
+};
+
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short s4;
+
+// 8 cells of a channel: two transposing reads, the second 4 cells on
+__device__ __forceinline__ bf16x8 read_cells(const uint16_t* p, int step4)
 {
-    constexpr int MB = (CO + 15) / 16, NBI = (CI + 15) / 16;
-    constexpr int KSTEPS = WT_Y * WT_Z;
-    constexpr int XROWS = WL_Z * WL_Y;                       // 4 x 6 rows of x per tile
-    constexpr int XCS = XROWS * WT_X + 16;                   // channel strides, padded as above
-    constexpr int DX = WT_X + 16;                            // dy row with 8 halo cells each side
-    constexpr int DYS = KSTEPS * DX + 16;
-    constexpr int NT = 64 * WG_WAVES;
-    __shared__ __align__(16) uint16_t xs[CI * XCS];
-    __shared__ __align__(16) uint16_t dys[CO * DYS];
+    typedef __attribute__((address_space(3))) s4* lds4;
+    const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)p);
+    const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds4)(p + step4));
+    typedef __attribute__((__vector_size__(8 * sizeof(short)))) short s8;
+    return __builtin_bit_cast(bf16x8, s8{ a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3] });
+}
+
+template <int CI, int CO>
+__global__ void __launch_bounds__((64 * WgradShape<CI, CO>::WAVES), 3) conv3d_wgrad_kernel(WgradArgs A)
+{
+    using S = WgradShape<CI, CO>;
+    constexpr int NT = 64 * S::WAVES, ND = S::ND, MB = S::MB;
+    // dy behind x: the last folded columns read one cell past x's last row
+    __shared__ __align__(16) uint16_t smem[S::XS + S::DS];
+    uint16_t* const xs = smem;
+    uint16_t* const ds = smem + S::XS;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane >> 4, r = lane & 15;
-    const int ddz = wave - 1;
+    const int g = lane >> 4, i = lane & 15;
+    const int dz = wave / S::HALVES, half = wave % S::HALVES;
     const int nx = A.n[0], ny = A.n[1], nz = A.n[2];
-    const size_t N = (size_t)nx * ny * nz;
-    const int tx = nx / WT_X, ty = ny / WT_Y, ntiles = tx * ty * (nz / WT_Z);
+    const int tx = nx / WT_X, ty = ny / WT_Y, per = (tx * ty * (nz / WT_Z)) >> 3;
 
-    // 8 channels of dy (x) fill only half of an MFMA block's rows (columns):
-    // there the rows (columns) carry (channel, dx) ((channel, dy)) pairs,
-    // 8 channels x 2 offsets per block, two blocks for the three offsets
-    constexpr bool FM = CO == 8 && CI > 8, FN = CI == 8 && CO > 8;
-    constexpr int AN = FM ? 2 : 3, BN = FN ? 2 : 3;
-    f4 acc[AN][BN][MB][NBI];                                // [dx + 1][dy + 1], or the folded blocks
-#pragma unroll
-    for (int a = 0; a < AN; ++a)
-#pragma unroll
-        for (int b = 0; b < BN; ++b)
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int q = 0; q < NBI; ++q) acc[a][b][m][q] = f4{ 0.f, 0.f, 0.f, 0.f };
+    // lane bases: cell 8 g + i / 4, channels 4 (i % 4) .. of the wave's block;
+    // folded: channels 4 (i % 2) .. of this cell or, for i % 4 >= 2, of the other
+    const int c0 = 8 * g + (i >> 2);
+    const uint16_t* const xb = xs + dz * (WL_Y * WL_X * CI) +
+                               (S::FN ? (c0 + ((i >> 1) & 1)) * CI + 4 * (i & 1) : c0 * CI + 16 * half + 4 * (i & 3));
+    const uint16_t* const db = ds + (S::FM    ? (c0 + 1 - ((i >> 1) & 1)) * CO + 4 * (i & 1)
+                                     : CO == 8 ? c0 * CO + 4 * (i & 1)
+                                               : c0 * CO + (S::FN ? 16 * half : 0) + 4 * (i & 3));
 
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    f4 acc[3][ND][MB];                                      // [dy][block of dx][m]
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int m = 0; m < MB; ++m) acc[a][d][m] = f4{ 0.f, 0.f, 0.f, 0.f };
+    // bias: thread t < BT sums 8 channels of the cells t / (CO / 8) + BT / (CO / 8) j
+    constexpr int BT = NT < 256 ? 128 : 256, BQ = CO / 8, BSTEP = BT / BQ;
+    double bias[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
+
+    for (int t = (blockIdx.x & 7) * per + (blockIdx.x >> 3); t < ((blockIdx.x & 7) + 1) * per; t += gridDim.x >> 3) {
         const int x0 = (t % tx) * WT_X, y0 = ((t / tx) % ty) * WT_Y, z0 = (t / (tx * ty)) * WT_Z;
-        // fill: x rows (ci, hz, hy) of 32 cells = 4 loads of 16 bytes, dy rows
-        // (co, ks) of 48 cells (x0 - 8 .. x0 + 40, periodic) = 6 loads
-        constexpr int XI = CI * XROWS * (WT_X / 8), DI = CO * KSTEPS * (DX / 8), ITEMS = XI + DI;
-        // as many of a thread's loads in flight at once as the registers
-        // allow (the fill waits for one round trip per batch): 24 (all) with
-        // 32 -> 32 channels at one wave per SIMD, 12 at two
-        constexpr int FMAX = CI * CO > 256 ? 24 : 12;
-        constexpr int FILL = (ITEMS + NT - 1) / NT, FB = FILL < FMAX ? FILL : FMAX;
-        __syncthreads();                                   // previous tile's reads are done
+        // two batches of loads for 32 -> 32 channels: 12 in flight would spill
+        // at 3 waves per SIMD
+        constexpr int XI = S::XS / 8, ITEMS = (S::XS + S::DS) / 8, FILL = (ITEMS + NT - 1) / NT;
+        constexpr int FB = FILL > 8 ? (FILL + 1) / 2 : FILL;
+        int tid = threadIdx.x;
+        // opaque with 32 -> 32 channels, where the places of all pieces, kept
+        // in registers over the loop, would spill
+        if constexpr (CI * CO > 256) asm volatile("" : "+v"(tid));
+        auto item = [&](int f) { return min(tid + NT * f, ITEMS - 1); };     // past the end: the last piece again
 #pragma unroll
         for (int f0 = 0; f0 < FILL; f0 += FB) {
             uint4 fv[FB];
 #pragma unroll
             for (int f = 0; f < FB; ++f) {
-                const int it = threadIdx.x + NT * (f0 + f);
-                fv[f] = make_uint4(0, 0, 0, 0);
-                if (f0 + f < FILL && it < XI) {
-                    const int gx = it % (WT_X / 8), row = (it / (WT_X / 8)) % XROWS, ci = it / (WT_X / 8 * XROWS);
-                    const int hy = row % WL_Y, hz = row / WL_Y;
-                    const size_t src = (size_t)ci * N + (size_t)(x0 + 8 * gx) +
-                                       (size_t)nx * ((size_t)wrap1(y0 - 1 + hy, ny) + (size_t)ny * wrap1(z0 - 1 + hz, nz));
-                    fv[f] = ld16(A.xT + src);
-                } else if (f0 + f < FILL && it < ITEMS) {
-                    const int d = it - XI, gx = d % (DX / 8), ks = (d / (DX / 8)) % KSTEPS;
-                    const int co = d / (DX / 8 * KSTEPS);
-                    const int sx = x0 - 8 + 8 * gx, gxs = sx < 0 ? sx + nx : (sx >= nx ? sx - nx : sx);
-                    const size_t src = (size_t)co * N + (size_t)gxs +
-                                       (size_t)nx * ((size_t)(y0 + ks % WT_Y) + (size_t)ny * (z0 + ks / WT_Y));
-                    fv[f] = ld16(A.dyT + src);
-                }
+                const int it = item(f0 + f);
+                const bool isx = it < XI;
+                const int d = isx ? it : it - XI;
+                const int q = isx ? d % (CI / 8) : d % (CO / 8), c = isx ? d / (CI / 8) : d / (CO / 8);
+                const int cx = isx ? c % WL_X - 1 : c % S::DX - (S::FM ? 1 : 0), row = isx ? c / WL_X : c / S::DX;
+                const int cy = isx ? row % WL_Y - 1 : row % WT_Y, cz = isx ? row / WL_Y - 1 : row / WT_Y;
+                const unsigned src = (unsigned)wrap1(x0 + cx, nx) +
+                                     (unsigned)nx * ((unsigned)wrap1(y0 + cy, ny) + (unsigned)ny * (unsigned)wrap1(z0 + cz, nz));
+                fv[f] = ld16(isx ? A.x + (size_t)src * CI + 8 * q : A.dy + (size_t)src * CO + 8 * q);
+            }
+            if (f0 == 0) __syncthreads();                  // the previous tile's reads are done
+#pragma unroll
+            for (int f = 0; f < FB; ++f) *reinterpret_cast<uint4*>(smem + 8 * item(f0 + f)) = fv[f];
+        }
+        __syncthreads();
+        if (threadIdx.x < BT) {
+            float part[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
+#pragma unroll
+            for (int j = 0; j < 256 / BSTEP; ++j) {
+                const int c = threadIdx.x / BQ + BSTEP * j;
+                const uint4 v = *reinterpret_cast<const uint4*>(ds + (c + (S::FM ? c / WT_X + 1 : 0)) * CO + 8 * (threadIdx.x % BQ));
+                const uint32_t w[4] = { v.x, v.y, v.z, v.w };
+#pragma unroll
+                for (int e = 0; e < 8; ++e) part[e] += bf2f((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
             }
 #pragma unroll
-            for (int f = 0; f < FB; ++f) {
-                const int it = threadIdx.x + NT * (f0 + f);
-                if (f0 + f < FILL && it < XI) {
-                    const int gx = it % (WT_X / 8), row = (it / (WT_X / 8)) % XROWS, ci = it / (WT_X / 8 * XROWS);
-                    *reinterpret_cast<uint4*>(xs + ci * XCS + row * WT_X + 8 * gx) = fv[f];
-                } else if (f0 + f < FILL && it < ITEMS) {
-                    const int d = it - XI, gx = d % (DX / 8), ks = (d / (DX / 8)) % KSTEPS;
-                    const int co = d / (DX / 8 * KSTEPS);
-                    *reinterpret_cast<uint4*>(dys + co * DYS + ks * DX + 8 * gx) = fv[f];
+            for (int e = 0; e < 8; ++e) bias[e] += (double)part[e];
+        }
+#pragma unroll 1
+        for (int kz = 0; kz < WT_Z; ++kz) {
+            bf16x8 a[WT_Y][MB];
+#pragma unroll
+            for (int ky = 0; ky < WT_Y; ++ky)
+#pragma unroll
+                for (int m = 0; m < MB; ++m) a[ky][m] = read_cells(db + (kz * WT_Y + ky) * (S::DX * CO) + 16 * m, 4 * CO);
+#pragma unroll
+            for (int row = 0; row < WL_Y; ++row) {
+                bf16x8 b[ND];
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+                    b[d] = read_cells(xb + ((kz * WL_Y + row) * WL_X + (ND == 2 ? 2 * d : d)) * CI, 4 * CI);
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int ky = row - dy;
+                    if (ky < 0 || ky >= WT_Y) continue;
+#pragma unroll
+                    for (int d = 0; d < ND; ++d)
+#pragma unroll
+                        for (int m = 0; m < MB; ++m)
+                            acc[dy][d][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ky][m], b[d], acc[dy][d][m], 0, 0, 0);
                 }
             }
         }
-        __syncthreads();
-#pragma unroll 1
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            const int ky = ks % WT_Y, kz = ks / WT_Y;
-            // A: dy of channel co = 16 m + r (FM: r mod 8), cells 8 g .. 8 g + 7
-            // of the row, shifted by -dx
-            bf16x8 af[AN][MB];
+    }
+    // D of a block: lane holds rows 4 g + e (e = 0..3), column i
+    float* const out = A.partial + (size_t)blockIdx.x * 27 * CI * CO;
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
 #pragma unroll
             for (int m = 0; m < MB; ++m) {
-                const int co = FM ? (r & 7) : 16 * m + r;
-                const uint16_t* row = dys + (co < CO ? co : 0) * DYS + ks * DX;
-                uint4 mid = *reinterpret_cast<const uint4*>(row + 8 + 8 * g);
-                // the row's halo element before (g = 0: cell -1) or after
-                // (g = 3: cell 32) the lane's segment
-                const uint32_t halo = *reinterpret_cast<const uint32_t*>(row + (g == 3 ? 40 : 6));
-                const uint32_t pw = (uint32_t)__shfl((int)mid.w, lane - 16, 64);
-                const uint32_t nw = (uint32_t)__shfl((int)mid.x, lane + 16, 64);
-                const uint32_t prev = g == 0 ? halo : pw;       // its high half: cell 8 g - 1
-                const uint32_t next = g == 3 ? halo : nw;       // its low half: cell 8 g + 8
-                if (co >= CO) mid = make_uint4(0, 0, 0, 0);
-                const uint32_t prevv = co < CO ? prev : 0u, nextv = co < CO ? next : 0u;
-                const uint4 sm1 = shift_right1(mid, make_uint4(nextv, 0, 0, 0));   // dx = -1: dy at c + 1
-                const uint4 sp1 = shift_left1(make_uint4(0, 0, 0, prevv), mid);    // dx = +1: dy at c - 1
-                if constexpr (FM) {
-                    // rows r < 8: dx = -1 | +1, rows r >= 8: dx = 0 | none
-                    af[0][m] = as_bf8(r < 8 ? sm1 : mid);
-                    af[1][m] = as_bf8(r < 8 ? sp1 : make_uint4(0, 0, 0, 0));
-                } else {
-                    af[0][m] = as_bf8(sm1);
-                    af[1][m] = as_bf8(mid);
-                    af[2][m] = as_bf8(sp1);
-                }
+                const int row = 4 * g;
+                const int co = S::FM || CO == 8 ? row & 7 : (S::FN ? 16 * half : 16 * m) + row;
+                const int ci = S::FN ? i & 7 : 16 * half + i;
+                const int dx = ND == 2 ? 2 * d + (S::FN ? i >> 3 : row >> 3) : d;
+                if (dx > 2 || (CO == 8 && !S::FM && row >= 8)) continue;
+                const int o = dz * 9 + dy * 3 + dx;
+                *reinterpret_cast<f4*>(out + ((size_t)o * CI + ci) * CO + co) = acc[dy][d][m];
             }
-            if constexpr (FN) {
-                // columns r < 8: dy = -1 | +1, columns r >= 8: dy = 0 | none
-                bf16x8 bf[2];
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int b = 2 * j + (r >> 3), ci = r & 7;
-                    bf[j] = as_bf8(b < 3 ? *reinterpret_cast<const uint4*>(
-                                               xs + ci * XCS + ((kz + 1 + ddz) * WL_Y + ky + b) * WT_X + 8 * g)
-                                         : make_uint4(0, 0, 0, 0));
-                }
-#pragma unroll
-                for (int a = 0; a < AN; ++a)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int m = 0; m < MB; ++m)
-                            acc[a][j][m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a][m], bf[j], acc[a][j][m][0],
-                                                                                      0, 0, 0);
-            } else {
-#pragma unroll
-                for (int b = 0; b < 3; ++b) {              // dy = b - 1
-                    bf16x8 bf[NBI];
-#pragma unroll
-                    for (int q = 0; q < NBI; ++q) {
-                        const int ci = 16 * q + r;
-                        bf[q] = as_bf8(ci < CI ? *reinterpret_cast<const uint4*>(
-                                                     xs + ci * XCS + ((kz + 1 + ddz) * WL_Y + ky + b) * WT_X + 8 * g)
-                                               : make_uint4(0, 0, 0, 0));
-                    }
-#pragma unroll
-                    for (int a = 0; a < AN; ++a)
-#pragma unroll
-                        for (int m = 0; m < MB; ++m)
-#pragma unroll
-                            for (int q = 0; q < NBI; ++q)
-                                acc[a][b][m][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a][m], bf[q],
-                                                                                          acc[a][b][m][q], 0, 0, 0);
-                }
-            }
-        }
-    }
-    // D of an MFMA block: lane holds rows 4 g + e (e = 0..3), column r;
-    // unfolded, row = co - 16 m and column = ci - 16 q
-    float* out = A.partial + (size_t)blockIdx.x * 27 * CI * CO;
-#pragma unroll
-    for (int a = 0; a < AN; ++a)
-#pragma unroll
-        for (int b = 0; b < BN; ++b)
-#pragma unroll
-            for (int m = 0; m < MB; ++m)
-#pragma unroll
-                for (int q = 0; q < NBI; ++q)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int row = 4 * g + e;
-                        const int co = FM ? (row & 7) : 16 * m + row;
-                        const int dxi = FM ? 2 * a + (row >> 3) : a;            // dx + 1
-                        const int ci = FN ? (r & 7) : 16 * q + r;
-                        const int dyi = FN ? 2 * b + (r >> 3) : b;              // dy + 1
-                        if (co >= CO || ci >= CI || dxi > 2 || dyi > 2) continue;
-                        const int o = (ddz + 1) * 9 + dyi * 3 + dxi;
-                        out[((size_t)o * CI + ci) * CO + co] = acc[a][b][m][q][e];
-                    }
-}
-
-// dw[i] = sum over workgroups of partial[wg][i] in workgroup order: pass 1
-// sums WR_GROUPS contiguous ranges of workgroups, pass 2 the ranges
-constexpr int WR_GROUPS = 16;
-__global__ void wgrad_reduce1_kernel(const float* __restrict__ partial, int nwg, int count, float* __restrict__ mid)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int grp = blockIdx.y;
-    if (i >= count) return;
-    const int per = (nwg + WR_GROUPS - 1) / WR_GROUPS;
-    const int w0 = grp * per, w1 = min(nwg, w0 + per);
-    float acc = 0.0f;
-    for (int w = w0; w < w1; ++w) acc += partial[(size_t)w * count + i];
-    mid[(size_t)grp * count + i] = acc;
-}
-
-__global__ void wgrad_reduce2_kernel(const float* __restrict__ mid, int count, float* __restrict__ dw)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    float acc = 0.0f;
-    for (int k = 0; k < WR_GROUPS; ++k) acc += mid[(size_t)k * count + i];
-    dw[i] = acc;
-}
-
-// dbias[co] = sum_cell dyT[co][cell]: BG_BLOCKS workgroups per channel
-// (blockIdx.y = channel) write FP64 partials, a final pass adds them in
-// block order (deterministic)
-__global__ void __launch_bounds__(256) bias_grad_partial_kernel(const uint16_t* __restrict__ dyT, size_t N,
-                                                                double* __restrict__ partial)
-{
-    const int co = blockIdx.y;
-    const uint16_t* row = dyT + (size_t)co * N;
-    double acc = 0.0;
-    // 8 values per thread per iteration (one 16-byte load; N is a multiple of 8)
-    for (size_t c = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8; c < N; c += (size_t)gridDim.x * 256 * 8) {
-        const uint4 v = ld16(row + c);
-        const uint32_t w[4] = { v.x, v.y, v.z, v.w };
-        float part = 0.0f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) part += bf2f((uint16_t)(w[q] & 0xffff)) + bf2f((uint16_t)(w[q] >> 16));
-        acc += (double)part;
-    }
-    __shared__ double sh[256];
-    sh[threadIdx.x] = acc;
+    // bias: threads of a chunk of channels added in order
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-        __syncthreads();
+    double* const sh = reinterpret_cast<double*>(smem);
+    if (threadIdx.x < BT)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sh[e * BT + threadIdx.x] = bias[e];
+    __syncthreads();
+    if (threadIdx.x < CO) {
+        double v = 0.0;
+        for (int j = threadIdx.x >> 3; j < BT; j += BQ) v += sh[(threadIdx.x & 7) * BT + j];
+        A.bias_partial[(size_t)blockIdx.x * CO + threadIdx.x] = v;
     }
-    if (threadIdx.x == 0) partial[(size_t)co * gridDim.x + blockIdx.x] = sh[0];
 }
 
-__global__ void bias_grad_final_kernel(const double* __restrict__ partial, int nblk, int cout, float* dbias)
+// grads of up to 3 layers from their workgroups' partial sums, in workgroup
+// order: a block of 256 threads takes 64 consecutive weights, thread group j
+// the j-th quarter of the workgroups (8 running sums each), then the quarters
+// in order; the blocks past the weights take the biases
+struct WgradReduce {
+    WgradLayer layer[3];
+    int nlayer, nwg;
+};
+constexpr int WR_GROUPS = 4, WR_SUMS = 8;
+__global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduce R)
 {
-    const int co = threadIdx.x;
-    if (co >= cout) return;
-    double acc = 0.0;
-    for (int b = 0; b < nblk; ++b) acc += partial[(size_t)co * nblk + b];
-    dbias[co] = (float)acc;
+    int b = blockIdx.x, l = 0;
+    while (l < R.nlayer && b >= (R.layer[l].count + 63) / 64) b -= (R.layer[l++].count + 63) / 64;
+    if (l == R.nlayer) {                                   // biases: a wave per channel
+        int c = 4 * b + (threadIdx.x >> 6);
+        for (l = 0; l < R.nlayer && c >= R.layer[l].cout; ++l) c -= R.layer[l].cout;
+        if (l == R.nlayer) return;
+        double v = 0.0;
+        for (int w = threadIdx.x & 63; w < R.nwg; w += 64) v += R.layer[l].bias_partial[(size_t)w * R.layer[l].cout + c];
+#pragma unroll
+        for (int st = 32; st > 0; st >>= 1) v += __shfl_xor(v, st, 64);
+        if ((threadIdx.x & 63) == 0) R.layer[l].dbias[c] = (float)v;
+        return;
+    }
+    const WgradLayer& L = R.layer[l];
+    const int e = threadIdx.x & 63, j = threadIdx.x >> 6;
+    const int k = b * 64 + e;                              // counts are multiples of 64
+    const int per = (R.nwg + WR_GROUPS - 1) / WR_GROUPS;
+    const int w0 = j * per, w1 = min(R.nwg, w0 + per);
+    float acc[WR_SUMS] = {};
+    int w = w0;
+    for (; w + WR_SUMS <= w1; w += WR_SUMS)
+#pragma unroll
+        for (int q = 0; q < WR_SUMS; ++q) acc[q] += L.partial[(size_t)(w + q) * L.count + k];
+    for (int q = 0; w < w1; ++w, ++q) acc[q] += L.partial[(size_t)w * L.count + k];
+    __shared__ float sh[WR_GROUPS][64];
+    sh[j][e] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+    __syncthreads();
+    if (j == 0) L.dw[k] = (sh[0][e] + sh[1][e]) + (sh[2][e] + sh[3][e]);
 }
 
-int wgrad_blocks(const int n[3], int& tiles_per_wg)
+// Workgroups of a wgrad launch, a multiple of 8: two per CU; one where that
+// leaves them fewer than 8 tiles each, as every workgroup's 110 KiB of partial
+// sums are written and read again.
+int wgrad_blocks(const int n[3])
 {
     const int ntiles = (n[0] / WT_X) * (n[1] / WT_Y) * (n[2] / WT_Z);
-    const int nwg = ntiles < WGRAD_MAX_WG ? ntiles : WGRAD_MAX_WG;
-    tiles_per_wg = (ntiles + nwg - 1) / nwg;
-    return nwg;
+    const int most = ntiles >= 8 * WGRAD_MAX_WG ? WGRAD_MAX_WG : WGRAD_MAX_WG / 2;
+    return ntiles < most ? ntiles : most;
 }
 
-hipError_t launch_conv3d_wgrad(const WgradArgs& A, int cin, int cout, float* dw, hipStream_t s)
+hipError_t launch_conv3d_wgrad(const WgradArgs& A, int cin, int cout, hipStream_t s)
 {
-    int tpw = 0;
-    const int nwg = wgrad_blocks(A.n, tpw);
-    constexpr int T2 = 64 * WG_WAVES;
+    const int nwg = wgrad_blocks(A.n);
     if (cin == 8 && cout == 32)
-        hipLaunchKernelGGL((conv3d_wgrad_kernel<8, 32>), dim3(nwg), dim3(T2), 0, s, A);
+        hipLaunchKernelGGL((conv3d_wgrad_kernel<8, 32>), dim3(nwg), dim3(64 * WgradShape<8, 32>::WAVES), 0, s, A);
     else if (cin == 32 && cout == 32)
-        hipLaunchKernelGGL((conv3d_wgrad_kernel<32, 32>), dim3(nwg), dim3(T2), 0, s, A);
+        hipLaunchKernelGGL((conv3d_wgrad_kernel<32, 32>), dim3(nwg), dim3(64 * WgradShape<32, 32>::WAVES), 0, s, A);
     else if (cin == 32 && cout == 8)
-        hipLaunchKernelGGL((conv3d_wgrad_kernel<32, 8>), dim3(nwg), dim3(T2), 0, s, A);
+        hipLaunchKernelGGL((conv3d_wgrad_kernel<32, 8>), dim3(nwg), dim3(64 * WgradShape<32, 8>::WAVES), 0, s, A);
     else if (cin == 8 && cout == 8)
-        hipLaunchKernelGGL((conv3d_wgrad_kernel<8, 8>), dim3(nwg), dim3(T2), 0, s, A);
+        hipLaunchKernelGGL((conv3d_wgrad_kernel<8, 8>), dim3(nwg), dim3(64 * WgradShape<8, 8>::WAVES), 0, s, A);
     else
         return hipErrorInvalidValue;
-    const int count = 27 * cin * cout;
-    float* mid = A.partial + (size_t)nwg * count;
-    hipLaunchKernelGGL(wgrad_reduce1_kernel, dim3((count + 255) / 256, WR_GROUPS), dim3(256), 0, s, A.partial, nwg,
-                       count, mid);
-    hipLaunchKernelGGL(wgrad_reduce2_kernel, dim3((count + 255) / 256), dim3(256), 0, s, mid, count, dw);
     return hipGetLastError();
 }
 
-hipError_t launch_bias_grad(const uint16_t* dyT, size_t N, int cout, float* dbias, double* partial, hipStream_t s)
+hipError_t launch_wgrad_reduce(const WgradLayer* layers, int nlayer, int nwg, hipStream_t s)
 {
-    hipLaunchKernelGGL(bias_grad_partial_kernel, dim3(BG_BLOCKS, cout), dim3(256), 0, s, dyT, N, partial);
-    hipLaunchKernelGGL(bias_grad_final_kernel, dim3(1), dim3(64), 0, s, partial, BG_BLOCKS, cout, dbias);
+    WgradReduce R;
+    int blocks = 0;
+    R.nlayer = nlayer;
+    R.nwg = nwg;
+    for (int l = 0; l < nlayer; ++l) {
+        R.layer[l] = layers[l];
+        blocks += (layers[l].count + 63) / 64 + layers[l].cout / 4;     // 64 weights or 4 biases each
+    }
+    hipLaunchKernelGGL(wgrad_reduce_kernel, dim3(blocks), dim3(256), 0, s, R);
     return hipGetLastError();
 }
 
@@ -594,19 +734,23 @@ hipError_t launch_bias_grad(const uint16_t* dyT, size_t N, int cout, float* dbia
 // conversions
 // ---------------------------------------------------------------------------
 
-// float [cell][c] -> bf16 [cell][c] and (if dstT) bf16 [c][cell]
-__global__ void to_bf16_kernel(const float* __restrict__ src, size_t N, int c, uint16_t* dst, uint16_t* dstT)
+// bf16 [c][cell] -> [cell][c] (c = 8 or 32; the single-layer entry point takes
+// channel-major operands): a workgroup takes 64 cells, through LDS
+template <int C>
+__global__ void __launch_bounds__(256) channel_last_kernel(const uint16_t* __restrict__ src, size_t N, uint16_t* __restrict__ dst)
 {
-    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < N * c; t += (size_t)gridDim.x * blockDim.x) {
-        const uint16_t b = f2bf(src[t]);
-        if (dst) dst[t] = b;
-        if (dstT) dstT[(t % c) * N + t / c] = b;
-    }
+    __shared__ uint16_t sh[64][C + 2];
+    const size_t c0 = (size_t)blockIdx.x * 64;
+    for (int t = threadIdx.x; t < 64 * C; t += 256) sh[t & 63][t >> 6] = src[(size_t)(t >> 6) * N + c0 + (t & 63)];
+    __syncthreads();
+    for (int t = threadIdx.x; t < 64 * C; t += 256) dst[c0 * C + t] = sh[t / C][t % C];
 }
 
-hipError_t launch_to_bf16(const float* src, size_t N, int c, uint16_t* dst, uint16_t* dstT, hipStream_t s)
+hipError_t launch_channel_last(const uint16_t* src, size_t N, int c, uint16_t* dst, hipStream_t s)
 {
-    hipLaunchKernelGGL(to_bf16_kernel, dim3(2048), dim3(256), 0, s, src, N, c, dst, dstT);
+    if (c == 8) hipLaunchKernelGGL(channel_last_kernel<8>, dim3((unsigned)(N / 64)), dim3(256), 0, s, src, N, dst);
+    else if (c == 32) hipLaunchKernelGGL(channel_last_kernel<32>, dim3((unsigned)(N / 64)), dim3(256), 0, s, src, N, dst);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -614,30 +758,22 @@ hipError_t launch_to_bf16(const float* src, size_t N, int c, uint16_t* dst, uint
 // closure elementwise and reduction kernels
 // ---------------------------------------------------------------------------
 // States are FP32 field-major u[f][cell]; the network sees x[cell][8] =
-// (u - mean) / std in bf16 (and its channel-major copy for wgrad).
+// (u - mean) / std in bf16.
 
-__global__ void normalize_kernel(const float* __restrict__ u, size_t N, ClosureScales sc,
-                                 uint16_t* __restrict__ x, uint16_t* __restrict__ xT)
+__global__ void normalize_kernel(const float* __restrict__ u, size_t N, ClosureScales sc, uint16_t* __restrict__ x)
 {
     for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
-        uint16_t b[8];
+        float b[8];
 #pragma unroll
-        for (int f = 0; f < 8; ++f) {
-            b[f] = f2bf((u[(size_t)f * N + c] - sc.in_mean[f]) / sc.in_std[f]);
-            if (xT) xT[(size_t)f * N + c] = b[f];
-        }
-        uint4 v;
-        v.x = (uint32_t)b[0] | ((uint32_t)b[1] << 16);
-        v.y = (uint32_t)b[2] | ((uint32_t)b[3] << 16);
-        v.z = (uint32_t)b[4] | ((uint32_t)b[5] << 16);
-        v.w = (uint32_t)b[6] | ((uint32_t)b[7] << 16);
-        *reinterpret_cast<uint4*>(x + c * 8) = v;
+        for (int f = 0; f < 8; ++f) b[f] = (u[(size_t)f * N + c] - sc.in_mean[f]) / sc.in_std[f];
+        *reinterpret_cast<uint4*>(x + c * 8) =
+            make_uint4(f2bf2(b[0], b[1]), f2bf2(b[2], b[3]), f2bf2(b[4], b[5]), f2bf2(b[6], b[7]));
     }
 }
 
-hipError_t launch_normalize(const float* u, size_t N, const ClosureScales& sc, uint16_t* x, uint16_t* xT, hipStream_t s)
+hipError_t launch_normalize(const float* u, size_t N, const ClosureScales& sc, uint16_t* x, hipStream_t s)
 {
-    hipLaunchKernelGGL(normalize_kernel, dim3(2048), dim3(256), 0, s, u, N, sc, x, xT);
+    hipLaunchKernelGGL(normalize_kernel, dim3(2048), dim3(256), 0, s, u, N, sc, x);
     return hipGetLastError();
 }
 
@@ -716,31 +852,42 @@ hipError_t launch_project(const float* o, const double* mean, const int n[3], co
     return hipGetLastError();
 }
 
-// adjoint of the projection: g[f][c] -> go[c][8]
-__global__ void project_T_kernel(const float* __restrict__ g, const double* __restrict__ gmean, int nx, int ny,
-                                 int nz, ClosureScales sc, float* __restrict__ go)
+// adjoint of the projection, g[f][c] -> go[c][8], times the gate (gate may be
+// null) and rounded to bf16: the output gradient as dgrad and wgrad read it
+__global__ void project_T_kernel(const float* __restrict__ g, const double* __restrict__ gmean,
+                                 const float* __restrict__ gate, int nx, int ny, int nz, ClosureScales sc,
+                                 uint16_t* __restrict__ go)
 {
     const size_t N = (size_t)nx * ny * nz;
     for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
         int i, j, k;
         cell_ijk((unsigned)c, nx, ny, i, j, k);
-        for (int f = 0; f < 5; ++f) go[c * 8 + f] = sc.out_scale[f] * (float)((double)g[(size_t)f * N + c] - gmean[f]);
+        float v[8];
+#pragma unroll
+        for (int f = 0; f < 5; ++f) v[f] = sc.out_scale[f] * (float)((double)g[(size_t)f * N + c] - gmean[f]);
         const size_t cxm = (size_t)wrap1(i - 1, nx) + (size_t)nx * (j + (size_t)ny * k);
         const size_t cym = (size_t)i + (size_t)nx * (wrap1(j - 1, ny) + (size_t)ny * k);
         const size_t czm = (size_t)i + (size_t)nx * (j + (size_t)ny * wrap1(k - 1, nz));
         const float* gx = g + 5 * N;
         const float* gy = g + 6 * N;
         const float* gz = g + 7 * N;
-        go[c * 8 + 7] = sc.out_scale[7] * ((gx[cym] - gx[c]) - (gy[cxm] - gy[c]));
-        go[c * 8 + 6] = sc.out_scale[6] * ((gz[cxm] - gz[c]) - (gx[czm] - gx[c]));
-        go[c * 8 + 5] = sc.out_scale[5] * ((gy[czm] - gy[c]) - (gz[cym] - gz[c]));
+        v[7] = sc.out_scale[7] * ((gx[cym] - gx[c]) - (gy[cxm] - gy[c]));
+        v[6] = sc.out_scale[6] * ((gz[cxm] - gz[c]) - (gx[czm] - gx[c]));
+        v[5] = sc.out_scale[5] * ((gy[czm] - gy[c]) - (gz[cym] - gz[c]));
+        if (gate) {
+            const float s = gate[c];
+#pragma unroll
+            for (int f = 0; f < 8; ++f) v[f] *= s;
+        }
+        *reinterpret_cast<uint4*>(go + c * 8) =
+            make_uint4(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7]));
     }
 }
 
-hipError_t launch_project_T(const float* g, const double* gmean, const int n[3], const ClosureScales& sc, float* go,
-                            hipStream_t s)
+hipError_t launch_project_T(const float* g, const double* gmean, const float* gate, const int n[3],
+                            const ClosureScales& sc, uint16_t* go, hipStream_t s)
 {
-    hipLaunchKernelGGL(project_T_kernel, dim3(2048), dim3(256), 0, s, g, gmean, n[0], n[1], n[2], sc, go);
+    hipLaunchKernelGGL(project_T_kernel, dim3(2048), dim3(256), 0, s, g, gmean, gate, n[0], n[1], n[2], sc, go);
     return hipGetLastError();
 }
 

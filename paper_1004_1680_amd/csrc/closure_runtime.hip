@@ -44,15 +44,16 @@ struct mhd_closure {
     uint16_t* wp[3];       // packed forward weights
     uint16_t* wpT[3];      // packed dgrad weights (layers 2, 3)
     bool packed;
-    uint16_t *x0, *x0T, *a1, *a1T, *a2, *a2T, *gob, *gobT, *g2, *g2T, *g1, *g1T;
-    float *o, *delta, *g, *go;
-    float* wpart;          // wgrad partials
+    uint16_t *x0, *a1, *a2, *gob, *g2, *g1;
+    float *o, *delta, *g;
+    float* wpart;          // wgrad partials of the three layers
+    double* bpart;         // bias partials of the three layers
     double *chpart, *chout, *loss, *stpart, *stout;
     bool gate_on;           // roughness gate of the output (mhd_closure_set_gate)
     GateScales gs;
     float *gate0, *gate;
     int *bad, *fallbacks;
-    int tiles_per_wg, nwg;
+    int nwg;               // workgroups of a wgrad launch
 };
 
 static int check_cl(const mhd_closure* c)
@@ -67,8 +68,8 @@ extern "C" void mhd_closure_destroy(mhd_closure* c)
     if (!c) return;
     (void)hipStreamSynchronize(c->stream);
     void* ptrs[] = { c->params, c->grads, c->adam_m, c->adam_v, c->wp[0], c->wp[1], c->wp[2], c->wpT[0],
-                     c->wpT[1], c->wpT[2], c->x0, c->x0T, c->a1, c->a1T, c->a2, c->a2T, c->gob, c->gobT,
-                     c->g2, c->g2T, c->g1, c->g1T, c->o, c->delta, c->g, c->go, c->wpart,
+                     c->wpT[1], c->wpT[2], c->x0, c->a1, c->a2, c->gob,
+                     c->g2, c->g1, c->o, c->delta, c->g, c->wpart, c->bpart,
                      c->chpart, c->chout, c->loss, c->stpart, c->stout, c->bad, c->fallbacks,
                      c->gate0, c->gate };
     for (void* p : ptrs)
@@ -93,7 +94,7 @@ extern "C" mhd_closure* mhd_closure_create(int nx, int ny, int nz, void* hip_str
         c->sc.out_scale[f] = 1.0f; c->sc.target_scale[f] = 1.0f;
     }
     const size_t N = c->N;
-    c->nwg = wgrad_blocks(c->n, c->tiles_per_wg);
+    c->nwg = wgrad_blocks(c->n);
     bool ok = true;
     auto A = [&](void** p, size_t bytes) { if (ok && hipMalloc(p, bytes) != hipSuccess) ok = false; };
     A((void**)&c->params, NPARAM * 4); A((void**)&c->grads, NPARAM * 4);
@@ -102,15 +103,11 @@ extern "C" mhd_closure* mhd_closure_create(int nx, int ny, int nz, void* hip_str
         A((void**)&c->wp[l], packed_weight_elems(LCIN[l], LCOUT[l]) * 2);
         A((void**)&c->wpT[l], packed_weight_elems(LCOUT[l], LCIN[l]) * 2);
     }
-    A((void**)&c->x0, N * 8 * 2); A((void**)&c->x0T, N * 8 * 2);
-    A((void**)&c->a1, N * 32 * 2); A((void**)&c->a1T, N * 32 * 2);
-    A((void**)&c->a2, N * 32 * 2); A((void**)&c->a2T, N * 32 * 2);
-    A((void**)&c->gob, N * 8 * 2); A((void**)&c->gobT, N * 8 * 2);
-    A((void**)&c->g2, N * 32 * 2); A((void**)&c->g2T, N * 32 * 2);
-    A((void**)&c->g1, N * 32 * 2); A((void**)&c->g1T, N * 32 * 2);
+    A((void**)&c->x0, N * 8 * 2); A((void**)&c->a1, N * 32 * 2); A((void**)&c->a2, N * 32 * 2);
+    A((void**)&c->gob, N * 8 * 2); A((void**)&c->g2, N * 32 * 2); A((void**)&c->g1, N * 32 * 2);
     A((void**)&c->o, N * 8 * 4); A((void**)&c->delta, N * 8 * 4); A((void**)&c->g, N * 8 * 4);
-    A((void**)&c->go, N * 8 * 4);
-    A((void**)&c->wpart, (size_t)(c->nwg + 16) * 27 * 32 * 32 * 4);
+    A((void**)&c->wpart, (size_t)c->nwg * 27 * (8 * 32 + 32 * 32 + 32 * 8) * 4);
+    A((void**)&c->bpart, (size_t)c->nwg * (32 + 32 + 8) * 8);
     A((void**)&c->chpart, (size_t)CHSUM_BLOCKS * 8 * 8); A((void**)&c->chout, 16 * 8);
     A((void**)&c->loss, 8); A((void**)&c->bad, 4); A((void**)&c->fallbacks, 8);
     A((void**)&c->stpart, (size_t)STATS_BLOCKS * 8 * 5 * 8); A((void**)&c->stout, 40 * 8);
@@ -209,21 +206,20 @@ static int pack_all(mhd_closure* c)
     return MHD_OK;
 }
 
-// u: FP32 field-major [8][cell] -> delta [8][cell]; with `train` the
-// channel-major activation copies that wgrad reads are written too
-static int forward(mhd_closure* c, const float* u, bool train)
+// u: FP32 field-major [8][cell] -> delta [8][cell]
+static int forward(mhd_closure* c, const float* u)
 {
     int r = pack_all(c);
     if (r) return r;
-    HIP_TRY(c, launch_normalize(u, c->N, c->sc, c->x0, train ? c->x0T : nullptr, c->stream));
+    HIP_TRY(c, launch_normalize(u, c->N, c->sc, c->x0, c->stream));
     ConvArgs A;
     memset(&A, 0, sizeof A);
     A.n[0] = c->n[0]; A.n[1] = c->n[1]; A.n[2] = c->n[2];
-    A.x = c->x0; A.wp = c->wp[0]; A.bias = c->params + boff(0); A.yb = c->a1; A.ybT = train ? c->a1T : nullptr;
+    A.x = c->x0; A.wp = c->wp[0]; A.bias = c->params + boff(0); A.yb = c->a1;
     HIP_TRY(c, launch_conv3d(A, 8, 32, EPI_BIAS_RELU, c->stream));
-    A.x = c->a1; A.wp = c->wp[1]; A.bias = c->params + boff(1); A.yb = c->a2; A.ybT = train ? c->a2T : nullptr;
+    A.x = c->a1; A.wp = c->wp[1]; A.bias = c->params + boff(1); A.yb = c->a2;
     HIP_TRY(c, launch_conv3d(A, 32, 32, EPI_BIAS_RELU, c->stream));
-    A.x = c->a2; A.wp = c->wp[2]; A.bias = c->params + boff(2); A.yb = nullptr; A.ybT = nullptr; A.yf = c->o;
+    A.x = c->a2; A.wp = c->wp[2]; A.bias = c->params + boff(2); A.yb = nullptr; A.yf = c->o;
     HIP_TRY(c, launch_conv3d(A, 32, 8, EPI_BIAS_F32, c->stream));
     if (c->gate_on) {
         HIP_TRY(c, launch_gate(u, c->n, c->gs, c->gate0, c->gate, c->stream));
@@ -241,32 +237,31 @@ static int backward(mhd_closure* c, const float* target)
     const size_t N = c->N;
     HIP_TRY(c, launch_loss(c->delta, target, N, c->sc, c->g, c->chpart, c->loss, c->stream));
     HIP_TRY(c, launch_chsum(c->g, N, 1, N, 5, 1.0 / (double)N, c->chpart, c->chout + 8, c->stream));
-    HIP_TRY(c, launch_project_T(c->g, c->chout + 8, c->n, c->sc, c->go, c->stream));
-    if (c->gate_on) HIP_TRY(c, launch_row_scale(c->go, c->gate, N, c->stream));
-    HIP_TRY(c, launch_to_bf16(c->go, N, 8, c->gob, c->gobT, c->stream));
+    HIP_TRY(c, launch_project_T(c->g, c->chout + 8, c->gate_on ? c->gate : nullptr, c->n, c->sc, c->gob, c->stream));
+    WgradLayer L[3];
     WgradArgs W;
     W.n[0] = c->n[0]; W.n[1] = c->n[1]; W.n[2] = c->n[2];
     W.partial = c->wpart;
-    W.tiles_per_wg = c->tiles_per_wg;
-    // layer 3
-    W.xT = c->a2T; W.dyT = c->gobT;
-    HIP_TRY(c, launch_conv3d_wgrad(W, 32, 8, c->grads + woff(2), c->stream));
-    HIP_TRY(c, launch_bias_grad(c->gobT, N, 8, c->grads + boff(2), c->chpart, c->stream));
+    W.bias_partial = c->bpart;
+    auto wgrad = [&](int l, const uint16_t* x, const uint16_t* dy) {
+        W.x = x; W.dy = dy;
+        L[l] = WgradLayer{ W.partial, W.bias_partial, c->grads + woff(l), c->grads + boff(l), 27 * LCIN[l] * LCOUT[l], LCOUT[l] };
+        const hipError_t e = launch_conv3d_wgrad(W, LCIN[l], LCOUT[l], c->stream);
+        W.partial += (size_t)c->nwg * L[l].count;
+        W.bias_partial += (size_t)c->nwg * LCOUT[l];
+        return e;
+    };
+    HIP_TRY(c, wgrad(2, c->a2, c->gob));
     ConvArgs A;
     memset(&A, 0, sizeof A);
     A.n[0] = c->n[0]; A.n[1] = c->n[1]; A.n[2] = c->n[2];
-    A.x = c->gob; A.wp = c->wpT[2]; A.mask = c->a2; A.yb = c->g2; A.ybT = c->g2T;
+    A.x = c->gob; A.wp = c->wpT[2]; A.mask = c->a2; A.yb = c->g2;
     HIP_TRY(c, launch_conv3d(A, 8, 32, EPI_MASK, c->stream));
-    // layer 2
-    W.xT = c->a1T; W.dyT = c->g2T;
-    HIP_TRY(c, launch_conv3d_wgrad(W, 32, 32, c->grads + woff(1), c->stream));
-    HIP_TRY(c, launch_bias_grad(c->g2T, N, 32, c->grads + boff(1), c->chpart, c->stream));
-    A.x = c->g2; A.wp = c->wpT[1]; A.mask = c->a1; A.yb = c->g1; A.ybT = c->g1T;
+    HIP_TRY(c, wgrad(1, c->a1, c->g2));
+    A.x = c->g2; A.wp = c->wpT[1]; A.mask = c->a1; A.yb = c->g1;
     HIP_TRY(c, launch_conv3d(A, 32, 32, EPI_MASK, c->stream));
-    // layer 1
-    W.xT = c->x0T; W.dyT = c->g1T;
-    HIP_TRY(c, launch_conv3d_wgrad(W, 8, 32, c->grads + woff(0), c->stream));
-    HIP_TRY(c, launch_bias_grad(c->g1T, N, 32, c->grads + boff(0), c->chpart, c->stream));
+    HIP_TRY(c, wgrad(0, c->x0, c->g1));
+    HIP_TRY(c, launch_wgrad_reduce(L, 3, c->nwg, c->stream));
     return MHD_OK;
 }
 
@@ -275,7 +270,7 @@ extern "C" int mhd_closure_forward(mhd_closure* c, const float* u_dev, float* de
     int r = check_cl(c);
     if (r) return r;
     if (!u_dev || !delta_dev) return mhd_fail(MHD_EINVAL, "null device pointer");
-    if ((r = forward(c, u_dev, false))) return r;
+    if ((r = forward(c, u_dev))) return r;
     HIP_TRY(c, hipMemcpyAsync(delta_dev, c->delta, c->N * 8 * 4, hipMemcpyDeviceToDevice, c->stream));
     return MHD_OK;
 }
@@ -287,7 +282,7 @@ extern "C" int mhd_closure_grad(mhd_closure* c, const float* u_dev, const float*
     if (r) return r;
     if (!u_dev || !target_dev) return mhd_fail(MHD_EINVAL, "null device pointer");
     if (grad_host && n != NPARAM) return mhd_fail(MHD_EINVAL, "expected %zu gradient entries", NPARAM);
-    if ((r = forward(c, u_dev, true))) return r;
+    if ((r = forward(c, u_dev))) return r;
     if ((r = backward(c, target_dev))) return r;
     if (loss) HIP_TRY(c, hipMemcpyAsync(loss, c->loss, 8, hipMemcpyDeviceToHost, c->stream));
     if (grad_host) HIP_TRY(c, hipMemcpyAsync(grad_host, c->grads, NPARAM * 4, hipMemcpyDeviceToHost, c->stream));
@@ -302,7 +297,7 @@ extern "C" int mhd_closure_train_step(mhd_closure* c, const float* u_dev, const 
     if (r) return r;
     if (!u_dev || !target_dev) return mhd_fail(MHD_EINVAL, "null device pointer");
     if (!(lr > 0.0f)) return mhd_fail(MHD_EINVAL, "learning rate must be > 0");
-    if ((r = forward(c, u_dev, true))) return r;
+    if ((r = forward(c, u_dev))) return r;
     if ((r = backward(c, target_dev))) return r;
     c->adam_step += 1;
     HIP_TRY(c, launch_adam(c->params, c->grads, c->adam_m, c->adam_v, (int)NPARAM, lr, 0.9f, 0.999f, 1e-8f,
@@ -332,7 +327,7 @@ extern "C" int mhd_closure_step(mhd_closure* c, mhd_ctx* coarse, double cfl)
     int all0 = 0;
     float* u = (float*)mhd_internal_state(coarse, &all0);
     if (!all0) return mhd_fail(MHD_ESTATE, "coarse state not in its first buffer");
-    if ((r = forward(c, u, false))) return r;
+    if ((r = forward(c, u))) return r;
     HIP_TRY(c, launch_zero_int(c->bad, c->stream));
     HIP_TRY(c, launch_guard_levels(u, c->delta, c->n, (float)mhd_internal_gamma(coarse), c->bad, c->stream));
     HIP_TRY(c, launch_apply_level(u, c->delta, c->N * 8, c->bad, c->fallbacks, c->stream));
@@ -459,20 +454,26 @@ extern "C" int mhd_conv3d_wgrad(const int* n, int cin, int cout, const void* xT,
     hipStream_t s = (hipStream_t)stream;
     WgradArgs W;
     W.n[0] = n[0]; W.n[1] = n[1]; W.n[2] = n[2];
-    W.xT = (const uint16_t*)xT; W.dyT = (const uint16_t*)dyT;
-    const int nwg = wgrad_blocks(W.n, W.tiles_per_wg);
+    const int nwg = wgrad_blocks(W.n);
+    const size_t nw = (size_t)27 * cin * cout, N = (size_t)n[0] * n[1] * n[2];
     float *part = nullptr, *dw = nullptr, *db = nullptr;
-    const size_t nw = (size_t)27 * cin * cout;
-    HIP_TRY(&h, hipMalloc(&part, (size_t)(nwg + 16) * nw * 4));
+    double* bpart = nullptr;
+    uint16_t *x = nullptr, *dy = nullptr;
+    HIP_TRY(&h, hipMalloc(&part, nwg * nw * 4));
+    HIP_TRY(&h, hipMalloc(&bpart, (size_t)nwg * cout * 8));
     HIP_TRY(&h, hipMalloc(&dw, nw * 4));
     HIP_TRY(&h, hipMalloc(&db, cout * 4));
-    W.partial = part;
-    HIP_TRY(&h, launch_conv3d_wgrad(W, cin, cout, dw, s));
-    // the wgrad partials are consumed by then (same stream): reuse them
-    HIP_TRY(&h, launch_bias_grad((const uint16_t*)dyT, (size_t)n[0] * n[1] * n[2], cout, db, (double*)part, s));
+    HIP_TRY(&h, hipMalloc(&x, N * cin * 2));
+    HIP_TRY(&h, hipMalloc(&dy, N * cout * 2));
+    HIP_TRY(&h, launch_channel_last((const uint16_t*)xT, N, cin, x, s));
+    HIP_TRY(&h, launch_channel_last((const uint16_t*)dyT, N, cout, dy, s));
+    W.x = x; W.dy = dy; W.partial = part; W.bias_partial = bpart;
+    HIP_TRY(&h, launch_conv3d_wgrad(W, cin, cout, s));
+    const WgradLayer L{ part, bpart, dw, db, (int)nw, cout };
+    HIP_TRY(&h, launch_wgrad_reduce(&L, 1, nwg, s));
     HIP_TRY(&h, hipMemcpyAsync(dw_host, dw, nw * 4, hipMemcpyDeviceToHost, s));
     if (dbias_host) HIP_TRY(&h, hipMemcpyAsync(dbias_host, db, cout * 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(&h, hipStreamSynchronize(s));
-    (void)hipFree(part); (void)hipFree(dw); (void)hipFree(db);
+    (void)hipFree(part); (void)hipFree(bpart); (void)hipFree(dw); (void)hipFree(db); (void)hipFree(x); (void)hipFree(dy);
     return MHD_OK;
 }
