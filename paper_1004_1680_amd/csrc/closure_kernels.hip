@@ -113,7 +113,7 @@ hipError_t launch_pack_weights(const float* w, int cin, int cout, int flip, uint
 constexpr int CT_X = 16, CT_Y = 4;
 constexpr int CH_X = CT_X + 2, CH_Y = CT_Y + 2;
 constexpr int CL_X = 20;         // LDS cells per halo row (18 used)
-constexpr int CONV_WAVES = 8, CONV_THREADS = 64 * CONV_WAVES;
+constexpr int CONV_WAVES = 8, CONV_THREADS = 64 * CONV_WAVES, CONV_WGS = 256;
 
 template <int CIN, int COUT>
 struct ConvShape {
@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int co = 16 * (m0 + m) + 4 * g + e;
-            bias[m][e] = (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32) && co < COUT ? A.bias[co] : 0.0f;
+            bias[m][e] = (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32 || EPI == EPI_CLOSURE) && co < COUT ? A.bias[co] : 0.0f;
         }
     // waited for here: in the loop the wait would take in the halo loads that
     // are to stay in flight over the products
@@ -217,6 +217,9 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
 
     // the offsets within a halo fit in 32 bits (any grid of interest)
     const bool near = (unsigned long long)nx * ny * (S::TZ + 2) * (CIN * 2) < (1ull << 32);
+
+    double sum[4] = { 0, 0, 0, 0 };                         // EPI_CLOSURE: of the lane's 4 channels
+    __shared__ double wave_sum[EPI == EPI_CLOSURE ? CONV_WAVES : 1][8];
 
     // visits o, o + stride, ... below end of this workgroup's XCD
     const int tx = nx / CT_X, tz = nz / S::TZ, per = (tx * (ny / CT_Y) * tz) >> 3;
@@ -281,6 +284,13 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
     // before the previous barrier)
     auto work = [&](int visit, int buf, auto fetched) {
         const uint16_t* const tile = tiles + buf * S::LDS;
+        int bx, by, bz;
+        conv_tile(visit, tx, tz, bx, by, bz);
+        const long c0 = (long)(bx * CT_X) + (long)nx * ((long)(by * CT_Y) + (long)ny * (bz * S::TZ));
+        float gate[NB];
+        if constexpr (EPI == EPI_CLOSURE)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) gate[nb] = A.gate ? A.gate[c0 + r + (long)nx * (nb + (long)ny * wz)] : 1.0f;
         f4 acc[MBW][NB];
 #pragma unroll
         for (int m = 0; m < MBW; ++m)
@@ -361,13 +371,7 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
         }
 
         // epilogue: lane holds channels co = 16 (m0 + m) + 4 g + e of cell
-        // (x0 + r, y0 + nb, z0 + wz).  Stored from there, consecutive lanes
-        // would write 8 or 16 bytes 32 to 64 bytes apart, which the memory
-        // pipe takes lane by lane: 128^3, 32 -> 32 channels 162 us, 58 with
-        // no stores at all; 32 -> 8 93 and 42, 8 -> 32 61 and 14.
-        int bx, by, bz;
-        conv_tile(visit, tx, tz, bx, by, bz);
-        const long c0 = (long)(bx * CT_X) + (long)nx * ((long)(by * CT_Y) + (long)ny * (bz * S::TZ));
+        // (x0 + r, y0 + nb, z0 + wz)
 #pragma unroll
         for (int m = 0; m < MBW; ++m) {
             const int co0 = 16 * (m0 + m) + 4 * g;
@@ -379,7 +383,11 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[e] = acc[m][nb][e];
-                    if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32) v[e] += bias[m][e];
+                    if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32 || EPI == EPI_CLOSURE) v[e] += bias[m][e];
+                    if (EPI == EPI_CLOSURE) {
+                        if (A.gate) v[e] *= gate[nb];
+                        sum[e] += (double)v[e];
+                    }
                     if (EPI == EPI_BIAS_RELU) v[e] = fmaxf(v[e], 0.0f);
                 }
                 if (EPI == EPI_MASK && !STAGED) {
@@ -390,7 +398,7 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
                     for (int e = 0; e < 4; ++e)
                         if (!(bf2f(mm[e]) > 0.0f)) v[e] = 0.0f;
                 }
-                if (EPI == EPI_BIAS_F32 || EPI == EPI_F32) {
+                if (EPI == EPI_BIAS_F32 || EPI == EPI_F32 || EPI == EPI_CLOSURE) {
                     *reinterpret_cast<float4*>(A.yf + (size_t)c * COUT + co0) = make_float4(v[0], v[1], v[2], v[3]);
                 } else {
                     const uint2 w = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
@@ -432,19 +440,48 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
         work(o, buf, std::true_type());
     }
     work(o, buf, std::false_type());
+    if constexpr (EPI == EPI_CLOSURE) {
+        // the workgroup's channel sums: 16 lanes of a channel, then the waves
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int st = 8; st > 0; st >>= 1) sum[e] += __shfl_xor(sum[e], st, 64);
+        if (r == 0 && g < 2)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) wave_sum[wave][4 * g + e] = sum[e];
+        __syncthreads();
+        if (threadIdx.x < 8) {
+            double v = 0.0;
+            for (int w = 0; w < CONV_WAVES; ++w) v += wave_sum[w][threadIdx.x];
+            A.sums[(size_t)blockIdx.x * 8 + threadIdx.x] = v;
+        }
+    }
 }
+
+// one workgroup per CU, or one per tile: multiples of 8
+template <int CIN, int COUT>
+static int conv_grid(const int n[3])
+{
+    const int ntiles = (n[0] / CT_X) * (n[1] / CT_Y) * (n[2] / ConvShape<CIN, COUT>::TZ);
+    return ntiles < CONV_WGS ? ntiles : CONV_WGS;
+}
+int closure_sum_blocks(const int n[3]) { return conv_grid<32, 8>(n); }
 
 template <int CIN, int COUT>
 static hipError_t conv_dispatch_epi(const ConvArgs& A, int epi, hipStream_t s)
 {
-    const int ntiles = (A.n[0] / CT_X) * (A.n[1] / CT_Y) * (A.n[2] / ConvShape<CIN, COUT>::TZ);
-    constexpr int resident = 256;
-    const unsigned grid = (unsigned)(ntiles < resident ? ntiles : resident);      // multiples of 8
+    const unsigned grid = (unsigned)conv_grid<CIN, COUT>(A.n);
     switch (epi) {
     case EPI_BIAS_RELU: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_RELU>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
     case EPI_BIAS_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_F32>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
     case EPI_MASK: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_MASK>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
     case EPI_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_F32>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
+    case EPI_CLOSURE:
+        if constexpr (CIN == 32 && COUT == 8) {
+            hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_CLOSURE>), dim3(grid), dim3(CONV_THREADS), 0, s, A);
+            break;
+        }
+        return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -457,6 +494,42 @@ hipError_t launch_conv3d(const ConvArgs& A, int cin, int cout, int epi, hipStrea
     if (cin == 32 && cout == 8) return conv_dispatch_epi<32, 8>(A, epi, s);
     if (cin == 8 && cout == 8) return conv_dispatch_epi<8, 8>(A, epi, s);
     return hipErrorInvalidValue;
+}
+
+// ---------------------------------------------------------------------------
+// reductions over workgroups
+// ---------------------------------------------------------------------------
+
+// Sums of NV FP64 values per thread over the 256 threads of a workgroup, to
+// every thread: a fixed tree over the lanes, then the four waves in order.
+template <int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV])
+{
+    __shared__ double sh[NV][4];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+#pragma unroll
+        for (int st = 32; st > 0; st >>= 1) v[q] += __shfl_xor(v[q], st, 64);
+        if ((threadIdx.x & 63) == 0) sh[q][threadIdx.x >> 6] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) v[q] = ((sh[q][0] + sh[q][1]) + sh[q][2]) + sh[q][3];
+}
+
+// Totals of the nblk workgroups' sums partial[b * stride + first + q] of the
+// launch before, by every workgroup for itself: a launch of one workgroup for
+// them took 5 to 6 us, as long as the pass that needs them at 64^3.
+template <int NV>
+__device__ __forceinline__ void block_totals(const double* __restrict__ partial, int nblk, int stride, int first,
+                                             double (&total)[NV])
+{
+#pragma unroll
+    for (int q = 0; q < NV; ++q) total[q] = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += 256)
+#pragma unroll
+        for (int q = 0; q < NV; ++q) total[q] += partial[(size_t)b * stride + first + q];
+    block_sum(total);
 }
 
 // ---------------------------------------------------------------------------
@@ -652,15 +725,25 @@ __global__ void __launch_bounds__((64 * WgradShape<CI, CO>::WAVES), 3) conv3d_wg
 // grads of up to 3 layers from their workgroups' partial sums, in workgroup
 // order: a block of 256 threads takes 64 consecutive weights, thread group j
 // the j-th quarter of the workgroups (8 running sums each), then the quarters
-// in order; the blocks past the weights take the biases
+// in order; the blocks past the weights take the biases, the last one the loss
 struct WgradReduce {
     WgradLayer layer[3];
     int nlayer, nwg;
+    const double* loss_partial;                             // LOSS_SUMS per workgroup, or null
+    int nloss;
+    double loss_scale;
+    double* loss;
 };
 constexpr int WR_GROUPS = 4, WR_SUMS = 8;
 __global__ void __launch_bounds__(256) wgrad_reduce_kernel(WgradReduce R)
 {
     int b = blockIdx.x, l = 0;
+    if (R.loss_partial && blockIdx.x == gridDim.x - 1) {
+        double total[1];
+        block_totals(R.loss_partial, R.nloss, LOSS_SUMS, 0, total);
+        if (threadIdx.x == 0) *R.loss = total[0] * R.loss_scale;
+        return;
+    }
     while (l < R.nlayer && b >= (R.layer[l].count + 63) / 64) b -= (R.layer[l++].count + 63) / 64;
     if (l == R.nlayer) {                                   // biases: a wave per channel
         int c = 4 * b + (threadIdx.x >> 6);
@@ -716,10 +799,15 @@ hipError_t launch_conv3d_wgrad(const WgradArgs& A, int cin, int cout, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_wgrad_reduce(const WgradLayer* layers, int nlayer, int nwg, hipStream_t s)
+hipError_t launch_wgrad_reduce(const WgradLayer* layers, int nlayer, int nwg, const double* loss_partial, size_t N,
+                               double* loss, hipStream_t s)
 {
     WgradReduce R;
-    int blocks = 0;
+    int blocks = loss_partial ? 1 : 0;
+    R.loss_partial = loss_partial;
+    R.nloss = loss_partial ? loss_blocks(N) : 0;
+    R.loss_scale = 1.0 / (8.0 * (double)N);
+    R.loss = loss;
     R.nlayer = nlayer;
     R.nwg = nwg;
     for (int l = 0; l < nlayer; ++l) {
@@ -760,105 +848,136 @@ hipError_t launch_channel_last(const uint16_t* src, size_t N, int c, uint16_t* d
 // States are FP32 field-major u[f][cell]; the network sees x[cell][8] =
 // (u - mean) / std in bf16.
 
-__global__ void normalize_kernel(const float* __restrict__ u, size_t N, ClosureScales sc, uint16_t* __restrict__ x)
+// A state's fields: the fluid fields from one base, the faces from another
+// (the two may sit in different buffers of a solver).
+__device__ __forceinline__ const float* field(const ClosureState& u, int f, size_t N)
+{
+    return (f < 5 ? u.fluid : u.faces) + (size_t)f * N;
+}
+
+__global__ void normalize_kernel(ClosureState u, size_t N, ClosureScales sc, uint16_t* __restrict__ x)
 {
     for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
         float b[8];
 #pragma unroll
-        for (int f = 0; f < 8; ++f) b[f] = (u[(size_t)f * N + c] - sc.in_mean[f]) / sc.in_std[f];
+        for (int f = 0; f < 8; ++f) b[f] = (field(u, f, N)[c] - sc.in_mean[f]) / sc.in_std[f];
         *reinterpret_cast<uint4*>(x + c * 8) =
             make_uint4(f2bf2(b[0], b[1]), f2bf2(b[2], b[3]), f2bf2(b[4], b[5]), f2bf2(b[6], b[7]));
     }
 }
 
-hipError_t launch_normalize(const float* u, size_t N, const ClosureScales& sc, uint16_t* x, hipStream_t s)
+hipError_t launch_normalize(const ClosureState& u, size_t N, const ClosureScales& sc, uint16_t* x, hipStream_t s)
 {
     hipLaunchKernelGGL(normalize_kernel, dim3(2048), dim3(256), 0, s, u, N, sc, x);
     return hipGetLastError();
 }
 
-// Deterministic channel sums: a[c * cstride + f * fstride] over cells c for
-// channels f < nch; per-block partials then one final block.
-__global__ void __launch_bounds__(256) chsum_partial_kernel(const float* __restrict__ a, size_t N, size_t cstride,
-                                                            size_t fstride, int nch, double* partial)
-{
-    double acc[8] = { 0, 0, 0, 0, 0, 0, 0, 0 };
-    for (size_t c = (size_t)blockIdx.x * 256 + threadIdx.x; c < N; c += (size_t)gridDim.x * 256)
-        for (int f = 0; f < nch; ++f) acc[f] += (double)a[c * cstride + (size_t)f * fstride];
-    __shared__ double sh[8][256];
-    for (int f = 0; f < nch; ++f) sh[f][threadIdx.x] = acc[f];
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st)
-            for (int f = 0; f < nch; ++f) sh[f][threadIdx.x] += sh[f][threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x < nch) partial[(size_t)blockIdx.x * 8 + threadIdx.x] = sh[threadIdx.x][0];
-}
-
-// out[f] = scale * sum over blocks of partial[b * 8 + f]: 256 threads, each a
-// fixed stride of blocks, then a fixed tree (deterministic)
-__global__ void __launch_bounds__(256) chsum_final_kernel(const double* partial, int nblk, int nch, double scale,
-                                                          double* out)
-{
-    __shared__ double sh[8][256];
-    for (int f = 0; f < nch; ++f) {
-        double acc = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += 256) acc += partial[(size_t)b * 8 + f];
-        sh[f][threadIdx.x] = acc;
-    }
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st)
-            for (int f = 0; f < nch; ++f) sh[f][threadIdx.x] += sh[f][threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x < nch) out[threadIdx.x] = sh[threadIdx.x][0] * scale;
-}
-
-hipError_t launch_chsum(const float* a, size_t N, size_t cstride, size_t fstride, int nch, double scale,
-                        double* partial, double* out, hipStream_t s)
-{
-    const int nblk = CHSUM_BLOCKS;
-    hipLaunchKernelGGL(chsum_partial_kernel, dim3(nblk), dim3(256), 0, s, a, N, cstride, fstride, nch, partial);
-    hipLaunchKernelGGL(chsum_final_kernel, dim3(1), dim3(256), 0, s, partial, nblk, nch, scale, out);
-    return hipGetLastError();
-}
-
-// delta[f][c] = s_f (o[c][f] - mean_f) (f < 5); delta_b = curl of A = s (o5, o6, o7)
-__global__ void project_kernel(const float* __restrict__ o, const double* __restrict__ mean, int nx, int ny, int nz,
-                               ClosureScales sc, float* __restrict__ delta)
+// The passes over cells between the convolutions are bound by memory, so each
+// value is read as few times as its producers and readers allow: the gate and
+// the network's input come from one read of the state, the gate is applied
+// and the channel sums taken where the last layer's outputs are registers,
+// and the loss is taken where the correction is.  128^3, gated forward:
+// normalise + gate + scale + sums + projection + copy of the result 151 us ->
+// 77 us; 96 x 64 x 64 forward and backward, from 15 launches to 7.
+//
+// delta[f][c] = s_f (o[c][f] - mean_f) (f < 5); delta_b = curl of A = s (o5,
+// o6, o7), the means from the convolution's channel sums.  TRAIN: instead of
+// storing delta, the loss against target in the same pass: r = (delta -
+// target) / t_f, g = 2 r / t_f / (8 N), and per workgroup the sums of r^2 and
+// of the five fluid g (LOSS_SUMS values).  clear (may be null): set to 0.
+struct LossScales {
+    double g[8];        // 2 / t_f / (8 N): FP64 divisions, once on the host
+};
+template <bool TRAIN>
+__global__ void __launch_bounds__(256) project_kernel(const float* __restrict__ o, const double* __restrict__ sums,
+                                                      int nsums, int nx, int ny, int nz, ClosureScales sc,
+                                                      float* __restrict__ delta, const float* __restrict__ target,
+                                                      LossScales ls, double* __restrict__ partial, int* clear)
 {
     const size_t N = (size_t)nx * ny * nz;
+    double mean[5];
+    block_totals(sums, nsums, 8, 0, mean);
+#pragma unroll
+    for (int f = 0; f < 5; ++f) mean[f] *= 1.0 / (double)N;
+    if (clear && blockIdx.x == 0 && threadIdx.x == 0) *clear = 0;
+    double acc[LOSS_SUMS] = { 0, 0, 0, 0, 0, 0 };
     for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
         int i, j, k;
         cell_ijk((unsigned)c, nx, ny, i, j, k);
-        for (int f = 0; f < 5; ++f) delta[(size_t)f * N + c] = sc.out_scale[f] * (float)((double)o[c * 8 + f] - mean[f]);
+        const float4 lo = *reinterpret_cast<const float4*>(o + c * 8), hi = *reinterpret_cast<const float4*>(o + c * 8 + 4);
+        const float oc[8] = { lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w };
+        float d[8];
+#pragma unroll
+        for (int f = 0; f < 5; ++f) d[f] = sc.out_scale[f] * (float)((double)oc[f] - mean[f]);
         const size_t cxp = (size_t)wrap1(i + 1, nx) + (size_t)nx * (j + (size_t)ny * k);
         const size_t cyp = (size_t)i + (size_t)nx * (wrap1(j + 1, ny) + (size_t)ny * k);
         const size_t czp = (size_t)i + (size_t)nx * (j + (size_t)ny * wrap1(k + 1, nz));
         const float s5 = sc.out_scale[5], s6 = sc.out_scale[6], s7 = sc.out_scale[7];
-        const float ax = s5 * o[c * 8 + 5], ay = s6 * o[c * 8 + 6], az = s7 * o[c * 8 + 7];
-        delta[5 * N + c] = (s7 * o[cyp * 8 + 7] - az) - (s6 * o[czp * 8 + 6] - ay);
-        delta[6 * N + c] = (s5 * o[czp * 8 + 5] - ax) - (s7 * o[cxp * 8 + 7] - az);
-        delta[7 * N + c] = (s6 * o[cxp * 8 + 6] - ay) - (s5 * o[cyp * 8 + 5] - ax);
+        const float ax = s5 * oc[5], ay = s6 * oc[6], az = s7 * oc[7];
+        d[5] = (s7 * o[cyp * 8 + 7] - az) - (s6 * o[czp * 8 + 6] - ay);
+        d[6] = (s5 * o[czp * 8 + 5] - ax) - (s7 * o[cxp * 8 + 7] - az);
+        d[7] = (s6 * o[cxp * 8 + 6] - ay) - (s5 * o[cyp * 8 + 5] - ax);
+#pragma unroll
+        for (int f = 0; f < 8; ++f) {
+            if constexpr (TRAIN) {
+                const float ts = sc.target_scale[f];
+                const float r = (d[f] - target[(size_t)f * N + c]) / ts;
+                const float g = (float)((double)r * ls.g[f]);
+                acc[0] += (double)r * (double)r;
+                if (f < 5) acc[1 + f] += (double)g;
+                delta[(size_t)f * N + c] = g;
+            } else {
+                delta[(size_t)f * N + c] = d[f];
+            }
+        }
+    }
+    if constexpr (TRAIN) {
+        block_sum(acc);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int q = 0; q < LOSS_SUMS; ++q) partial[(size_t)blockIdx.x * LOSS_SUMS + q] = acc[q];
     }
 }
 
-hipError_t launch_project(const float* o, const double* mean, const int n[3], const ClosureScales& sc, float* delta,
-                          hipStream_t s)
+// one cell per thread up to LOSS_BLOCKS workgroups
+static unsigned cell_blocks(size_t N)
 {
-    hipLaunchKernelGGL(project_kernel, dim3(2048), dim3(256), 0, s, o, mean, n[0], n[1], n[2], sc, delta);
+    const size_t b = (N + 255) / 256;
+    return (unsigned)(b < LOSS_BLOCKS ? b : LOSS_BLOCKS);
+}
+int loss_blocks(size_t N) { return (int)cell_blocks(N); }
+
+hipError_t launch_project(const float* o, const double* sums, int nsums, const int n[3], const ClosureScales& sc,
+                          float* delta, int* clear, hipStream_t s)
+{
+    hipLaunchKernelGGL(project_kernel<false>, dim3(cell_blocks((size_t)n[0] * n[1] * n[2])), dim3(256), 0, s, o, sums,
+                       nsums, n[0], n[1], n[2], sc, delta, nullptr, LossScales{}, nullptr, clear);
+    return hipGetLastError();
+}
+
+hipError_t launch_project_loss(const float* o, const double* sums, int nsums, const int n[3], const ClosureScales& sc,
+                               const float* target, float* g, double* partial, hipStream_t s)
+{
+    const size_t N = (size_t)n[0] * n[1] * n[2];
+    LossScales ls;
+    for (int f = 0; f < 8; ++f) ls.g[f] = 2.0 / (double)sc.target_scale[f] / (8.0 * (double)N);
+    hipLaunchKernelGGL(project_kernel<true>, dim3(cell_blocks(N)), dim3(256), 0, s, o, sums, nsums, n[0], n[1], n[2],
+                       sc, g, target, ls, partial, nullptr);
     return hipGetLastError();
 }
 
 // adjoint of the projection, g[f][c] -> go[c][8], times the gate (gate may be
-// null) and rounded to bf16: the output gradient as dgrad and wgrad read it
-__global__ void project_T_kernel(const float* __restrict__ g, const double* __restrict__ gmean,
-                                 const float* __restrict__ gate, int nx, int ny, int nz, ClosureScales sc,
-                                 uint16_t* __restrict__ go)
+// null) and rounded to bf16: the output gradient as dgrad and wgrad read it.
+// partial: the workgroups' sums of project_kernel<true>.
+__global__ void __launch_bounds__(256) project_T_kernel(const float* __restrict__ g, const double* __restrict__ partial,
+                                                        int npartial, const float* __restrict__ gate, int nx, int ny,
+                                                        int nz, ClosureScales sc, uint16_t* __restrict__ go)
 {
     const size_t N = (size_t)nx * ny * nz;
+    double gmean[5];
+    block_totals(partial, npartial, LOSS_SUMS, 1, gmean);
+#pragma unroll
+    for (int f = 0; f < 5; ++f) gmean[f] *= 1.0 / (double)N;
     for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
         int i, j, k;
         cell_ijk((unsigned)c, nx, ny, i, j, k);
@@ -884,62 +1003,12 @@ __global__ void project_T_kernel(const float* __restrict__ g, const double* __re
     }
 }
 
-hipError_t launch_project_T(const float* g, const double* gmean, const float* gate, const int n[3],
+hipError_t launch_project_T(const float* g, const double* partial, const float* gate, const int n[3],
                             const ClosureScales& sc, uint16_t* go, hipStream_t s)
 {
-    hipLaunchKernelGGL(project_T_kernel, dim3(2048), dim3(256), 0, s, g, gmean, gate, n[0], n[1], n[2], sc, go);
-    return hipGetLastError();
-}
-
-// r = (delta - target) / t_f; g = 2 r / t_f / (8 N); per-block sums of r^2
-__global__ void __launch_bounds__(256) loss_kernel(const float* __restrict__ delta, const float* __restrict__ target,
-                                                   size_t N, ClosureScales sc, float* __restrict__ g, double* partial)
-{
-    const int f = blockIdx.y;
-    const float ts = sc.target_scale[f];
-    const double gsc = 2.0 / (double)ts / (8.0 * (double)N);
-    const size_t off = (size_t)f * N;
-    double acc = 0.0;
-    for (size_t c = (size_t)blockIdx.x * 256 + threadIdx.x; c < N; c += (size_t)gridDim.x * 256) {
-        const float r = (delta[off + c] - target[off + c]) / ts;
-        acc += (double)r * (double)r;
-        g[off + c] = (float)((double)r * gsc);
-    }
-    __shared__ double sh[256];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[(size_t)f * gridDim.x + blockIdx.x] = sh[0];
-}
-
-// out = scale * sum of partial[0 .. n), 256 threads at fixed strides, then a
-// fixed tree (deterministic)
-__global__ void __launch_bounds__(256) sum_final_kernel(const double* __restrict__ partial, int n, double scale,
-                                                        double* out)
-{
-    __shared__ double sh[256];
-    double acc = 0.0;
-    for (int b = threadIdx.x; b < n; b += 256) acc += partial[b];
-    sh[threadIdx.x] = acc;
-    __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = sh[0] * scale;
-}
-
-hipError_t launch_loss(const float* delta, const float* target, size_t N, const ClosureScales& sc, float* g,
-                       double* partial, double* out, hipStream_t s)
-{
-    // LOSS_BLOCKS per field, 8 * LOSS_BLOCKS dense partials (fits the CHSUM_BLOCKS * 8 scratch)
-    constexpr int LOSS_BLOCKS = CHSUM_BLOCKS / 2;
-    hipLaunchKernelGGL(loss_kernel, dim3(LOSS_BLOCKS, 8), dim3(256), 0, s, delta, target, N, sc, g, partial);
-    hipLaunchKernelGGL(sum_final_kernel, dim3(1), dim3(256), 0, s, partial, 8 * LOSS_BLOCKS, 1.0 / (8.0 * (double)N),
-                       out);
+    const size_t N = (size_t)n[0] * n[1] * n[2];
+    hipLaunchKernelGGL(project_T_kernel, dim3(cell_blocks(N)), dim3(256), 0, s, g, partial, loss_blocks(N), gate, n[0],
+                       n[1], n[2], sc, go);
     return hipGetLastError();
 }
 
@@ -947,9 +1016,8 @@ hipError_t launch_loss(const float* delta, const float* target, size_t N, const 
 // bit k of *bad is raised if some cell has rho <= 0, p < 0 or a non-finite
 // value at that theta (pressure from the cell-centred field, the mean of
 // the two faces; tested without a division as 2 rho (e - |B|^2/2) >= |m|^2).
-__global__ void __launch_bounds__(256) guard_levels_kernel(const float* __restrict__ u,
-                                                          const float* __restrict__ delta, int nx, int ny, int nz,
-                                                          int* bad)
+__global__ void __launch_bounds__(256) guard_levels_kernel(ClosureState u, const float* __restrict__ delta, int nx,
+                                                          int ny, int nz, int* bad)
 {
     // 4 consecutive x cells per thread (nx is a multiple of 4)
     const unsigned N = (unsigned)nx * ny * nz, N4 = N / 4;
@@ -963,19 +1031,19 @@ __global__ void __launch_bounds__(256) guard_levels_kernel(const float* __restri
         const unsigned czp = (unsigned)i + (unsigned)nx * ((unsigned)j + (unsigned)ny * wrap1(k + 1, nz));
         float u0[8][4], d0[8][4], u1[3][4], d1[3][4];
         for (int f = 0; f < 8; ++f) {
-            const float4 a4 = *reinterpret_cast<const float4*>(u + (size_t)f * N + c);
+            const float4 a4 = *reinterpret_cast<const float4*>(field(u, f, N) + c);
             const float4 b4 = *reinterpret_cast<const float4*>(delta + (size_t)f * N + c);
             u0[f][0] = a4.x; u0[f][1] = a4.y; u0[f][2] = a4.z; u0[f][3] = a4.w;
             d0[f][0] = b4.x; d0[f][1] = b4.y; d0[f][2] = b4.z; d0[f][3] = b4.w;
         }
         // upper faces: b_x of the next cell along x, b_y / b_z of the next row / plane
         for (int q = 0; q < 3; ++q) { u1[0][q] = u0[5][q + 1]; d1[0][q] = d0[5][q + 1]; }
-        u1[0][3] = u[(size_t)5 * N + xp];
+        u1[0][3] = field(u, 5, N)[xp];
         d1[0][3] = delta[(size_t)5 * N + xp];
         {
-            const float4 a4 = *reinterpret_cast<const float4*>(u + (size_t)6 * N + cyp);
+            const float4 a4 = *reinterpret_cast<const float4*>(field(u, 6, N) + cyp);
             const float4 b4 = *reinterpret_cast<const float4*>(delta + (size_t)6 * N + cyp);
-            const float4 c4 = *reinterpret_cast<const float4*>(u + (size_t)7 * N + czp);
+            const float4 c4 = *reinterpret_cast<const float4*>(field(u, 7, N) + czp);
             const float4 e4 = *reinterpret_cast<const float4*>(delta + (size_t)7 * N + czp);
             u1[1][0] = a4.x; u1[1][1] = a4.y; u1[1][2] = a4.z; u1[1][3] = a4.w;
             d1[1][0] = b4.x; d1[1][1] = b4.y; d1[1][2] = b4.z; d1[1][3] = b4.w;
@@ -1013,7 +1081,7 @@ __global__ void __launch_bounds__(256) guard_levels_kernel(const float* __restri
     if ((threadIdx.x & 63) == 0 && wb) atomicOr(bad, wb);
 }
 
-hipError_t launch_guard_levels(const float* u, const float* delta, const int n[3], float gamma, int* bad,
+hipError_t launch_guard_levels(const ClosureState& u, const float* delta, const int n[3], float gamma, int* bad,
                                hipStream_t s)
 {
     (void)gamma;                      // the sign of p does not depend on gamma > 1
@@ -1021,11 +1089,12 @@ hipError_t launch_guard_levels(const float* u, const float* delta, const int n[3
     return hipGetLastError();
 }
 
-// u += theta delta with the largest theta = 2^-k whose guard bit is clear;
-// none clear: u stays (the plain step).  counts[0] counts dropped
-// corrections, counts[1] reduced ones (theta < 1).
-__global__ void apply_level_kernel(float* __restrict__ u, const float* __restrict__ delta, size_t n, const int* bad,
-                                   int* counts)
+// out = u + theta delta with the largest theta = 2^-k whose guard bit is
+// clear; none clear: out = u (the plain step).  out may hold part of u.
+// counts[0] counts dropped corrections, counts[1] reduced ones (theta < 1).
+// 4 values per thread: a field is a multiple of 4 long.
+__global__ void __launch_bounds__(256) apply_level_kernel(ClosureState u, const float* __restrict__ delta, size_t N,
+                                                          const int* bad, int* counts, float* out)
 {
     const int mask = *bad;
     int lev = 0;
@@ -1034,22 +1103,23 @@ __global__ void apply_level_kernel(float* __restrict__ u, const float* __restric
         if (lev == GUARD_LEVELS) counts[0] += 1;
         else if (lev > 0) counts[1] += 1;
     }
-    if (lev == GUARD_LEVELS) return;
     const float th = ldexpf(1.0f, -lev);
-    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (size_t)gridDim.x * blockDim.x)
-        u[t] = u[t] + th * delta[t];
+    for (size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x; t < 2 * N; t += (size_t)gridDim.x * blockDim.x) {
+        const float* const src = 4 * t < 5 * N ? u.fluid : u.faces;
+        if (lev == GUARD_LEVELS && src == out) continue;
+        float4 v = reinterpret_cast<const float4*>(src)[t];
+        if (lev < GUARD_LEVELS) {
+            const float4 d = reinterpret_cast<const float4*>(delta)[t];
+            v.x = v.x + th * d.x; v.y = v.y + th * d.y; v.z = v.z + th * d.z; v.w = v.w + th * d.w;
+        }
+        reinterpret_cast<float4*>(out)[t] = v;
+    }
 }
 
-hipError_t launch_apply_level(float* u, const float* delta, size_t n, const int* bad, int* counts, hipStream_t s)
+hipError_t launch_apply_level(const ClosureState& u, const float* delta, size_t N, const int* bad, int* counts,
+                              float* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(apply_level_kernel, dim3(2048), dim3(256), 0, s, u, delta, n, bad, counts);
-    return hipGetLastError();
-}
-
-__global__ void zero_int_kernel(int* p) { if (threadIdx.x == 0) *p = 0; }
-hipError_t launch_zero_int(int* p, hipStream_t s)
-{
-    hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(64), 0, s, p);
+    hipLaunchKernelGGL(apply_level_kernel, dim3(2048), dim3(256), 0, s, u, delta, N, bad, counts, out);
     return hipGetLastError();
 }
 
@@ -1157,11 +1227,13 @@ hipError_t launch_stats(const float* u, const float* t, const int n[3], double* 
 }
 
 // Roughness gate: g0(c) = (1/8) sum_f inv_R[f] * sum over axes
-// |u_f(c+a) - 2 u_f(c) + u_f(c-a)| (u field-major FP32).  A thread takes 4
+// |u_f(c+a) - 2 u_f(c) + u_f(c-a)| (u field-major FP32), and the network
+// input x of normalize_kernel from the same loads.  A thread takes 4
 // consecutive x cells (nx is a multiple of 4): one 16-byte load per field
 // for the cells and for each y / z neighbour row, two scalars for x.
-__global__ void __launch_bounds__(256) gate_rough_kernel(const float* __restrict__ u, int nx, int ny, int nz,
-                                                         GateScales gs, float* __restrict__ g0)
+__global__ void __launch_bounds__(256) gate_rough_kernel(ClosureState u, int nx, int ny, int nz, GateScales gs,
+                                                         ClosureScales sc, float* __restrict__ g0,
+                                                         uint16_t* __restrict__ x)
 {
     const unsigned N = (unsigned)nx * ny * nz, N4 = N / 4;
     for (unsigned t = blockIdx.x * blockDim.x + threadIdx.x; t < N4; t += gridDim.x * blockDim.x) {
@@ -1175,8 +1247,10 @@ __global__ void __launch_bounds__(256) gate_rough_kernel(const float* __restrict
         const unsigned czm = (unsigned)i + (unsigned)nx * ((unsigned)j + (unsigned)ny * wrap1(k - 1, nz));
         const unsigned xm = row + wrap1(i - 1, nx), xp = row + wrap1(i + 4, nx);
         float acc[4] = { 0.f, 0.f, 0.f, 0.f };
+        float b[4][8];
+#pragma unroll
         for (int f = 0; f < 8; ++f) {
-            const float* uf = u + (size_t)f * N;
+            const float* uf = field(u, f, N);
             const float4 v = *reinterpret_cast<const float4*>(uf + c);
             const float4 vyp = *reinterpret_cast<const float4*>(uf + cyp);
             const float4 vym = *reinterpret_cast<const float4*>(uf + cym);
@@ -1191,56 +1265,50 @@ __global__ void __launch_bounds__(256) gate_rough_kernel(const float* __restrict
                 const float x2 = 2.0f * a[q + 1];
                 const float r = fabsf((a[q + 2] - x2) + a[q]) + fabsf((yp[q] - x2) + ym[q]) + fabsf((zp[q] - x2) + zm[q]);
                 acc[q] += r * w;
+                b[q][f] = (a[q + 1] - sc.in_mean[f]) / sc.in_std[f];
             }
         }
         *reinterpret_cast<float4*>(g0 + c) = make_float4(0.125f * acc[0], 0.125f * acc[1], 0.125f * acc[2], 0.125f * acc[3]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<uint4*>(x + (size_t)(c + q) * 8) =
+                make_uint4(f2bf2(b[q][0], b[q][1]), f2bf2(b[q][2], b[q][3]), f2bf2(b[q][4], b[q][5]), f2bf2(b[q][6], b[q][7]));
     }
 }
 
-// g(c) = max of g0 over c and its six face neighbours
+// g(c) = max of g0 over c and its six face neighbours, 4 cells per thread
 __global__ void __launch_bounds__(256) gate_max_kernel(const float* __restrict__ g0, int nx, int ny, int nz,
                                                        float* __restrict__ g)
 {
-    const size_t N = (size_t)nx * ny * nz;
-    for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
+    const unsigned N4 = (unsigned)nx * ny * nz / 4;
+    for (unsigned t = blockIdx.x * blockDim.x + threadIdx.x; t < N4; t += gridDim.x * blockDim.x) {
+        const unsigned c = 4 * t;
         int i, j, k;
-        cell_ijk((unsigned)c, nx, ny, i, j, k);
-        const size_t row = (size_t)nx * (j + (size_t)ny * k);
-        float m = g0[c];
-        m = fmaxf(m, g0[row + wrap1(i + 1, nx)]);
-        m = fmaxf(m, g0[row + wrap1(i - 1, nx)]);
-        m = fmaxf(m, g0[(size_t)i + (size_t)nx * (wrap1(j + 1, ny) + (size_t)ny * k)]);
-        m = fmaxf(m, g0[(size_t)i + (size_t)nx * (wrap1(j - 1, ny) + (size_t)ny * k)]);
-        m = fmaxf(m, g0[(size_t)i + (size_t)nx * (j + (size_t)ny * wrap1(k + 1, nz))]);
-        m = fmaxf(m, g0[(size_t)i + (size_t)nx * (j + (size_t)ny * wrap1(k - 1, nz))]);
-        g[c] = m;
+        cell_ijk(c, nx, ny, i, j, k);
+        const unsigned row = c - i;
+        const unsigned near[4] = { (unsigned)i + (unsigned)nx * ((unsigned)wrap1(j + 1, ny) + (unsigned)ny * k),
+                                   (unsigned)i + (unsigned)nx * ((unsigned)wrap1(j - 1, ny) + (unsigned)ny * k),
+                                   (unsigned)i + (unsigned)nx * ((unsigned)j + (unsigned)ny * wrap1(k + 1, nz)),
+                                   (unsigned)i + (unsigned)nx * ((unsigned)j + (unsigned)ny * wrap1(k - 1, nz)) };
+        const float4 v = *reinterpret_cast<const float4*>(g0 + c);
+        const float a[6] = { g0[row + wrap1(i - 1, nx)], v.x, v.y, v.z, v.w, g0[row + wrap1(i + 4, nx)] };
+        float m[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) m[q] = fmaxf(fmaxf(a[q + 1], a[q + 2]), a[q]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float4 w = *reinterpret_cast<const float4*>(g0 + near[e]);
+            m[0] = fmaxf(m[0], w.x); m[1] = fmaxf(m[1], w.y); m[2] = fmaxf(m[2], w.z); m[3] = fmaxf(m[3], w.w);
+        }
+        *reinterpret_cast<float4*>(g + c) = make_float4(m[0], m[1], m[2], m[3]);
     }
 }
 
-hipError_t launch_gate(const float* u, const int n[3], const GateScales& gs, float* g0, float* g, hipStream_t s)
+hipError_t launch_gate(const ClosureState& u, const int n[3], const GateScales& gs, const ClosureScales& sc, float* g0,
+                       float* g, uint16_t* x, hipStream_t s)
 {
-    hipLaunchKernelGGL(gate_rough_kernel, dim3(2048), dim3(256), 0, s, u, n[0], n[1], n[2], gs, g0);
+    hipLaunchKernelGGL(gate_rough_kernel, dim3(2048), dim3(256), 0, s, u, n[0], n[1], n[2], gs, sc, g0, x);
     hipLaunchKernelGGL(gate_max_kernel, dim3(2048), dim3(256), 0, s, g0, n[0], n[1], n[2], g);
-    return hipGetLastError();
-}
-
-// a[c][f] *= g[c], channel-last rows of 8
-__global__ void row_scale_kernel(float* __restrict__ a, const float* __restrict__ g, size_t N)
-{
-    for (size_t c = (size_t)blockIdx.x * blockDim.x + threadIdx.x; c < N; c += (size_t)gridDim.x * blockDim.x) {
-        const float s = g[c];
-        float4* p = reinterpret_cast<float4*>(a + c * 8);
-        float4 v0 = p[0], v1 = p[1];
-        v0.x *= s; v0.y *= s; v0.z *= s; v0.w *= s;
-        v1.x *= s; v1.y *= s; v1.z *= s; v1.w *= s;
-        p[0] = v0;
-        p[1] = v1;
-    }
-}
-
-hipError_t launch_row_scale(float* a, const float* g, size_t N, hipStream_t s)
-{
-    hipLaunchKernelGGL(row_scale_kernel, dim3(2048), dim3(256), 0, s, a, g, N);
     return hipGetLastError();
 }
 

@@ -48,7 +48,8 @@ struct mhd_closure {
     float *o, *delta, *g;
     float* wpart;          // wgrad partials of the three layers
     double* bpart;         // bias partials of the three layers
-    double *chpart, *chout, *loss, *stpart, *stout;
+    double *sums;           // channel sums of the last layer per workgroup
+    double *lpart, *loss, *stpart, *stout;
     bool gate_on;           // roughness gate of the output (mhd_closure_set_gate)
     GateScales gs;
     float *gate0, *gate;
@@ -70,7 +71,7 @@ extern "C" void mhd_closure_destroy(mhd_closure* c)
     void* ptrs[] = { c->params, c->grads, c->adam_m, c->adam_v, c->wp[0], c->wp[1], c->wp[2], c->wpT[0],
                      c->wpT[1], c->wpT[2], c->x0, c->a1, c->a2, c->gob,
                      c->g2, c->g1, c->o, c->delta, c->g, c->wpart, c->bpart,
-                     c->chpart, c->chout, c->loss, c->stpart, c->stout, c->bad, c->fallbacks,
+                     c->sums, c->lpart, c->loss, c->stpart, c->stout, c->bad, c->fallbacks,
                      c->gate0, c->gate };
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -108,7 +109,8 @@ extern "C" mhd_closure* mhd_closure_create(int nx, int ny, int nz, void* hip_str
     A((void**)&c->o, N * 8 * 4); A((void**)&c->delta, N * 8 * 4); A((void**)&c->g, N * 8 * 4);
     A((void**)&c->wpart, (size_t)c->nwg * 27 * (8 * 32 + 32 * 32 + 32 * 8) * 4);
     A((void**)&c->bpart, (size_t)c->nwg * (32 + 32 + 8) * 8);
-    A((void**)&c->chpart, (size_t)CHSUM_BLOCKS * 8 * 8); A((void**)&c->chout, 16 * 8);
+    A((void**)&c->sums, (size_t)closure_sum_blocks(c->n) * 8 * 8);
+    A((void**)&c->lpart, (size_t)LOSS_BLOCKS * LOSS_SUMS * 8);
     A((void**)&c->loss, 8); A((void**)&c->bad, 4); A((void**)&c->fallbacks, 8);
     A((void**)&c->stpart, (size_t)STATS_BLOCKS * 8 * 5 * 8); A((void**)&c->stout, 40 * 8);
     A((void**)&c->gate0, N * 4); A((void**)&c->gate, N * 4);
@@ -206,12 +208,16 @@ static int pack_all(mhd_closure* c)
     return MHD_OK;
 }
 
-// u: FP32 field-major [8][cell] -> delta [8][cell]
-static int forward(mhd_closure* c, const float* u)
+// The network on a state: its gated output o and the channel sums (and the
+// activations and the gate a backward pass reads)
+static int network(mhd_closure* c, const ClosureState& u)
 {
     int r = pack_all(c);
     if (r) return r;
-    HIP_TRY(c, launch_normalize(u, c->N, c->sc, c->x0, c->stream));
+    if (c->gate_on)
+        HIP_TRY(c, launch_gate(u, c->n, c->gs, c->sc, c->gate0, c->gate, c->x0, c->stream));
+    else
+        HIP_TRY(c, launch_normalize(u, c->N, c->sc, c->x0, c->stream));
     ConvArgs A;
     memset(&A, 0, sizeof A);
     A.n[0] = c->n[0]; A.n[1] = c->n[1]; A.n[2] = c->n[2];
@@ -220,24 +226,22 @@ static int forward(mhd_closure* c, const float* u)
     A.x = c->a1; A.wp = c->wp[1]; A.bias = c->params + boff(1); A.yb = c->a2;
     HIP_TRY(c, launch_conv3d(A, 32, 32, EPI_BIAS_RELU, c->stream));
     A.x = c->a2; A.wp = c->wp[2]; A.bias = c->params + boff(2); A.yb = nullptr; A.yf = c->o;
-    HIP_TRY(c, launch_conv3d(A, 32, 8, EPI_BIAS_F32, c->stream));
-    if (c->gate_on) {
-        HIP_TRY(c, launch_gate(u, c->n, c->gs, c->gate0, c->gate, c->stream));
-        HIP_TRY(c, launch_row_scale(c->o, c->gate, c->N, c->stream));
-    }
-    // projection: means of the 5 fluid outputs over the box
-    HIP_TRY(c, launch_chsum(c->o, c->N, 8, 1, 5, 1.0 / (double)c->N, c->chpart, c->chout, c->stream));
-    HIP_TRY(c, launch_project(c->o, c->chout, c->n, c->sc, c->delta, c->stream));
+    A.gate = c->gate_on ? c->gate : nullptr;
+    A.sums = c->sums;
+    HIP_TRY(c, launch_conv3d(A, 32, 8, EPI_CLOSURE, c->stream));
     return MHD_OK;
 }
 
-// loss of the last forward against target, and every parameter gradient
-static int backward(mhd_closure* c, const float* target)
+// u: FP32 field-major [8][cell]
+static ClosureState whole(const float* u) { return ClosureState{ u, u }; }
+
+// the network on u, the loss against target and every parameter gradient
+static int loss_and_grads(mhd_closure* c, const float* u, const float* target)
 {
-    const size_t N = c->N;
-    HIP_TRY(c, launch_loss(c->delta, target, N, c->sc, c->g, c->chpart, c->loss, c->stream));
-    HIP_TRY(c, launch_chsum(c->g, N, 1, N, 5, 1.0 / (double)N, c->chpart, c->chout + 8, c->stream));
-    HIP_TRY(c, launch_project_T(c->g, c->chout + 8, c->gate_on ? c->gate : nullptr, c->n, c->sc, c->gob, c->stream));
+    int r = network(c, whole(u));
+    if (r) return r;
+    HIP_TRY(c, launch_project_loss(c->o, c->sums, closure_sum_blocks(c->n), c->n, c->sc, target, c->g, c->lpart, c->stream));
+    HIP_TRY(c, launch_project_T(c->g, c->lpart, c->gate_on ? c->gate : nullptr, c->n, c->sc, c->gob, c->stream));
     WgradLayer L[3];
     WgradArgs W;
     W.n[0] = c->n[0]; W.n[1] = c->n[1]; W.n[2] = c->n[2];
@@ -261,8 +265,25 @@ static int backward(mhd_closure* c, const float* target)
     A.x = c->g2; A.wp = c->wpT[1]; A.mask = c->a1; A.yb = c->g1;
     HIP_TRY(c, launch_conv3d(A, 32, 32, EPI_MASK, c->stream));
     HIP_TRY(c, wgrad(0, c->x0, c->g1));
-    HIP_TRY(c, launch_wgrad_reduce(L, 3, c->nwg, c->stream));
+    HIP_TRY(c, launch_wgrad_reduce(L, 3, c->nwg, c->lpart, c->N, c->loss, c->stream));
     return MHD_OK;
+}
+
+// p begins bytes of memory of the current device, at a float's alignment.
+// Anything else a copy can write (host or a peer's memory) or refuse (a
+// range past its allocation) is left to a copy.
+static bool kernel_writable(const float* p, size_t bytes)
+{
+    hipPointerAttribute_t at;
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    int dev = -1;
+    const bool ok = reinterpret_cast<uintptr_t>(p) % sizeof(float) == 0 && hipGetDevice(&dev) == hipSuccess &&
+                    hipPointerGetAttributes(&at, p) == hipSuccess && at.type == hipMemoryTypeDevice &&
+                    at.device == dev && hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)p) == hipSuccess &&
+                    (const char*)p + bytes <= (const char*)base + size;
+    if (!ok) (void)hipGetLastError();       // what these calls left must not fail the next launch
+    return ok;
 }
 
 extern "C" int mhd_closure_forward(mhd_closure* c, const float* u_dev, float* delta_dev)
@@ -270,8 +291,13 @@ extern "C" int mhd_closure_forward(mhd_closure* c, const float* u_dev, float* de
     int r = check_cl(c);
     if (r) return r;
     if (!u_dev || !delta_dev) return mhd_fail(MHD_EINVAL, "null device pointer");
-    if ((r = forward(c, u_dev))) return r;
-    HIP_TRY(c, hipMemcpyAsync(delta_dev, c->delta, c->N * 8 * 4, hipMemcpyDeviceToDevice, c->stream));
+    if ((r = network(c, whole(u_dev)))) return r;
+    // u has been read by now: delta may be written over it
+    const size_t bytes = c->N * 8 * 4;
+    float* const out = kernel_writable(delta_dev, bytes) ? delta_dev : c->delta;
+    HIP_TRY(c, launch_project(c->o, c->sums, closure_sum_blocks(c->n), c->n, c->sc, out, nullptr, c->stream));
+    if (out != delta_dev)
+        HIP_TRY(c, hipMemcpyAsync(delta_dev, out, bytes, hipMemcpyDeviceToDevice, c->stream));
     return MHD_OK;
 }
 
@@ -282,8 +308,7 @@ extern "C" int mhd_closure_grad(mhd_closure* c, const float* u_dev, const float*
     if (r) return r;
     if (!u_dev || !target_dev) return mhd_fail(MHD_EINVAL, "null device pointer");
     if (grad_host && n != NPARAM) return mhd_fail(MHD_EINVAL, "expected %zu gradient entries", NPARAM);
-    if ((r = forward(c, u_dev))) return r;
-    if ((r = backward(c, target_dev))) return r;
+    if ((r = loss_and_grads(c, u_dev, target_dev))) return r;
     if (loss) HIP_TRY(c, hipMemcpyAsync(loss, c->loss, 8, hipMemcpyDeviceToHost, c->stream));
     if (grad_host) HIP_TRY(c, hipMemcpyAsync(grad_host, c->grads, NPARAM * 4, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -297,8 +322,7 @@ extern "C" int mhd_closure_train_step(mhd_closure* c, const float* u_dev, const 
     if (r) return r;
     if (!u_dev || !target_dev) return mhd_fail(MHD_EINVAL, "null device pointer");
     if (!(lr > 0.0f)) return mhd_fail(MHD_EINVAL, "learning rate must be > 0");
-    if ((r = forward(c, u_dev))) return r;
-    if ((r = backward(c, target_dev))) return r;
+    if ((r = loss_and_grads(c, u_dev, target_dev))) return r;
     c->adam_step += 1;
     HIP_TRY(c, launch_adam(c->params, c->grads, c->adam_m, c->adam_v, (int)NPARAM, lr, 0.9f, 0.999f, 1e-8f,
                            c->adam_step, c->stream));
@@ -323,14 +347,13 @@ extern "C" int mhd_closure_step(mhd_closure* c, mhd_ctx* coarse, double cfl)
     if (mhd_internal_stream(coarse) != c->stream)
         return mhd_fail(MHD_EINVAL, "closure and coarse handle must share a stream");
     if ((r = mhd_step_auto(coarse, cfl))) return r;
-    if ((r = mhd_internal_gather_first(coarse))) return r;
-    int all0 = 0;
-    float* u = (float*)mhd_internal_state(coarse, &all0);
-    if (!all0) return mhd_fail(MHD_ESTATE, "coarse state not in its first buffer");
-    if ((r = forward(c, u))) return r;
-    HIP_TRY(c, launch_zero_int(c->bad, c->stream));
+    void *fluid, *faces, *first;
+    mhd_internal_state(coarse, &fluid, &faces, &first);
+    const ClosureState u{ (const float*)fluid, (const float*)faces };
+    if ((r = network(c, u))) return r;
+    HIP_TRY(c, launch_project(c->o, c->sums, closure_sum_blocks(c->n), c->n, c->sc, c->delta, c->bad, c->stream));
     HIP_TRY(c, launch_guard_levels(u, c->delta, c->n, (float)mhd_internal_gamma(coarse), c->bad, c->stream));
-    HIP_TRY(c, launch_apply_level(u, c->delta, c->N * 8, c->bad, c->fallbacks, c->stream));
+    HIP_TRY(c, launch_apply_level(u, c->delta, c->N, c->bad, c->fallbacks, (float*)first, c->stream));
     mhd_internal_state_changed(coarse);   // the fused CFL of the plain step no longer applies
     return MHD_OK;
 }
@@ -470,7 +493,7 @@ extern "C" int mhd_conv3d_wgrad(const int* n, int cin, int cout, const void* xT,
     W.x = x; W.dy = dy; W.partial = part; W.bias_partial = bpart;
     HIP_TRY(&h, launch_conv3d_wgrad(W, cin, cout, s));
     const WgradLayer L{ part, bpart, dw, db, (int)nw, cout };
-    HIP_TRY(&h, launch_wgrad_reduce(&L, 1, nwg, s));
+    HIP_TRY(&h, launch_wgrad_reduce(&L, 1, nwg, nullptr, N, nullptr, s));
     HIP_TRY(&h, hipMemcpyAsync(dw_host, dw, nw * 4, hipMemcpyDeviceToHost, s));
     if (dbias_host) HIP_TRY(&h, hipMemcpyAsync(dbias_host, db, cout * 4, hipMemcpyDeviceToHost, s));
     HIP_TRY(&h, hipStreamSynchronize(s));

@@ -72,3 +72,40 @@ def test_layers_over_many_tiles(env, cin, cout):
     flat = d64.reshape(N, cout)
     close(torch.from_numpy(dw).cuda(), torch.stack([shifted(torch, x64, o).T @ flat for o in range(27)]), "wgrad")
     close(torch.from_numpy(db).cuda(), flat.sum(0), "bias gradient")
+
+
+def test_forward_destinations(env):
+    """The correction written over the state, at an address of 4 but not 16
+    bytes, into pinned host memory and from a captured graph is the one of a
+    plain call, bit for bit."""
+    torch, mhd = env
+    say("case: forward destinations")
+    n = (32, 32, 64)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    u = torch.randn((8, n[2], n[1], n[0]), generator=g, device="cuda") * 0.1 + 1.0
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        cl = mhd.Closure(n, stream=side)
+        cl.set_params(np.random.default_rng(5).normal(0.0, 0.05, mhd.NPARAM).astype(np.float32))
+        cl.set_gate(np.full(8, 0.5))
+        want = cl.forward(u)
+        over = u.clone()
+        cl.forward(over, out=over)
+        odd = torch.empty(u.numel() + 1, device="cuda")[1:].reshape(u.shape)
+        cl.forward(u, out=odd)
+        host = torch.empty(u.shape, pin_memory=True)
+        cl.forward(u, out=host)
+        side.synchronize()
+        for name, got in (("over the state", over), ("odd address", odd), ("host", host.cuda())):
+            say("destination:", name)
+            assert torch.equal(got, want)
+        replayed = torch.empty_like(u)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            cl.forward(u, out=replayed)
+        for _ in range(3):
+            replayed.zero_()
+            graph.replay()
+            side.synchronize()
+            assert torch.equal(replayed, want)
