@@ -91,17 +91,28 @@ hipError_t launch_pack_weights(const float* w, int cin, int cout, int flip, uint
 // forward / dgrad convolution
 // ---------------------------------------------------------------------------
 
-// Persistent workgroups of 8 waves, one per CU.  A wave keeps its weights in
-// registers for the whole launch (read from L2 once per workgroup, where a
-// workgroup per tile read 55 KiB per wave and tile, as many L1 cycles as MFMA
-// cycles), and the next tile's halo is fetched into registers while the
-// current tile is multiplied from LDS (two buffers, one barrier per tile).
-// A wave takes 16 output channels of one z plane: with 32 output channels two
-// waves share a plane (tile 16 x 4 x 4 cells), with 8 one wave does (16 x 4 x
-// 8).  Its weights are 27 fragments (108 registers) with 32 input channels,
-// one offset per K step, and 7 with 8, four offsets per K step.
-// A wave's 4 MFMA column blocks are the 4 rows y of its plane, lane r the
-// cell x.  The input halo is staged in LDS once per tile, rows of 20 cells.
+// Persistent workgroups, one per CU.  A wave keeps its weights in registers
+// for the whole launch (a workgroup per tile read 55 KiB of them per wave and
+// tile, as many L1 cycles as MFMA cycles), and the next tile's halo is on its
+// way through registers to the second of two LDS buffers while a tile is
+// multiplied (one barrier per tile).  With 32 input channels a workgroup is 4
+// waves, one per SIMD with all its registers: a halo row read from LDS feeds
+// all 32 output channels of a z plane (54 weight fragments, 216 registers;
+// tile 16 x 4 x 4 cells), or the 8 of two planes (16 x 4 x 8), whose 16 MFMA
+// rows are those of two neighbouring rows y (a pair of output rows has 4 input
+// rows, so 36 products where one row per accumulator takes 54; 36 fragments
+// with the absent offsets zero).  With 8 input channels (7 fragments of four
+// offsets each) it is 8 waves: bound by memory, not by products.
+// 128^3 in us (workgroup per tile -> persistent, 8 waves, loads and epilogue
+// before and after the products -> now): 32 -> 32 channels 151 -> 135 -> 114,
+// 32 -> 8 99 -> 83 -> 62, 8 -> 32 64 -> 58 -> 49.  Gated forward with all
+// passes, of the last two forms: 96 x 64 x 64 83.5 -> 81.5, 64^3 65.5 -> 66.2,
+// 32^3 36.3 -> 38.6 (a tile or less per workgroup: the longer start is not
+// paid back).  The products alone with their LDS reads take 75, 36 and
+// 31 (all 116 GFLOP of the first at 1.5 PFLOP/s); the halo's way through
+// registers costs 25, the epilogue 10, stores in flight 10.
+// A wave's MFMA columns are the 16 cells of a row, lane r the cell x.  The
+// input halo is staged in LDS once per tile, rows of 20 cells.
 // A B read has 16 lanes on 16 consecutive cells reading the same 16-byte
 // chunk; with 64-byte cells (CIN = 32) the chunks of cells h and h + 4 would
 // share banks, so chunk q of cell h is stored at position q ^ 2 ((h >> 2) &
@@ -113,19 +124,28 @@ hipError_t launch_pack_weights(const float* w, int cin, int cout, int flip, uint
 constexpr int CT_X = 16, CT_Y = 4;
 constexpr int CH_X = CT_X + 2, CH_Y = CT_Y + 2;
 constexpr int CL_X = 20;         // LDS cells per halo row (18 used)
-constexpr int CONV_WAVES = 8, CONV_THREADS = 64 * CONV_WAVES, CONV_WGS = 256;
+constexpr int CONV_WGS = 256;
 
 template <int CIN, int COUT>
 struct ConvShape {
+    static constexpr int WAVES = CIN == 32 ? 4 : 8, THREADS = 64 * WAVES;
+    static constexpr bool FOLD = CIN == 32 && COUT == 8;   // MFMA rows hold 8 channels of two rows y
     static constexpr int MB = (COUT + 15) / 16;            // 16-row blocks of output channels
-    static constexpr int MBW = 1;                          // of them in a wave
-    static constexpr int WM = MB / MBW;                    // waves that share a z plane
-    static constexpr int TZ = CONV_WAVES / WM;             // z planes of a tile
+    static constexpr int MBW = CIN == 32 ? MB : 1;         // of them in a wave
+    static constexpr int ZW = FOLD ? 2 : 1;                // z planes of a wave
+    static constexpr int TZ = WAVES * MBW / MB * ZW;       // of a tile
     static constexpr int CELLS = CH_X * CH_Y * (TZ + 2);   // halo cells
     static constexpr int LDS = CL_X * CH_Y * (TZ + 2) * CIN;   // bf16 values of a buffer
     static constexpr int PARTS = CIN / 8;                  // 16-byte pieces per cell
-    static constexpr int KS = (27 * CIN + 31) / 32;
-    static constexpr int FILL = (CELLS * PARTS + CONV_THREADS - 1) / CONV_THREADS;
+    static constexpr int KS = FOLD ? 36 : (27 * CIN + 31) / 32;    // weight fragments per 16 rows
+    static constexpr int NB = FOLD ? CT_Y / 2 : CT_Y;      // accumulators per plane and 16 rows
+    static constexpr int NA = ZW * MBW * NB;
+    static constexpr int FILL = (CELLS * PARTS + THREADS - 1) / THREADS;
+    // tiles the loads run ahead: to be filled at the end of this one, or of
+    // the next, each piece loaded when the one before has left its registers
+    // (128^3, 32 -> 8 channels 69 -> 63 us; 32 -> 32 has no registers for it)
+    static constexpr int AHEAD = FOLD ? 2 : 1;
+    static constexpr int PHASES = CIN == 32 ? (ZW + 2) * CH_Y : KS;    // parts a tile's products are taken in
 };
 // position (in 8-bf16 chunks) of chunk q of halo cell h
 template <int CIN>
@@ -139,12 +159,30 @@ __device__ __forceinline__ int conv_chunk(int h, int q) { return CIN == 32 ? (q 
 // the next z are read again a few dozen visits later.  (Grids are multiples of
 // 32: the number of tiles is a multiple of 16 and ty of 8.)
 constexpr int CONV_YG = 4;
-__device__ __forceinline__ void conv_tile(int o, int tx, int tz, int& x, int& y, int& z)
+// A visit o is x + tx (y % YG + YG (z + tz (y / YG))), tile coordinates
+// stepped by a fixed number of visits with carries (a division by tx or tz is
+// a chain of a dozen scalar instructions).
+struct ConvVisit {
+    int x, yl, z, yh;
+};
+__device__ __forceinline__ ConvVisit conv_visit(int o, int tx, int tz)
 {
-    x = o % tx;
     const int q = o / tx, w = q / CONV_YG;
-    y = (w / tz) * CONV_YG + q % CONV_YG;
-    z = w % tz;
+    return ConvVisit{ o % tx, q % CONV_YG, w % tz, w / tz };
+}
+__device__ __forceinline__ ConvVisit conv_next(ConvVisit v, ConvVisit d, int tx, int tz)
+{
+    v.x += d.x;
+    int c = v.x >= tx;
+    v.x -= c ? tx : 0;
+    v.yl += d.yl + c;
+    c = v.yl >= CONV_YG;
+    v.yl -= c ? CONV_YG : 0;
+    v.z += d.z + c;
+    c = v.z >= tz;
+    v.z -= c ? tz : 0;
+    v.yh += d.yh + c;
+    return v;
 }
 
 // the fragment of cells x from those of x - 1 and x + 1 (16 lanes of a K
@@ -157,7 +195,7 @@ __device__ __forceinline__ bf16x8 between(bf16x8 left, bf16x8 right)
     i4 o;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int a = __builtin_amdgcn_update_dpp(0, l[q], 0x101, 0xf, 0x7, false);        // row_shl:1
+        const int a = __builtin_amdgcn_mov_dpp(l[q], 0x101, 0xf, 0x7, false);              // row_shl:1, the others follow
         o[q] = __builtin_amdgcn_update_dpp(a, r[q], 0x111, 0xf, 0x8, false);               // row_shr:1
     }
     return __builtin_bit_cast(bf16x8, o);
@@ -171,131 +209,261 @@ __device__ __forceinline__ uint32_t masked2(uint32_t v, uint32_t mk)
     return lo | hi;
 }
 
-template <int CIN, int COUT, int EPI>
-__global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
+#define INLINE __attribute__((always_inline))   // (a lambda called outright keeps what it captures in memory)
+// Offset: an unsigned type that counts the 16-byte pieces of the input
+template <int CIN, int COUT, int EPI, typename Offset>
+__global__ void __launch_bounds__((ConvShape<CIN, COUT>::THREADS), (ConvShape<CIN, COUT>::WAVES / 4)) conv3d_kernel(ConvArgs A)
 {
     using S = ConvShape<CIN, COUT>;
-    constexpr int MBW = S::MBW, NB = CT_Y, KS = S::KS, FILL = S::FILL, PIECES = S::CELLS * S::PARTS;
+    constexpr int THREADS = S::THREADS, MBW = S::MBW, ZW = S::ZW, NB = S::NB, NA = S::NA, KS = S::KS, FILL = S::FILL, AHEAD = S::AHEAD;
+    constexpr int PIECES = S::CELLS * S::PARTS;
+    constexpr bool FOLD = S::FOLD, BIAS = EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32 || EPI == EPI_CLOSURE;
     // 32 output channels in bf16 leave through LDS (two buffers, so that the
     // barrier of a tile is enough): 4 chunks of 16 bytes per cell, chunk q of
     // cell c at q ^ ((c >> 2) & 3), which spreads 16 cells over the banks
     constexpr bool STAGED = COUT == 32 && (EPI == EPI_BIAS_RELU || EPI == EPI_MASK);
     constexpr int OUT = STAGED ? CT_X * CT_Y * S::TZ * COUT : 8;
+    constexpr int CHUNKS = STAGED ? OUT / 8 / THREADS : 1;
     __shared__ __align__(16) uint16_t tiles[2 * S::LDS];
     __shared__ __align__(16) uint16_t stage[2 * OUT];
+    __shared__ double wave_sum[EPI == EPI_CLOSURE ? S::WAVES : 1][8];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 4, r = lane & 15;
-    const int m0 = (wave % S::WM) * MBW, wz = wave / S::WM;
+    const int m0 = (wave * MBW) % S::MB, wz = wave * MBW / S::MB * ZW;     // first block and plane of the wave
     const int nx = A.n[0], ny = A.n[1], nz = A.n[2];
     const uint16_t* __restrict__ x = A.x;
     const uint4* __restrict__ wp = reinterpret_cast<const uint4*>(A.wp);
 
     bf16x8 a[KS][MBW];
+    int rows[2] = { r < 8 ? -1 : 0, r < 8 ? 0 : -1 };       // (opaque: no branch around the loads)
+    asm volatile("" : "+v"(rows[0]), "+v"(rows[1]));
 #pragma unroll
     for (int s = 0; s < KS; ++s)
 #pragma unroll
-        for (int m = 0; m < MBW; ++m) a[s][m] = as_bf8(wp[((size_t)s * S::MB + m0 + m) * 64 + lane]);
+        for (int m = 0; m < MBW; ++m) {
+            if constexpr (FOLD) {
+                // fragment (dz, j, dx): rows 0 - 7 the weights of dy = j, rows
+                // 8 - 15 those of dy = j - 1 (input row 2 P + j to output rows
+                // 2 P and 2 P + 1)
+                const int dz = s / 12, j = s / 3 % 4, dx = s % 3, dy = j - (r >> 3);
+                uint4 v = wp[(dz * 9 + (dy < 0 ? 0 : dy > 2 ? 2 : dy) * 3 + dx) * 64 + (lane & ~8)];
+                if (j == 0 || j == 3) {
+                    const int keep = rows[j / 3];
+                    v = make_uint4(v.x & keep, v.y & keep, v.z & keep, v.w & keep);
+                }
+                a[s][m] = as_bf8(v);
+            } else {
+                a[s][m] = as_bf8(wp[((size_t)s * S::MB + m0 + m) * 64 + lane]);
+            }
+        }
+    // the lane's 4 output channels of block m; where it holds none of COUT = 8
+    // (rows 8 - 15 without FOLD) it stores nothing
+    auto channel = [&](int m) INLINE { return FOLD ? 4 * (g & 1) : 16 * (m0 + m) + 4 * g; };
     float bias[MBW][4];
 #pragma unroll
     for (int m = 0; m < MBW; ++m)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int co = 16 * (m0 + m) + 4 * g + e;
-            bias[m][e] = (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32 || EPI == EPI_CLOSURE) && co < COUT ? A.bias[co] : 0.0f;
-        }
-    // waited for here: in the loop the wait would take in the halo loads that
-    // are to stay in flight over the products
-#pragma unroll
-    for (int s = 0; s < KS; ++s)
-#pragma unroll
-        for (int m = 0; m < MBW; ++m) asm volatile("" : "+v"(a[s][m]));
-#pragma unroll
-    for (int m = 0; m < MBW; ++m)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(bias[m][e]));
-
-    // the offsets within a halo fit in 32 bits (any grid of interest)
-    const bool near = (unsigned long long)nx * ny * (S::TZ + 2) * (CIN * 2) < (1ull << 32);
-
-    double sum[4] = { 0, 0, 0, 0 };                         // EPI_CLOSURE: of the lane's 4 channels
-    __shared__ double wave_sum[EPI == EPI_CLOSURE ? CONV_WAVES : 1][8];
-
+        for (int e = 0; e < 4; ++e) bias[m][e] = BIAS && channel(m) + e < COUT ? A.bias[channel(m) + e] : 0.0f;
     // visits o, o + stride, ... below end of this workgroup's XCD
-    const int tx = nx / CT_X, tz = nz / S::TZ, per = (tx * (ny / CT_Y) * tz) >> 3;
+    const int tx = nx / CT_X, ty = ny / CT_Y, tz = nz / S::TZ, per = (tx * ty * tz) >> 3;
     const int stride = gridDim.x >> 3, end = ((blockIdx.x & 7) + 1) * per;
     int o = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (o >= end) return;
+    ConvVisit at = conv_visit(o, tx, tz);
+    const ConvVisit hop = conv_visit(stride, tx, tz);
 
     // piece q of halo cell h per thread and round, consecutive threads on
-    // consecutive pieces (contiguous along x in global memory); the cell and
-    // its LDS place, one register per round (opaque below, or the compiler
-    // keeps every derived address across the loop and spills)
-    int place[FILL];                                        // LDS offset / 8, hx, hy, hz
-    uint4 fv[FILL];
+    // consecutive pieces (contiguous along x in global memory): its LDS place
+    // (in pieces) with the faces of the halo it lies on (bits 14 + 2 axis lower, 15 + 2
+    // axis upper; one register per round, opaque below, or the compiler keeps
+    // every derived value across the loop and spills), and its offset from
+    // the halo's first cell, unwrapped
+    int place[FILL];
+    Offset delta[FILL], src[FILL];                          // in pieces, modulo the type's range
+    typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i4;
+    i4 fv[FILL];
+    const Offset wx = (Offset)S::PARTS * nx, wy = wx * ny, wz_ = wy * nz;      // periods
+    constexpr int HOP = THREADS / S::PARTS;                 // cells from round to round
+    const int h0 = threadIdx.x / S::PARTS, q = threadIdx.x % S::PARTS;
+    int hx = h0 % CH_X, hy = h0 / CH_X % CH_Y, hz = h0 / (CH_X * CH_Y);
+    Offset off = (Offset)(S::PARTS * hx + q) + wx * hy + wy * hz;
 #pragma unroll
     for (int f = 0; f < FILL; ++f) {
-        // threads past the last piece repeat the first ones (the same values
-        // to the same place), so that no load sits in a branch
-        int t = threadIdx.x + CONV_THREADS * f;
-        t = t < PIECES ? t : t - PIECES;
-        const int h = t / S::PARTS, q = t % S::PARTS;
-        const int hx = h % CH_X, hy = (h / CH_X) % CH_Y, hz = h / (CH_X * CH_Y);
+        if (f + 1 == FILL && THREADS * FILL > PIECES && (int)threadIdx.x + THREADS * f >= PIECES) {
+            // threads past the last piece repeat the first ones (the same
+            // values to the same place), so that no load sits in a branch
+            const int h = (threadIdx.x + THREADS * f - PIECES) / S::PARTS;
+            hx = h % CH_X; hy = h / CH_X % CH_Y; hz = h / (CH_X * CH_Y);
+            off = (Offset)(S::PARTS * hx + q) + wx * hy + wy * hz;
+        }
         const int hl = (hz * CH_Y + hy) * CL_X + hx;
-        place[f] = (hl * S::PARTS + conv_chunk<CIN>(hl, q)) | hx << 14 | hy << 19 | hz << 22 | q << 26;
+        place[f] = (hl * S::PARTS + conv_chunk<CIN>(hl, q)) | (hx == 0) << 14 | (hx == CH_X - 1) << 15 | (hy == 0) << 16 |
+                   (hy == CH_Y - 1) << 17 | (hz == 0) << 18 | (hz == S::TZ + 1) << 19;
+        delta[f] = off;
+        // the next round's cell, without divisions
+        off += (Offset)(S::PARTS * (HOP % CH_X)) + wx * (HOP / CH_X % CH_Y) + wy * (HOP / (CH_X * CH_Y));
+        hx += HOP % CH_X;
+        hy += HOP / CH_X % CH_Y;
+        hz += HOP / (CH_X * CH_Y);
+        if (hx >= CH_X) { hx -= CH_X; ++hy; off += wx - S::PARTS * CH_X; }
+        if (hy >= CH_Y) { hy -= CH_Y; ++hz; off += wy - wx * CH_Y; }
     }
-    unsigned delta[FILL];                                   // byte offset from the halo's first cell, unwrapped
+    // where the pieces of a tile's halo are; its first cell
+    auto aim = [&](const ConvVisit& v) INLINE {
+        const int by = v.yh * CONV_YG + v.yl;
+        const long c0 = (long)(v.x * CT_X) + (long)nx * ((long)(by * CT_Y) + (long)ny * (v.z * S::TZ));
+        const Offset first = (Offset)(c0 * S::PARTS) - (S::PARTS + wx + wy);
 #pragma unroll
-    for (int f = 0; f < FILL; ++f)
-        delta[f] = (unsigned)CIN * 2u * ((unsigned)(place[f] >> 14 & 31) +
-                                         (unsigned)nx * ((unsigned)(place[f] >> 19 & 7) + (unsigned)ny * (unsigned)(place[f] >> 22 & 15))) +
-                   16u * (unsigned)(place[f] >> 26 & 3);
-    auto fetch = [&](int v) {
-        int bx, by, bz;
-        conv_tile(v, tx, tz, bx, by, bz);
-        const int x0 = bx * CT_X - 1, y0 = by * CT_Y - 1, z0 = bz * S::TZ - 1;
-        if (bx > 0 && by > 0 && bz > 0 && bx + 1 < tx && by + 1 < ny / CT_Y && bz + 1 < tz && near) {
-            // a halo that does not wrap: one addition per load
-            const char* const p = reinterpret_cast<const char*>(x + (size_t)CIN * ((size_t)x0 + (size_t)nx * ((size_t)y0 + (size_t)ny * z0)));
-#pragma unroll
-            for (int f = 0; f < FILL; ++f) fv[f] = *reinterpret_cast<const uint4*>(p + delta[f]);
-        } else {
+        for (int f = 0; f < FILL; ++f) src[f] = first + delta[f];
+        // a tile at a face of the grid: the pieces beyond it, one period back
+        auto wrap = [&](int bit, Offset period) INLINE {
 #pragma unroll
             for (int f = 0; f < FILL; ++f) {
                 int p = place[f];
                 asm volatile("" : "+v"(p));
-                const unsigned src = (unsigned)wrap1(x0 + (p >> 14 & 31), nx) +
-                                     (unsigned)nx * ((unsigned)wrap1(y0 + (p >> 19 & 7), ny) +
-                                                     (unsigned)ny * (unsigned)wrap1(z0 + (p >> 22 & 15), nz));
-                fv[f] = ld16(x + (size_t)src * CIN + 8 * (p >> 26 & 3));
+                src[f] += (Offset)0 - (Offset)(p >> bit & 1) & period;
+            }
+        };
+        if (v.x == 0) wrap(14, wx);
+        if (v.x + 1 == tx) wrap(15, 0 - wx);
+        if (by == 0) wrap(16, wy);
+        if (by + 1 == ty) wrap(17, 0 - wy);
+        if (v.z == 0) wrap(18, wz_);
+        if (v.z + 1 == tz) wrap(19, 0 - wz_);
+        return c0;
+    };
+    auto load = [&](int f) INLINE { fv[f] = reinterpret_cast<const i4*>(x)[src[f]]; };
+    auto fill = [&](uint16_t* tile, int f) INLINE {
+        int p = place[f];
+        asm volatile("" : "+v"(p));
+        *reinterpret_cast<i4*>(tile + 8 * (p & 0x3fff)) = fv[f];
+    };
+
+    // All waves of the CU are in the same phase between two barriers, so what
+    // a wave does outside its products is time without products.  Each tile's
+    // products are therefore taken in PHASES parts, and between them go: the
+    // loads of the next halo (first), the epilogue of the tile before (acc_old,
+    // an accumulator per phase: to LDS where STAGED, else to memory), the
+    // stores of the tile before that one (STAGED), and the next halo's way to
+    // LDS (last).
+    f4 acc[NA], acc_old[NA];                                // [plane][block][row or pair of rows]
+    float gate[NA];                                         // EPI_CLOSURE, of acc_old's cells
+    double sum[4] = { 0, 0, 0, 0 };                         // EPI_CLOSURE: of the lane's 4 channels
+    uint4 mask[CHUNKS], chunk[CHUNKS];
+    long c_fetched = 0, c_now, c_old = 0, c_out = 0;        // first cells: of fv, of acc, of acc_old, staged
+
+    // the cell of the tile that the lane holds of accumulator u
+    auto row = [&](int u) INLINE { return FOLD ? 2 * (u % NB) + (g >> 1) : u % NB; };
+    auto plane_of = [&](int u) INLINE { return wz + u / (NB * MBW); };
+    auto cell = [&](long c0, int u) INLINE { return c0 + r + (long)nx * (row(u) + (long)ny * plane_of(u)); };
+    auto epilogue = [&](int u, uint16_t* st) INLINE {
+        const int m = u / NB % MBW, co0 = channel(m);
+        if (co0 >= COUT) return;
+        const long c = cell(c_old, u);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = acc_old[u][e];
+            if (BIAS) v[e] += bias[m][e];
+            if (EPI == EPI_CLOSURE) {
+                if (A.gate) v[e] *= gate[u];
+                sum[e] += (double)v[e];
+            }
+            if (EPI == EPI_BIAS_RELU) v[e] = fmaxf(v[e], 0.0f);
+        }
+        if (EPI == EPI_MASK && !STAGED) {
+            const uint2 mk = *reinterpret_cast<const uint2*>(A.mask + (size_t)c * COUT + co0);
+            const uint16_t mm[4] = { (uint16_t)(mk.x & 0xffff), (uint16_t)(mk.x >> 16),
+                                     (uint16_t)(mk.y & 0xffff), (uint16_t)(mk.y >> 16) };
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (!(bf2f(mm[e]) > 0.0f)) v[e] = 0.0f;
+        }
+        if (EPI == EPI_BIAS_F32 || EPI == EPI_F32 || EPI == EPI_CLOSURE) {
+            *reinterpret_cast<float4*>(A.yf + (size_t)c * COUT + co0) = make_float4(v[0], v[1], v[2], v[3]);
+        } else {
+            const uint2 w = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+            if constexpr (STAGED) {
+                const int cl = (plane_of(u) * CT_Y + row(u)) * CT_X + r, q = co0 >> 3;
+                *reinterpret_cast<uint2*>(st + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)) + (co0 & 4)) = w;
+            } else {
+                *reinterpret_cast<uint2*>(A.yb + (size_t)c * COUT + co0) = w;
             }
         }
     };
-    auto fill = [&](uint16_t* tile) {
-#pragma unroll
-        for (int f = 0; f < FILL; ++f) {
-            int p = place[f];
-            asm volatile("" : "+v"(p));
-            *reinterpret_cast<uint4*>(tile + 8 * (p & 0x3fff)) = fv[f];
-        }
-    };
-    // products and epilogue of a visit whose halo is in buffer buf; fetched:
-    // the next halo is in registers and goes to the other buffer (last read
-    // before the previous barrier)
-    auto work = [&](int visit, int buf, auto fetched) {
-        const uint16_t* const tile = tiles + buf * S::LDS;
-        int bx, by, bz;
-        conv_tile(visit, tx, tz, bx, by, bz);
-        const long c0 = (long)(bx * CT_X) + (long)nx * ((long)(by * CT_Y) + (long)ny * (bz * S::TZ));
-        float gate[NB];
+    auto load_gate = [&]() INLINE {
         if constexpr (EPI == EPI_CLOSURE)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) gate[nb] = A.gate ? A.gate[c0 + r + (long)nx * (nb + (long)ny * wz)] : 1.0f;
-        f4 acc[MBW][NB];
+            for (int u = 0; u < NA; ++u) gate[u] = A.gate ? A.gate[cell(c_old, u)] : 1.0f;
+    };
+    // STAGED: consecutive threads store consecutive chunks, 1 KiB per wave and row
+    auto staged_cell = [&](int i, int& cl, int& q) INLINE {
+        const int p = threadIdx.x + THREADS * i;
+        cl = p >> 2;
+        q = p & 3;
+        return c_out + cl % CT_X + (long)nx * ((cl / CT_X) % CT_Y + (long)ny * (cl / (CT_X * CT_Y)));
+    };
+    auto load_mask = [&]() INLINE {
+        if constexpr (STAGED && EPI == EPI_MASK)
 #pragma unroll
-        for (int m = 0; m < MBW; ++m)
+            for (int i = 0; i < CHUNKS; ++i) {
+                int cl, q;
+                const long c = staged_cell(i, cl, q);
+                mask[i] = ld16(A.mask + (size_t)c * COUT + 8 * q);
+            }
+    };
+    auto load_staged = [&](const uint16_t* st, int i) INLINE {
+        int cl, q;
+        staged_cell(i, cl, q);
+        return *reinterpret_cast<const uint4*>(st + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)));
+    };
+    auto store_staged = [&](uint4 v, int i) INLINE {
+        int cl, q;
+        const long c = staged_cell(i, cl, q);
+        if constexpr (EPI == EPI_MASK) {
+            v.x = masked2(v.x, mask[i].x); v.y = masked2(v.y, mask[i].y);
+            v.z = masked2(v.z, mask[i].z); v.w = masked2(v.w, mask[i].w);
+        }
+        *reinterpret_cast<uint4*>(A.yb + (size_t)c * COUT + 8 * q) = v;
+    };
+
+    // products of the tile in buffer buf, and what goes between them; old,
+    // out, fetch: there is a tile before, one before that, one to load
+    auto work = [&](int buf, auto old, auto out, auto fetch) INLINE {
+        constexpr bool FETCH = decltype(fetch)::value;
+        const uint16_t* const tile = tiles + buf * S::LDS;
+        long c_next = 0;
+        auto between_products = [&](int k) INLINE {
+            constexpr int ROW0 = EPI == EPI_CLOSURE ? 5 : 1;        // later where the gate is loaded first
+            constexpr int STORE = CIN == 32 ? 2 : 1, FILLS = AHEAD == 2 ? 1 : CIN == 32 ? 2 : FILL;
+            if (k == 0) {
+                if (STAGED && out) load_mask();
+                if (old) load_gate();
+                if constexpr (FETCH) c_next = aim(at);
+            }
+            if constexpr (FETCH && AHEAD == 1)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[m][nb] = f4{ 0.f, 0.f, 0.f, 0.f };
+                for (int f = 0; f < FILL; ++f)
+                    if (k == f / FILLS) load(f);
+            if (k >= ROW0 && k < ROW0 + NA)
+                if (old) epilogue(k - ROW0, stage + (buf ^ 1) * OUT);
+            if (STAGED && out)
+#pragma unroll
+                for (int i = 0; i < CHUNKS; ++i) {
+                    if (k == STORE + 2 * i) chunk[i] = load_staged(stage + buf * OUT, i);
+                    if (k == STORE + 2 * i + 1) store_staged(chunk[i], i);
+                }
+            if constexpr (FETCH)
+#pragma unroll
+                for (int f = 0; f < FILL; ++f)
+                    if (k == S::PHASES - (FILL + FILLS - 1) / FILLS + f / FILLS) {
+                        fill(tiles + (buf ^ 1) * S::LDS, f);
+                        if constexpr (AHEAD == 2) load(f);
+                    }
+        };
+#pragma unroll
+        for (int u = 0; u < NA; ++u) acc[u] = f4{ 0.f, 0.f, 0.f, 0.f };
         if constexpr (CIN == 32) {
             // one offset per K step.  Read offset by offset, every row of the
             // halo would be read from LDS nine times (3 dy, 3 dx), twice the
@@ -310,31 +478,31 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
                 leftp[p] = plane + r * CIN + 8 * conv_chunk<CIN>(4 * p + r, g);
                 rightp[p] = plane + (r + 2) * CIN + 8 * conv_chunk<CIN>(4 * p + r + 2, g);
             }
-            auto ld_row = [&](const uint16_t* const (&base)[2], int k) {    // row k of the wave's three planes
+            auto ld_row = [&](const uint16_t* const (&base)[2], int k) INLINE {    // row k of the wave's three planes
                 return as_bf8(*reinterpret_cast<const uint4*>(base[k & 1] + k * (CL_X * CIN)));
             };
             bf16x8 left = ld_row(leftp, 0), right = ld_row(rightp, 0);
 #pragma unroll
-            for (int k = 0; k < 3 * CH_Y; ++k) {
-                const int dz = k / CH_Y, row = k % CH_Y;
+            for (int k = 0; k < S::PHASES; ++k) {
+                const int p = k / CH_Y, in = k % CH_Y;
                 bf16x8 left1 = left, right1 = right;
-                if (k + 1 < 3 * CH_Y) {                     // the next row, ahead of this one's products
+                if (k + 1 < S::PHASES) {                    // the next row, ahead of this one's products
                     left1 = ld_row(leftp, k + 1);
                     right1 = ld_row(rightp, k + 1);
+                    __builtin_amdgcn_sched_barrier(0);      // (the scheduler would move them behind)
                 }
                 const bf16x8 b[3] = { left, between(left, right), right };
                 // dx outside: consecutive products go to different accumulators
 #pragma unroll
                 for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-                    for (int dy = 0; dy < 3; ++dy) {
-                        const int nb = row - dy;
-                        if (nb < 0 || nb >= NB) continue;
-#pragma unroll
-                        for (int m = 0; m < MBW; ++m)
-                            acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[dz * 9 + dy * 3 + dx][m], b[dx],
-                                                                                 acc[m][nb], 0, 0, 0);
+                    for (int u = 0; u < NA; ++u) {
+                        const int dz = p - u / (NB * MBW), m = u / NB % MBW;
+                        const int j = in - (FOLD ? 2 : 1) * (u % NB);       // dy, or the pair's input row
+                        if (dz < 0 || dz > 2 || j < 0 || j > (FOLD ? 3 : 2)) continue;
+                        acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[(dz * (FOLD ? 4 : 3) + j) * 3 + dx][m], b[dx], acc[u], 0, 0, 0);
                     }
+                between_products(k);
                 left = left1;
                 right = right1;
                 __builtin_amdgcn_sched_barrier(0);
@@ -342,7 +510,7 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
         } else {
             // 4 offsets per K step, one per K chunk g (offset 27 is padding)
             const int hbase = (wz + 1) * (CL_X * CH_Y) + CL_X + (r + 1);
-            auto load_b = [&](int s, bf16x8* bv) {
+            auto load_b = [&](int s, bf16x8* bv) INLINE {
                 const int of = 4 * s + g;
                 const int dx = of % 3 - 1, dy = (of / 3) % 3 - 1, dz = of / 9 - 1;
                 const int h0 = hbase + dz * (CL_X * CH_Y) + dy * CL_X + dx;
@@ -360,103 +528,109 @@ __global__ void __launch_bounds__(CONV_THREADS, 2) conv3d_kernel(ConvArgs A)
                 bf16x8 b_nxt[NB];
                 if (s + 1 < KS) load_b(s + 1, b_nxt);
 #pragma unroll
-                for (int m = 0; m < MBW; ++m)
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[m][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s][m], b_cur[nb], acc[m][nb], 0, 0, 0);
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s][0], b_cur[nb], acc[nb], 0, 0, 0);
+                between_products(s);
                 if (s + 1 < KS)
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) b_cur[nb] = b_nxt[nb];
             }
         }
-
-        // epilogue: lane holds channels co = 16 (m0 + m) + 4 g + e of cell
-        // (x0 + r, y0 + nb, z0 + wz)
+        __syncthreads();
 #pragma unroll
-        for (int m = 0; m < MBW; ++m) {
-            const int co0 = 16 * (m0 + m) + 4 * g;
-            if (co0 >= COUT) continue;
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const long c = c0 + r + (long)nx * (nb + (long)ny * wz);
-                float v[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    v[e] = acc[m][nb][e];
-                    if (EPI == EPI_BIAS_RELU || EPI == EPI_BIAS_F32 || EPI == EPI_CLOSURE) v[e] += bias[m][e];
-                    if (EPI == EPI_CLOSURE) {
-                        if (A.gate) v[e] *= gate[nb];
-                        sum[e] += (double)v[e];
-                    }
-                    if (EPI == EPI_BIAS_RELU) v[e] = fmaxf(v[e], 0.0f);
-                }
-                if (EPI == EPI_MASK && !STAGED) {
-                    const uint2 mk = *reinterpret_cast<const uint2*>(A.mask + (size_t)c * COUT + co0);
-                    const uint16_t mm[4] = { (uint16_t)(mk.x & 0xffff), (uint16_t)(mk.x >> 16),
-                                             (uint16_t)(mk.y & 0xffff), (uint16_t)(mk.y >> 16) };
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (!(bf2f(mm[e]) > 0.0f)) v[e] = 0.0f;
-                }
-                if (EPI == EPI_BIAS_F32 || EPI == EPI_F32 || EPI == EPI_CLOSURE) {
-                    *reinterpret_cast<float4*>(A.yf + (size_t)c * COUT + co0) = make_float4(v[0], v[1], v[2], v[3]);
-                } else {
-                    const uint2 w = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
-                    if constexpr (STAGED) {
-                        const int cl = (wz * CT_Y + nb) * CT_X + r, q = co0 >> 3;
-                        *reinterpret_cast<uint2*>(stage + buf * OUT + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)) + (co0 & 4)) = w;
-                    } else {
-                        *reinterpret_cast<uint2*>(A.yb + (size_t)c * COUT + co0) = w;
-                    }
-                }
-            }
-        }
-        if constexpr (decltype(fetched)::value) fill(tiles + (buf ^ 1) * S::LDS);
-        if constexpr (STAGED || decltype(fetched)::value) __syncthreads();
-        if constexpr (STAGED) {
-            // consecutive threads store consecutive chunks: 1 KiB per wave and row
-            constexpr int CHUNKS = OUT / 8 / CONV_THREADS;
-#pragma unroll
-            for (int i = 0; i < CHUNKS; ++i) {
-                const int p = threadIdx.x + CONV_THREADS * i;
-                const int cl = p >> 2, q = p & 3;
-                uint4 v = *reinterpret_cast<const uint4*>(stage + buf * OUT + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)));
-                const long c = c0 + cl % CT_X + (long)nx * ((cl / CT_X) % CT_Y + (long)ny * (cl / (CT_X * CT_Y)));
-                if constexpr (EPI == EPI_MASK) {
-                    const uint4 mk = ld16(A.mask + (size_t)c * COUT + 8 * q);
-                    v.x = masked2(v.x, mk.x); v.y = masked2(v.y, mk.y);
-                    v.z = masked2(v.z, mk.z); v.w = masked2(v.w, mk.w);
-                }
-                *reinterpret_cast<uint4*>(A.yb + (size_t)c * COUT + 8 * q) = v;
-            }
-        }
+        for (int u = 0; u < NA; ++u) acc_old[u] = acc[u];
+        c_out = c_old;
+        c_old = c_now;
+        c_now = AHEAD == 2 ? c_fetched : c_next;
+        c_fetched = c_next;
     };
-    fetch(o);
-    fill(tiles);
-    __syncthreads();
-    int buf = 0;
-    for (; o + stride < end; o += stride, buf ^= 1) {
-        fetch(o + stride);
-        work(o, buf, std::true_type());
+    // the visit loaded next, AHEAD of o: the last one again at the end (unused)
+    auto advance = [&](int ahead) INLINE {
+        if (o + ahead * stride < end) at = conv_next(at, hop, tx, tz);
+    };
+    c_now = aim(at);
+#pragma unroll
+    for (int u = 0; u < NA; ++u) acc_old[u] = f4{ 0.f, 0.f, 0.f, 0.f };
+#pragma unroll
+    for (int f = 0; f < FILL; ++f) load(f);
+    // waited for here: in the loop the wait would take in the halo loads that
+    // are to stay in flight over the products
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int m = 0; m < MBW; ++m) asm volatile("" : "+v"(a[s][m]));
+#pragma unroll
+    for (int m = 0; m < MBW; ++m)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(bias[m][e]));
+    if constexpr (AHEAD == 2) {
+        advance(1);
+        c_fetched = aim(at);
     }
-    work(o, buf, std::false_type());
+#pragma unroll
+    for (int f = 0; f < FILL; ++f) {
+        fill(tiles, f);
+        if constexpr (AHEAD == 2) load(f);
+    }
+    __syncthreads();
+    advance(AHEAD);
+    // the first tiles have none before them to store (the epilogue of a STAGED
+    // one that is not there goes to LDS, where nobody reads it), the last one
+    // none after it to load
+    constexpr int FIRST = STAGED ? 2 : 1;
+    int buf = 0, done = 0;
+    auto next = [&]() INLINE {
+        ++done;
+        buf ^= 1;
+        o += stride;
+        advance(AHEAD);
+    };
+#pragma unroll 1
+    while (done < FIRST && o + stride < end) {
+        work(buf, std::bool_constant<STAGED>(), std::false_type(), std::true_type());
+        next();
+    }
+#pragma unroll 1
+    while (o + stride < end) {
+        work(buf, std::true_type(), std::true_type(), std::true_type());
+        next();
+    }
+    work(buf, done > 0, done > 1, std::false_type());
+    ++done;
+    if constexpr (STAGED)
+        if (done > 1) {                                     // the last tile but one
+            load_mask();
+#pragma unroll
+            for (int i = 0; i < CHUNKS; ++i) store_staged(load_staged(stage + (buf ^ 1) * OUT, i), i);
+        }
+    load_gate();
+#pragma unroll
+    for (int u = 0; u < NA; ++u) epilogue(u, stage + buf * OUT);
+    if constexpr (STAGED) {
+        __syncthreads();
+        c_out = c_old;
+        load_mask();
+#pragma unroll
+        for (int i = 0; i < CHUNKS; ++i) store_staged(load_staged(stage + buf * OUT, i), i);
+    }
     if constexpr (EPI == EPI_CLOSURE) {
         // the workgroup's channel sums: 16 lanes of a channel, then the waves
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int st = 8; st > 0; st >>= 1) sum[e] += __shfl_xor(sum[e], st, 64);
+            for (int st = FOLD ? 32 : 8; st > 0; st >>= st == 32 ? 2 : 1) sum[e] += __shfl_xor(sum[e], st, 64);
         if (r == 0 && g < 2)
 #pragma unroll
             for (int e = 0; e < 4; ++e) wave_sum[wave][4 * g + e] = sum[e];
         __syncthreads();
         if (threadIdx.x < 8) {
             double v = 0.0;
-            for (int w = 0; w < CONV_WAVES; ++w) v += wave_sum[w][threadIdx.x];
+            for (int w = 0; w < S::WAVES; ++w) v += wave_sum[w][threadIdx.x];
             A.sums[(size_t)blockIdx.x * 8 + threadIdx.x] = v;
         }
     }
 }
+#undef INLINE
 
 // one workgroup per CU, or one per tile: multiples of 8
 template <int CIN, int COUT>
@@ -467,24 +641,31 @@ static int conv_grid(const int n[3])
 }
 int closure_sum_blocks(const int n[3]) { return conv_grid<32, 8>(n); }
 
+template <int CIN, int COUT, int EPI>
+static hipError_t conv_launch(const ConvArgs& A, hipStream_t s)
+{
+    using S = ConvShape<CIN, COUT>;
+    const dim3 grid((unsigned)conv_grid<CIN, COUT>(A.n)), block(S::THREADS);
+    const unsigned long long pieces = (unsigned long long)S::PARTS * A.n[0] * A.n[1] * A.n[2];
+    // offsets in 32 bits up to 2^30 cells of 32 channels (64 GiB)
+    if (pieces < 1ull << 32) hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI, unsigned>), grid, block, 0, s, A);
+    else hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI, unsigned long long>), grid, block, 0, s, A);
+    return hipGetLastError();
+}
+
 template <int CIN, int COUT>
 static hipError_t conv_dispatch_epi(const ConvArgs& A, int epi, hipStream_t s)
 {
-    const unsigned grid = (unsigned)conv_grid<CIN, COUT>(A.n);
     switch (epi) {
-    case EPI_BIAS_RELU: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_RELU>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
-    case EPI_BIAS_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_BIAS_F32>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
-    case EPI_MASK: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_MASK>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
-    case EPI_F32: hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_F32>), dim3(grid), dim3(CONV_THREADS), 0, s, A); break;
+    case EPI_BIAS_RELU: return conv_launch<CIN, COUT, EPI_BIAS_RELU>(A, s);
+    case EPI_BIAS_F32: return conv_launch<CIN, COUT, EPI_BIAS_F32>(A, s);
+    case EPI_MASK: return conv_launch<CIN, COUT, EPI_MASK>(A, s);
+    case EPI_F32: return conv_launch<CIN, COUT, EPI_F32>(A, s);
     case EPI_CLOSURE:
-        if constexpr (CIN == 32 && COUT == 8) {
-            hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI_CLOSURE>), dim3(grid), dim3(CONV_THREADS), 0, s, A);
-            break;
-        }
+        if constexpr (CIN == 32 && COUT == 8) return conv_launch<CIN, COUT, EPI_CLOSURE>(A, s);
         return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_conv3d(const ConvArgs& A, int cin, int cout, int epi, hipStream_t s)
