@@ -181,7 +181,12 @@ int mhd_step(mhd_ctx *h, double dt);
 /* CFL and full step with dt = cfl h / vmax kept on the device (no host
  * synchronisation; the form a HIP graph can capture).  A non-physical state
  * is recorded on the device and reported by the next mhd_status call (the
- * step then leaves the state unchanged). */
+ * step then leaves the state unchanged).
+ * A captured graph reads and writes the buffers that its calls used, so it
+ * can be replayed if it leaves every field where it found it.  One captured
+ * step does, except where mhd_get_launch reports MHD_TUNE_MIDDLE 1 (the
+ * middle in one launch, built in from 128^3 cells in FP32): there capture an
+ * even number of steps, or set MHD_TUNE_MIDDLE to 2. */
 int mhd_step_auto(mhd_ctx *h, double cfl);
 
 /* Synchronise the handle's stream; report a non-physical state recorded by

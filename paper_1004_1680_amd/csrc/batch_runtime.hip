@@ -70,6 +70,7 @@ struct mhd_batch {
     bool graph_valid;
     int graph_steps;        // steps in the captured graph (1, or 2 with the fused middle)
     int graph_bpar;         // buffer of the face fields when the graph starts
+    bool capturing;         // mhd_batch_run captures its graph
     bool failed;
 };
 
@@ -239,7 +240,7 @@ extern "C" mhd_batch* mhd_batch_create(int nbox, const int* dims, double gamma, 
     b->d_cfl_items = nullptr; b->d_item_first = nullptr;
     b->partial = nullptr; b->partial_bad = nullptr;
     b->graph = nullptr; b->exec = nullptr; b->graph_valid = false;
-    b->graph_steps = 1; b->graph_bpar = 0;
+    b->graph_steps = 1; b->graph_bpar = 0; b->capturing = false;
     b->failed = false;
     for (int q = 0; q < 8; ++q) b->cur[q] = 0;
     if (hipGetDevice(&b->device) != hipSuccess) {
@@ -437,7 +438,9 @@ static bool batch_mid_fused(const mhd_batch* b)
 // box runs the pairs in tiles and the choice is the library's, the pairs, and
 // in FP32 with van Leer's limiter the middle, are one launch each (the
 // launches of a step flip the fields' buffers, so one choice holds for all
-// boxes)
+// boxes).  A caller's capture of steps keeps the middle in two launches
+// unless its report says one: every field then ends a step in the buffer it
+// started in, and a captured single step can be replayed.
 static bool run_pairs_fused(const mhd_batch* b)
 {
     return batch_pairs_fused(b) || (b->rev_mode == 0 && all_tiles(b, 1) && all_tiles(b, 2));
@@ -445,7 +448,7 @@ static bool run_pairs_fused(const mhd_batch* b)
 static bool run_mid_fused(const mhd_batch* b)
 {
     if (batch_mid_fused(b)) return true;
-    return b->mid_mode == 0 && batch_pairs_fused(b) && b->prec == MHD_F32 && b->limiter == MHD_LIMITER_VANLEER &&
+    return b->mid_mode == 0 && (b->capturing || !mhd_capture_id(b->stream)) && batch_pairs_fused(b) && b->prec == MHD_F32 && b->limiter == MHD_LIMITER_VANLEER &&
            all_tiles(b, 2);
 }
 
@@ -556,8 +559,10 @@ extern "C" int mhd_batch_run(mhd_batch* b, double cfl, int nsteps, int use_graph
     if (!b->graph_valid) {
         const int bpar = b->cur[5];
         HIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+        b->capturing = true;
         r = enqueue_step(b, cfl);
         if (!r && gs == 2) r = enqueue_step(b, cfl);
+        b->capturing = false;
         hipGraph_t g = nullptr;
         const hipError_t e = hipStreamEndCapture(b->stream, &g);
         if (r) {

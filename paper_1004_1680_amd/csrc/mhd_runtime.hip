@@ -722,11 +722,15 @@ static bool mid_fused(const mhd_ctx* h)
 
 // the same with the tile kernels counted: where the library chooses and they
 // run the z axis, the middle is one launch at any size (16^3: 7.4 us against
-// 4.7 + 6.6 for M_z and the pair, 128^3: 46.6 against 17.8 + 33)
+// 4.7 + 6.6 for M_z and the pair, 128^3: 46.6 against 17.8 + 33).  Not while
+// a graph is captured: with the middle in one launch a step writes the faces
+// five times and leaves them in the other buffer, so a captured single step
+// could not be replayed; with two launches it can, on the grids below 128^3
+// whose choice this is.
 static bool mid_one_launch(const mhd_ctx* h)
 {
     if (mid_fused(h)) return true;
-    return h->mid_mode == 0 && pairs_fused(h) && h->limiter == MHD_LIMITER_VANLEER && h->prec == MHD_F32 &&
+    return h->mid_mode == 0 && !mhd_capture_id(h->stream) && pairs_fused(h) && h->limiter == MHD_LIMITER_VANLEER && h->prec == MHD_F32 &&
            tiles(h, 3, 2);
 }
 

@@ -15,6 +15,16 @@ int mhd_fail(int code, const char* fmt, ...);
         }                                                                              \
     } while (0)
 
+// The graph capture that records what is enqueued on the stream, 0 for none
+// (the legacy default stream takes part in none).
+inline unsigned long long mhd_capture_id(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    if (!s || hipStreamGetCaptureInfo(s, &status, &id) != hipSuccess) return 0;
+    return status == hipStreamCaptureStatusActive ? id : 0;
+}
+
 // Internal accessors of a single-grid handle (used by the closure runtime).
 struct mhd_ctx;
 // the buffers ([8][cell]) that hold the fluid fields (0 - 4) and the faces (5 - 7), and the first one
