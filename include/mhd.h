@@ -84,7 +84,10 @@ mhd_ctx *mhd_create(int nx, int ny, int nz, double gamma);
  * changes from operator to operator).  Violations of these conditions that
  * the runtime can see (one buffer NULL, host or managed memory, another
  * device, misalignment, an allocation too short, overlap) give NULL with
- * MHD_EINVAL in mhd_last_error.  The stream must outlive the handle. */
+ * MHD_EINVAL in mhd_last_error.  The stream must outlive the handle.
+ * Handles of FP32 grids below 128^3 cells keep one more copy of the faces (12
+ * bytes per cell, the library's in either case) where the tile kernels run
+ * the middle of a step (mhd_set_launch). */
 mhd_ctx *mhd_create_ex(int nx, int ny, int nz, double gamma, int prec,
                        void *hip_stream, void *dev_buf_a, void *dev_buf_b);
 

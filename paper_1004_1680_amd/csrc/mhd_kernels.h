@@ -11,6 +11,9 @@ enum { SCAL_DT = 0, SCAL_C = 1, SCAL_TIME = 2, SCAL_VMAX = 3, SCAL_COUNT = 4 };
 // Device flag block: [0] non-physical state recorded by the device-side
 // CFL of mhd_step_auto, [1] number of such steps that ran.
 enum { FLAG_NONPHYS = 0, FLAG_STEPS = 1, FLAG_COUNT = 4 };
+// cells (of a box on average) from which the march kernels run the middle of
+// a step in one launch where the choice is the library's
+constexpr size_t MID_CELLS = (size_t)128 * 128 * 128;
 constexpr int CFL_ACC_SLOTS = 256;     // fused-CFL maximum slots (+1 word for the flag)
 
 template <typename T>

@@ -4,7 +4,8 @@
 // Buffers.  Each handle owns two device allocations of 8 fields each.  Every
 // operator reads the current copy of its inputs and writes the other copy
 // of the fields it changes (never in place: neighbour pencils of one lane are
-// another lane's output), then the per-field "current" index flips.
+// another lane's output), then the per-field "current" index flips.  Handles
+// of small FP32 grids have a third copy of the faces (mid_aside).
 //
 // Time step on the device.  Kernels read dt and the relaxation speed from a
 // small device block; the host path writes it with a one-thread kernel
@@ -51,6 +52,11 @@ struct mhd_ctx {
     void* buf[2];
     bool own_buf;           // buf[] allocated here (false: the caller's, never freed here)
     int cur[8];
+    // a third place for the faces, which the one-launch middle of small grids
+    // writes (mid_aside; null: no such grid), and whether they are there now
+    // instead of in buf[cur]
+    void* aside;
+    bool in_aside;
     double* scal;           // device SCAL_COUNT doubles
     int* flag;              // device FLAG_COUNT ints
     double* partial;        // reduction partials (max of cfl and diag needs)
@@ -98,9 +104,21 @@ static T* field_ptr(mhd_ctx* h, int f, int which)
 }
 
 template <typename T>
+static T* aside_ptr(mhd_ctx* h, int f)
+{
+    return reinterpret_cast<T*>(h->aside) + (size_t)(f - 5) * h->N;
+}
+
+template <typename T>
+static T* current_ptr(mhd_ctx* h, int f)
+{
+    return f >= 5 && h->in_aside ? aside_ptr<T>(h, f) : field_ptr<T>(h, f, h->cur[f]);
+}
+
+template <typename T>
 static void current_fields(mhd_ctx* h, const T* f[8])
 {
-    for (int q = 0; q < 8; ++q) f[q] = field_ptr<T>(h, q, h->cur[q]);
+    for (int q = 0; q < 8; ++q) f[q] = current_ptr<T>(h, q);
 }
 
 // Built-in march chunk of a pencil of nd cells: the divisor (>= 8) with the
@@ -286,6 +304,12 @@ extern "C" mhd_ctx* mhd_create_ex(int nx, int ny, int nz, double gamma, int prec
     default_tuning(h);
     h->rev_mode = 0;
     h->acc_valid = false;
+    // (12 bytes a cell below 128^3 cells; without it the middle is two launches)
+    if (prec == MHD_F32 && h->N < MID_CELLS && sweep_uses_tiles<float>(h->n, 3, 2, h->tune) &&
+        hipMalloc(&h->aside, 3 * h->N * h->esize) != hipSuccess) {
+        (void)hipGetLastError();
+        h->aside = nullptr;
+    }
     return h;
 }
 
@@ -302,6 +326,7 @@ extern "C" void mhd_destroy(mhd_ctx* h)
         if (h->buf[0]) (void)hipFree(h->buf[0]);
         if (h->buf[1]) (void)hipFree(h->buf[1]);
     }
+    if (h->aside) (void)hipFree(h->aside);
     if (h->scal) (void)hipFree(h->scal);
     if (h->flag) (void)hipFree(h->flag);
     if (h->partial) (void)hipFree(h->partial);
@@ -327,6 +352,7 @@ static int reset_after_set(mhd_ctx* h)
 {
     h->acc_valid = false;
     for (int q = 0; q < 8; ++q) h->cur[q] = 0;
+    h->in_aside = false;
     h->have_c = false;
     h->c_host = 0.0;
     h->scal_known = false;
@@ -377,7 +403,7 @@ extern "C" int mhd_get_state(mhd_ctx* h, double* host, size_t n)
     HIP_TRY(h, hipSetDevice(h->device));
     if (h->prec == MHD_F64) {
         for (int q = 0; q < 8; ++q)
-            HIP_TRY(h, hipMemcpyAsync(host + (size_t)q * h->N, field_ptr<double>(h, q, h->cur[q]),
+            HIP_TRY(h, hipMemcpyAsync(host + (size_t)q * h->N, current_ptr<double>(h, q),
                                       h->N * sizeof(double), hipMemcpyDeviceToHost, h->stream));
         return sync_stream(h);
     }
@@ -387,7 +413,7 @@ extern "C" int mhd_get_state(mhd_ctx* h, double* host, size_t n)
         return fail(MHD_ENOMEM, "staging allocation failed");
     }
     for (int q = 0; q < 8 && !r; ++q) {
-        if (launch_convert_out<float>(field_ptr<float>(h, q, h->cur[q]), stage, h->N, h->stream) !=
+        if (launch_convert_out<float>(current_ptr<float>(h, q), stage, h->N, h->stream) !=
                 hipSuccess ||
             hipMemcpyAsync(host + (size_t)q * h->N, stage, h->N * sizeof(double),
                            hipMemcpyDeviceToHost, h->stream) != hipSuccess)
@@ -432,20 +458,20 @@ extern "C" int mhd_get_state_device(mhd_ctx* h, void* dst, size_t n, int prec)
     if (prec != MHD_F32 && prec != MHD_F64) return fail(MHD_EINVAL, "bad precision %d", prec);
     HIP_TRY(h, hipSetDevice(h->device));
     const size_t es = prec == MHD_F64 ? sizeof(double) : sizeof(float);
-    // one copy (or conversion) for each run of fields that share a buffer
+    // one copy (or conversion) for each run of fields that lie one after another
+    auto at = [&](int q) {
+        return h->prec == MHD_F64 ? (char*)current_ptr<double>(h, q) : (char*)current_ptr<float>(h, q);
+    };
     for (int q = 0, m; q < 8; q += m) {
-        for (m = 1; q + m < 8 && h->cur[q + m] == h->cur[q]; ++m) {}
+        for (m = 1; q + m < 8 && at(q + m) == at(q) + m * h->N * h->esize; ++m) {}
         char* d = (char*)dst + (size_t)q * h->N * es;
         hipError_t e;
         if (prec == h->prec)
-            e = hipMemcpyAsync(d, (char*)h->buf[h->cur[q]] + (size_t)q * h->N * h->esize,
-                               m * h->N * es, hipMemcpyDeviceToDevice, h->stream);
+            e = hipMemcpyAsync(d, at(q), m * h->N * es, hipMemcpyDeviceToDevice, h->stream);
         else if (prec == MHD_F64)
-            e = launch_cast<float, double>(field_ptr<float>(h, q, h->cur[q]), (double*)d, m * h->N,
-                                           h->stream);
+            e = launch_cast<float, double>((const float*)at(q), (double*)d, m * h->N, h->stream);
         else
-            e = launch_cast<double, float>(field_ptr<double>(h, q, h->cur[q]), (float*)d, m * h->N,
-                                           h->stream);
+            e = launch_cast<double, float>((const double*)at(q), (float*)d, m * h->N, h->stream);
         HIP_TRY(h, e);
     }
     return MHD_OK;
@@ -534,16 +560,23 @@ extern "C" int mhd_get_relaxation_speed(const mhd_ctx* hc, double* c)
 // operators
 // ---------------------------------------------------------------------------
 
+static bool mid_aside(const mhd_ctx* h);
+
 // op 0 = fluid, 1 = magnetic, 2 = magnetic then fluid in one launch, 3 =
 // magnetic twice then fluid in one launch; flag (nullable): skip-and-copy
 // switch
 template <typename T>
 static hipError_t enqueue_op(mhd_ctx* h, int op, int d, const int* flag, unsigned long long* acc)
 {
+    // the faces of a middle that stands for two launches stay where those two
+    // would leave them, or aside where that is what it reads
+    const bool twice = op == 3 && mid_aside(h);
     SweepParams<T> P;
     for (int q = 0; q < 8; ++q) {
-        P.in[q] = field_ptr<T>(h, q, h->cur[q]);
-        P.out[q] = field_ptr<T>(h, q, 1 - h->cur[q]);
+        P.in[q] = current_ptr<T>(h, q);
+        P.out[q] = q < 5 || !twice ? field_ptr<T>(h, q, 1 - h->cur[q])
+                   : h->in_aside   ? field_ptr<T>(h, q, h->cur[q])
+                                   : aside_ptr<T>(h, q);
     }
     P.nx = h->n[0]; P.ny = h->n[1]; P.nz = h->n[2];
     P.gamma = (T)h->gamma;
@@ -560,8 +593,11 @@ static hipError_t enqueue_op(mhd_ctx* h, int op, int d, const int* flag, unsigne
     if (e == hipSuccess) {
         if (op != 1)
             for (int q = 0; q < 5; ++q) h->cur[q] = 1 - h->cur[q];
-        if (op != 0)
-            for (int q = 5; q < 8; ++q) h->cur[q] = 1 - h->cur[q];
+        if (op != 0) {
+            if (!twice)
+                for (int q = 5; q < 8; ++q) h->cur[q] = 1 - h->cur[q];
+            h->in_aside = twice && !h->in_aside;
+        }
     }
     return e;
 }
@@ -716,22 +752,24 @@ extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
 static bool mid_fused(const mhd_ctx* h)
 {
     if (!pairs_fused(h) || h->limiter != MHD_LIMITER_VANLEER || h->prec != MHD_F32) return false;
-    if (h->mid_mode == 0) return (long)h->n[0] * h->n[1] * h->n[2] >= 128L * 128 * 128;
+    if (h->mid_mode == 0) return h->N >= MID_CELLS;
     return h->mid_mode == 1;
 }
 
 // the same with the tile kernels counted: where the library chooses and they
-// run the z axis, the middle is one launch at any size (16^3: 7.4 us against
-// 4.7 + 6.6 for M_z and the pair, 128^3: 46.6 against 17.8 + 33).  Not while
-// a graph is captured: with the middle in one launch a step writes the faces
-// five times and leaves them in the other buffer, so a captured single step
-// could not be replayed; with two launches it can, on the grids below 128^3
-// whose choice this is.
+// run the z axis, the middle is one launch on smaller grids too (16^3: 7.4 us
+// against 4.7 + 6.6 for M_z and the pair).  A step on such a grid has always
+// left every field in the buffer it started in, which a caller's captured
+// step, replayed on its own buffers, relies on; one launch in place of two
+// would leave the faces in the other one.  So it writes them to a third place,
+// from where the next launch that writes them goes on as after the two.
+static bool mid_aside(const mhd_ctx* h)
+{
+    return h->aside && h->mid_mode == 0 && pairs_fused(h) && h->limiter == MHD_LIMITER_VANLEER && tiles(h, 3, 2);
+}
 static bool mid_one_launch(const mhd_ctx* h)
 {
-    if (mid_fused(h)) return true;
-    return h->mid_mode == 0 && !mhd_capture_id(h->stream) && pairs_fused(h) && h->limiter == MHD_LIMITER_VANLEER && h->prec == MHD_F32 &&
-           tiles(h, 3, 2);
+    return mid_fused(h) || mid_aside(h);
 }
 
 // the 12 operators of a full step: x, y, z forward (fluid, magnetic), then
@@ -1021,6 +1059,7 @@ hipStream_t mhd_internal_stream(const mhd_ctx* h) { return h->stream; }
 void mhd_internal_state_changed(mhd_ctx* h)
 {
     for (int q = 0; q < 8; ++q) h->cur[q] = 0;
+    h->in_aside = false;
     h->acc_valid = false;
 }
 

@@ -1,7 +1,6 @@
 """Steps captured in a caller's HIP graph: every replay, with eager work
 between the replays, is the eager step bit for bit, also on grids whose
-eager steps run their middle in one launch (which moves the faces to the
-other buffer)."""
+steps run their middle in one launch (five writes of the faces a step)."""
 import sys
 
 import numpy as np
@@ -61,8 +60,45 @@ def test_captured_steps(env, n, prec, lim, times, host_dt):
             step(E)
         assert np.array_equal(S.get_state(), E.get_state()), k
         assert S.time() == E.time()
+        for X in (S, E):                          # the handle's own steps in between
+            for _ in range(times):
+                step(X)
+    if times == 1 and not host_dt:                # and another state, after an odd number of them
+        for X in (S, E):
+            X.set_state(smooth_state(n, seed=80))
+            step(X)
+        replay(torch, side, graph)
+        step(E)
+        assert np.array_equal(S.get_state(), E.get_state())
     S.close()
     E.close()
+
+
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+def test_operators_around_the_middle(env, prec):
+    """The middle of a step in one launch and in two, in turn and repeated,
+    between other operators: the same fields, read back at every point by the
+    host and into a tensor."""
+    torch, M, side = env
+    n = (20, 12, 36)
+    say(f"case: operators around the middle {prec}")
+    runs = []
+    for mode in (0, 2):
+        S = M.Solver(n, prec=prec)
+        S.set_launch(M.MHD_TUNE_MIDDLE, mode)
+        S.set_state(smooth_state(n, seed=85))
+        dt = 0.3 * S.cfl_dt(0.5)
+        got = []
+        for code in (7, 7, 7, 0, 7, 4, 3, 7, 6, 1, 7):
+            S.sweep(code, dt)
+            if len(got) == 2:
+                S.magnetic(1, dt)
+            got.append((S.get_state(), S.get_state_tensor(dtype=torch.float64).cpu().numpy()))
+            assert np.array_equal(*got[-1])
+        runs.append(got)
+        S.close()
+    for k, (a, b) in enumerate(zip(*runs)):
+        assert np.array_equal(a[0], b[0]), k
 
 
 @pytest.mark.parametrize("prec", ["f32", "f64"])
@@ -81,5 +117,7 @@ def test_captured_ensemble_step(env, prec):
         E.step_auto(0.5)
         for i in range(len(dims)):
             assert np.array_equal(C.get_state(i), E.get_state(i)), (k, i)
+        C.step_auto(0.5)
+        E.run(1, 0.5, graph=k > 0)
     C.close()
     E.close()
