@@ -68,9 +68,13 @@ struct mhd_ctx {
     bool scal_known;        // host knows what dt / c the device block holds
     // fused CFL: the last fluid operator of a step leaves the FP64 maximum
     // signal speed of the new state in cfl_acc; acc_valid while the state
-    // is still the one it describes
+    // is still the one it describes.  acc_capture: the graph capture that
+    // recorded that launch (0: it was enqueued to run); captured: some call
+    // that changes the state was ever recorded instead of run
     unsigned long long* cfl_acc;
     bool acc_valid;
+    unsigned long long acc_capture;
+    bool captured;
     // reverse-half pairs M_d F_d: one fused launch each (true) or the two
     // operators in turn; same result bit for bit
     int rev_mode;           // 0 built-in choice, 1 fused, 2 the two operators
@@ -348,9 +352,34 @@ extern "C" int mhd_info(const mhd_ctx* h, int dims[3], int* prec)
 // state transfer
 // ---------------------------------------------------------------------------
 
-static int reset_after_set(mhd_ctx* h)
+// a call that changes the state begins: what cfl_acc holds is void
+static void state_changes(mhd_ctx* h)
 {
     h->acc_valid = false;
+    if (mhd_capture_id(h->stream)) h->captured = true;
+}
+
+// the last launch enqueued leaves the maximum of the new state in cfl_acc
+static void maximum_follows(mhd_ctx* h)
+{
+    h->acc_valid = true;
+    h->acc_capture = mhd_capture_id(h->stream);
+}
+
+// cfl_acc will hold the maximum of the state that the next launch finds.
+// Within one capture it is what the launch recorded before leaves; a capture
+// takes nothing from before it, as each replay finds another state; and once
+// anything has been captured the host does not know what was replayed since.
+static bool maximum_holds(const mhd_ctx* h)
+{
+    if (!h->acc_valid) return false;
+    const unsigned long long id = mhd_capture_id(h->stream);
+    return id ? id == h->acc_capture : !h->captured;
+}
+
+static int reset_after_set(mhd_ctx* h)
+{
+    state_changes(h);
     for (int q = 0; q < 8; ++q) h->cur[q] = 0;
     h->in_aside = false;
     h->have_c = false;
@@ -483,14 +512,14 @@ extern "C" int mhd_get_state_device(mhd_ctx* h, void* dst, size_t n, int prec)
 
 // The CFL of the current state: from the maximum that the last launch of the
 // step before left (the same FP64 expression, the same maximum) where that
-// still describes the state, else a reduction of its own.  step: the CFL of a
+// describes the state, else a reduction of its own.  step: the CFL of a
 // device-dt step (record in the flag block, time advanced, accumulator left
 // clear); otherwise dt, vmax and the record go to report and a valid
 // accumulator stays valid.
 template <typename T>
 static hipError_t enqueue_cfl(mhd_ctx* h, double cfl, bool step, double* report)
 {
-    if (h->acc_valid)
+    if (maximum_holds(h))
         return launch_cfl_from_acc(h->cfl_acc, h->n[0], cfl, h->scal, h->flag, step, report, !step, h->stream);
     const T* f[8];
     current_fields<T>(h, f);
@@ -646,7 +675,7 @@ extern "C" int mhd_fluid(mhd_ctx* h, int dim, double dt)
     if (dim < 0 || dim > 2) return fail(MHD_EINVAL, "dim must be 0, 1 or 2 (got %d)", dim);
     int r = prepare_host_dt(h, dt, true);
     if (r) return r;
-    h->acc_valid = false;
+    state_changes(h);
     HIP_TRY(h, op(h, 0, dim, nullptr));
     return MHD_OK;
 }
@@ -656,7 +685,7 @@ extern "C" int mhd_magnetic(mhd_ctx* h, int dim, double dt)
     if (dim < 0 || dim > 2) return fail(MHD_EINVAL, "dim must be 0, 1 or 2 (got %d)", dim);
     int r = prepare_host_dt(h, dt, false);
     if (r) return r;
-    h->acc_valid = false;
+    state_changes(h);
     HIP_TRY(h, op(h, 1, dim, nullptr));
     return MHD_OK;
 }
@@ -701,7 +730,7 @@ extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
     if (dim < 0 || dim > 7) return fail(MHD_EINVAL, "sweep code must be 0..7 (got %d)", dim);
     int r = prepare_host_dt(h, dt, true);
     if (r) return r;
-    h->acc_valid = false;
+    state_changes(h);
     if (dim == 7) {
         // the middle of a step: M_z, then the reverse z pair
         if (mid_one_launch(h)) {
@@ -727,7 +756,7 @@ extern "C" int mhd_sweep(mhd_ctx* h, int dim, double dt)
             HIP_TRY(h, op(h, 1, 0, nullptr));
             HIP_TRY(h, op(h, 0, 0, nullptr, acc));
         }
-        h->acc_valid = true;
+        maximum_follows(h);
         return MHD_OK;
     }
     const int d = dim % 3;
@@ -845,9 +874,9 @@ extern "C" int mhd_step(mhd_ctx* h, double dt)
 {
     int r = prepare_host_dt(h, dt, true, true);
     if (r) return r;
-    h->acc_valid = false;
+    state_changes(h);
     if ((r = enqueue_step_ops(h, nullptr, h->cfl_acc))) return r;
-    h->acc_valid = true;
+    maximum_follows(h);
     return MHD_OK;
 }
 
@@ -859,9 +888,9 @@ extern "C" int mhd_step_auto(mhd_ctx* h, double cfl)
     HIP_TRY(h, hipSetDevice(h->device));
     h->scal_known = false;
     HIP_TRY(h, enqueue_cfl(h, cfl, true, nullptr));
-    h->acc_valid = false;
+    state_changes(h);
     if ((r = enqueue_step_ops(h, h->flag + FLAG_NONPHYS, h->cfl_acc))) return r;
-    h->acc_valid = true;
+    maximum_follows(h);
     // the device CFL also set the relaxation speed; it stays on the device
     // (c_host < 0 marks that) until read back
     h->have_c = true;

@@ -121,3 +121,61 @@ def test_captured_ensemble_step(env, prec):
         E.run(1, 0.5, graph=k > 0)
     C.close()
     E.close()
+
+
+# (row lengths whose x kernels' workgroups are whole waves, and not)
+@pytest.mark.parametrize("prec", ["f32", "f64"])
+@pytest.mark.parametrize("n", [(32, 16, 8), (20, 16, 8)])
+def test_cfl_around_captures(env, n, prec):
+    """A time step is that of the state it meets: on replays that follow a new
+    state, after a capture that has not run, and after replays that the host
+    does not see."""
+    torch, M, side = env
+    say(f"case: CFL around captures n={n} {prec}")
+    s0, s1 = smooth_state(n, seed=83), smooth_state(n, seed=84)
+    s1[4] *= 2.0                                  # another largest signal speed
+
+    def fresh(state):
+        F = M.Solver(n, prec=prec)
+        F.set_state(state)
+        return F
+
+    S = M.Solver(n, prec=prec, stream=side)
+    S.set_state(s0)
+    S.step_auto(0.5)
+    one = capture(torch, side, lambda: S.step_auto(0.5))
+    F = fresh(S.get_state())                      # recorded, not run
+    assert S.cfl_dt(0.5) == F.cfl_dt(0.5)
+    F.close()
+    S.set_state(s1)
+    F = fresh(s1)
+    for k in range(2):
+        replay(torch, side, one)
+        F.step_auto(0.5)
+        assert np.array_equal(S.get_state(), F.get_state()) and S.time() == F.time(), k
+    F.close()
+
+    S.set_state(s0)
+    dt = S.cfl_dt(0.4)
+    sweeps = capture(torch, side, lambda: (S.sweep(0, dt), S.sweep(3, dt)))
+    S.step(dt)                                    # leaves the maximum of its state
+    replay(torch, side, sweeps)
+    F = fresh(S.get_state())
+    assert S.cfl_dt(0.4) == F.cfl_dt(0.4)
+    for k in range(2):
+        S.step_auto(0.5)
+        F.step_auto(0.5)
+    assert np.array_equal(S.get_state(), F.get_state())
+    F.close()
+
+    S.set_state(s0)                               # two steps in one graph
+    two = capture(torch, side, lambda: (S.step_auto(0.5), S.step_auto(0.5)))
+    for s in (s1, s0):
+        S.set_state(s)
+        F = fresh(s)
+        replay(torch, side, two)
+        F.step_auto(0.5)
+        F.step_auto(0.5)
+        assert np.array_equal(S.get_state(), F.get_state())
+        F.close()
+    S.close()
