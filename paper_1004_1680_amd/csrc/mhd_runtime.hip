@@ -542,6 +542,13 @@ extern "C" int mhd_cfl_dt(mhd_ctx* h, double cfl, double* dt_out)
     h->scal_known = false;
     HIP_TRY(h, enqueue_cfl(h, cfl, false, h->pinned));
     if ((r = sync_stream(h))) return r;
+    if (h->pinned[2] != 0.0 && h->acc_valid) {
+        // the maximum carries a record, maybe one of an earlier state that a
+        // skipped step passed on: the state itself decides
+        h->acc_valid = false;
+        HIP_TRY(h, enqueue_cfl(h, cfl, false, h->pinned));
+        if ((r = sync_stream(h))) return r;
+    }
     const int bad = (int)h->pinned[2];
     if (bad == 1) {
         *dt_out = 0.0;
@@ -912,6 +919,7 @@ extern "C" int mhd_status(mhd_ctx* h, long long* steps_out)
     memcpy(fl, h->pinned, sizeof fl);
     if (steps_out) *steps_out = fl[FLAG_STEPS];
     if (fl[FLAG_NONPHYS]) {
+        h->acc_valid = false;       // skipped steps left the record in it, not a maximum
         HIP_TRY(h, hipMemsetAsync(h->flag + FLAG_NONPHYS, 0, sizeof(int), h->stream));
         if ((r = sync_stream(h))) return r;
         return fl[FLAG_NONPHYS] == 1
