@@ -108,9 +108,19 @@ static void drop_graph(mhd_batch* b)
     b->graph_valid = false;
 }
 
+// every field of every box has 32-bit byte offsets: the launches of a step
+// address all boxes alike (tiles, and x and march kernels with 32-bit offsets)
+static bool offsets32(const mhd_batch* b)
+{
+    if (b->wide) return false;
+    for (const BoxDesc& bd : b->boxes)
+        if ((unsigned long long)bd.ncell * b->esize > (1ull << 32)) return false;
+    return true;
+}
+
 // Box i runs axis d (y, z) in tiles of whole pencils: up to 64 cells where
-// the chunk target (pair: of the fused pairs) leaves the pencil whole, with
-// 32-bit offsets.  Lines and reasons as for a single grid (tile_shape): at
+// the chunk target (pair: of the fused pairs) leaves the pencil whole, in
+// ensembles with 32-bit offsets.  Lines and reasons as for a single grid (tile_shape): at
 // 64 cells tiles win at any number of pencils.  12 boxes of 16 to 48 cells
 // a side, FP32, us per launch: fluid 39 -> 12.5, magnetic 24 -> 12, pair 52
 // -> 20.6, middle 19.3 in place of M_z and the pair.
@@ -118,8 +128,7 @@ static bool box_tiles(const mhd_batch* b, int i, int d, bool pair)
 {
     const BoxDesc& bd = b->boxes[i];
     const int target = pair ? b->pair_chunk_target : b->chunk_target;
-    return d > 0 && !b->wide && bd.n[d] <= BATCH_TILE_CELLS && bd.n[d] <= target &&
-           (unsigned long long)bd.ncell * b->esize <= (1ull << 32);
+    return d > 0 && bd.n[d] <= BATCH_TILE_CELLS && bd.n[d] <= target && offsets32(b);
 }
 
 // every box runs the pairs along d in tiles
@@ -504,13 +513,11 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
         P.gamma = (T)b->gamma;
         P.scal = b->scal;
         P.flag = b->flag;
-        P.offsets32 = !b->wide;
+        P.offsets32 = offsets32(b);
         P.limiter = b->limiter;
         // the last launch (F_x or the x pair) also finds the next step's CFL
         P.cfl_acc = k == nops - 1 ? b->cfl_acc : nullptr;
         P.gamma64 = b->gamma;
-        for (const BoxDesc& bd : b->boxes)
-            if ((unsigned long long)bd.ncell * (b->prec == MHD_F64 ? 8 : 4) > (1ull << 32)) P.offsets32 = false;
         for (int t = 0; t < 2; ++t) {
             P.items = t ? b->d_titems[pl][d] : b->d_items[pl][d];
             P.nitems = t ? b->ntitems[pl][d] : b->nitems[pl][d];
