@@ -223,7 +223,9 @@ int mhd_restrict(mhd_ctx *fine, mhd_ctx *coarse);
  * CHUNK_Y or MHD_TUNE_PAIR_CHUNK_Z for the fused reverse-half pairs.  The
  * built-in choice takes kernels that hold tiles of whole pencils instead of
  * walking them where pencils are short (up to 64 cells, up to 128 on grids
- * of a few million cells); a value that is set selects the walk.
+ * of a few million cells); a value that is set selects the walk (along z, below
+ * 128^3 cells, also for the middle of a step, which then runs as M_z and the
+ * pair).
  * mhd_get_launch reports the walk's chunk and, for the next two keys, what
  * is chosen for the walking kernels: with tiles, MHD_TUNE_REVERSE 0 and
  * MHD_TUNE_MIDDLE 0 run the reverse pairs, and in FP32 with van Leer's

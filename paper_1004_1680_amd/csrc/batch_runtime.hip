@@ -465,11 +465,12 @@ static bool run_pairs_fused(const mhd_batch* b)
     return batch_pairs_fused(b) || (b->rev_mode == 0 && all_tiles(b, 1) && all_tiles(b, 2));
 }
 // (with a third buffer for the faces: every field then ends a step where it
-// started, as with two launches, and one captured step can be replayed)
+// started, as with two launches, and one captured step can be replayed; not
+// where the chunk target cuts the pencils of M_z or of the pair)
 static bool run_mid_aside(const mhd_batch* b)
 {
     return b->aside && !batch_mid_fused(b) && b->mid_mode == 0 && batch_pairs_fused(b) && b->prec == MHD_F32 &&
-           b->limiter == MHD_LIMITER_VANLEER && all_tiles(b, 2);
+           b->limiter == MHD_LIMITER_VANLEER && all_tiles(b, 2) && b->nitems[0][2] == 0;
 }
 
 template <typename T>

@@ -798,10 +798,11 @@ static bool mid_fused(const mhd_ctx* h)
 // left every field in the buffer it started in, which a caller's captured
 // step, replayed on its own buffers, relies on; one launch in place of two
 // would leave the faces in the other one.  So it writes them to a third place,
-// from where the next launch that writes them goes on as after the two.
+// from where the next launch that writes them goes on as after the two.  A
+// chunk that the caller set for M_z or the z pair asks for those two.
 static bool mid_aside(const mhd_ctx* h)
 {
-    return h->aside && h->mid_mode == 0 && pairs_fused(h) && h->limiter == MHD_LIMITER_VANLEER && tiles(h, 3, 2);
+    return h->aside && h->mid_mode == 0 && !h->tune.set_chunk[2] && !h->tune.set_pair[2] && pairs_fused(h) && h->limiter == MHD_LIMITER_VANLEER && tiles(h, 3, 2);
 }
 static bool mid_one_launch(const mhd_ctx* h)
 {
