@@ -8,11 +8,8 @@
 // written 6 times per step, so after a full step the state is back in the
 // buffer it started in, and the captured HIP graph of one step can be
 // replayed for any number of steps.  With the middle M_z M_z F_z in one
-// launch the face fields are written 5 times per step.  Where the marches
-// run it they then alternate between the buffers (cur), and the captured
-// graph holds two steps; where the tile kernels run it, in place of two
-// launches, it writes the faces to a third buffer (aside) and the next launch
-// goes on as after the two.
+// launch the face fields are written 5 times per step: they alternate
+// between the buffers (cur), and the captured graph holds two steps.
 #include <hip/hip_runtime.h>
 
 #include <math.h>
@@ -40,7 +37,6 @@ struct mhd_batch {
     int device;
     size_t total;                 // elements per buffer
     void* buf[2];
-    void* aside;                  // a third buffer for the faces (the tiles' one-launch middle), or null
     int cur[8];
     double* scal;                 // nbox x SCAL_COUNT
     int* flag;                    // nbox x FLAG_COUNT
@@ -74,6 +70,8 @@ struct mhd_batch {
     bool graph_valid;
     int graph_steps;        // steps in the captured graph (1, or 2 with the fused middle)
     int graph_bpar;         // buffer of the face fields when the graph starts
+    bool capturing;         // mhd_batch_run captures its own graph
+    bool captured;          // a caller captured a step
     bool failed;
 };
 
@@ -183,15 +181,6 @@ static int build_lists(mhd_batch* b)
                 HIP_TRY(b, hipMalloc(&dst, sizeof(int2) * v.size()));
                 HIP_TRY(b, hipMemcpy(dst, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice));
             }
-    // the third buffer of the tiles' one-launch middle (FP32 boxes below 128^3
-    // cells on average), laid out as the other two, of which it holds the
-    // faces; up to 1 GiB, and without it the middle is two launches
-    const size_t bytes = b->total * b->esize;
-    if (!b->aside && b->prec == MHD_F32 && all_tiles(b, 2) && b->total < (size_t)b->nbox * 8 * MID_CELLS &&
-        bytes <= (size_t)1 << 30 && hipMalloc(&b->aside, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        b->aside = nullptr;
-    }
     return MHD_OK;
 }
 
@@ -201,7 +190,7 @@ extern "C" void mhd_batch_destroy(mhd_batch* b)
     (void)hipStreamSynchronize(b->stream);
     drop_graph(b);
     free_lists(b);
-    void* ptrs[] = { b->buf[0], b->buf[1], b->aside, b->scal, b->flag, b->d_cfl_items, b->d_item_first,
+    void* ptrs[] = { b->buf[0], b->buf[1], b->scal, b->flag, b->d_cfl_items, b->d_item_first,
                      b->partial, b->partial_bad, b->cfl_acc };
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -256,12 +245,13 @@ extern "C" mhd_batch* mhd_batch_create(int nbox, const int* dims, double gamma, 
         }
         b->grid[d] = 1024;
     }
-    b->buf[0] = b->buf[1] = b->aside = nullptr;
+    b->buf[0] = b->buf[1] = nullptr;
     b->scal = nullptr; b->flag = nullptr;
     b->d_cfl_items = nullptr; b->d_item_first = nullptr;
     b->partial = nullptr; b->partial_bad = nullptr;
     b->graph = nullptr; b->exec = nullptr; b->graph_valid = false;
     b->graph_steps = 1; b->graph_bpar = 0;
+    b->capturing = b->captured = false;
     b->failed = false;
     for (int q = 0; q < 8; ++q) b->cur[q] = 0;
     if (hipGetDevice(&b->device) != hipSuccess) {
@@ -464,12 +454,17 @@ static bool run_pairs_fused(const mhd_batch* b)
 {
     return batch_pairs_fused(b) || (b->rev_mode == 0 && all_tiles(b, 1) && all_tiles(b, 2));
 }
-// (with a third buffer for the faces: every field then ends a step where it
-// started, as with two launches, and one captured step can be replayed; not
-// where the chunk target cuts the pencils of M_z or of the pair)
-static bool run_mid_aside(const mhd_batch* b)
+// (in place of two launches, so not once a caller has captured a step: the two
+// leave every field in the buffer that it started in, which replays of that
+// step rely on, whatever runs between them.  A third buffer for the faces, as
+// a single grid has, would keep the one launch there, but cost 9% where two
+// buffers just fit the infinity cache: 4 M cells of 32^3, 448 us a step for
+// 413, two launches 440.  Nor where the chunk target cuts the pencils of M_z
+// or of the pair.)
+static bool run_mid_fused(const mhd_batch* b)
 {
-    return b->aside && !batch_mid_fused(b) && b->mid_mode == 0 && batch_pairs_fused(b) && b->prec == MHD_F32 &&
+    if (batch_mid_fused(b)) return true;
+    return b->mid_mode == 0 && !b->captured && batch_pairs_fused(b) && b->prec == MHD_F32 &&
            b->limiter == MHD_LIMITER_VANLEER && all_tiles(b, 2) && b->nitems[0][2] == 0;
 }
 
@@ -495,17 +490,15 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
                                      { 2, 2 }, { 2, 1 }, { 2, 0 } };
     // op 3: the middle M_z M_z F_z in one launch
     static const int middle[8][2] = { { 0, 0 }, { 1, 0 }, { 0, 1 }, { 1, 1 }, { 0, 2 }, { 3, 2 }, { 2, 1 }, { 2, 0 } };
-    const bool fz = run_pairs_fused(b), twice = fz && run_mid_aside(b), mid = twice || (fz && batch_mid_fused(b));
-    bool in_aside = false;          // the faces are in the third buffer now
+    const bool fz = run_pairs_fused(b), mid = fz && run_mid_fused(b);
     const int nops = mid ? 8 : fz ? 9 : 12;
     for (int k = 0; k < nops; ++k) {
         const int op = mid ? middle[k][0] : fz ? fused[k][0] : separate[k][0];
         const int d = mid ? middle[k][1] : fz ? fused[k][1] : separate[k][1];
         BatchParams<T> P;
-        const bool to_aside = op == 3 && twice;
         for (int q = 0; q < 8; ++q) {
-            P.in_base[q] = reinterpret_cast<const T*>(q >= 5 && in_aside ? b->aside : b->buf[b->cur[q]]);
-            P.out_base[q] = reinterpret_cast<T*>(q >= 5 && to_aside ? b->aside : b->buf[1 - b->cur[q]]);
+            P.in_base[q] = reinterpret_cast<const T*>(b->buf[b->cur[q]]);
+            P.out_base[q] = reinterpret_cast<T*>(b->buf[1 - b->cur[q]]);
         }
         P.boxes = b->d_boxes;
         // the fused pairs along y and z (and the middle) have work lists of
@@ -529,11 +522,8 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
         }
         if (op != 1)
             for (int q = 0; q < 5; ++q) b->cur[q] = 1 - b->cur[q];
-        if (op != 0) {
-            if (!to_aside)
-                for (int q = 5; q < 8; ++q) b->cur[q] = 1 - b->cur[q];
-            in_aside = to_aside;
-        }
+        if (op != 0)
+            for (int q = 5; q < 8; ++q) b->cur[q] = 1 - b->cur[q];
     }
     b->acc_valid = true;
     return MHD_OK;
@@ -541,6 +531,7 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
 
 static int enqueue_step(mhd_batch* b, double cfl)
 {
+    if (!b->capturing && mhd_capture_id(b->stream)) b->captured = true;
     return b->prec == MHD_F64 ? enqueue_batch_step<double>(b, cfl) : enqueue_batch_step<float>(b, cfl);
 }
 
@@ -572,9 +563,9 @@ extern "C" int mhd_batch_run(mhd_batch* b, double cfl, int nsteps, int use_graph
         --nsteps;
     }
     if (nsteps == 0) return MHD_OK;
-    // with the marches' fused middle a step moves the face fields to the other
+    // with the fused middle a step moves the face fields to the other
     // buffer: the graph holds two steps and starts from one buffer of them
-    const int gs = batch_mid_fused(b) ? 2 : 1;
+    const int gs = run_mid_fused(b) ? 2 : 1;
     if (b->graph_valid && (b->graph_cfl != cfl || b->graph_steps != gs)) drop_graph(b);
     if (gs == 2 && b->graph_valid && b->cur[5] != b->graph_bpar) {
         if ((r = enqueue_step(b, cfl))) return r;
@@ -583,8 +574,10 @@ extern "C" int mhd_batch_run(mhd_batch* b, double cfl, int nsteps, int use_graph
     if (!b->graph_valid) {
         const int bpar = b->cur[5];
         HIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+        b->capturing = true;
         r = enqueue_step(b, cfl);
         if (!r && gs == 2) r = enqueue_step(b, cfl);
+        b->capturing = false;
         hipGraph_t g = nullptr;
         const hipError_t e = hipStreamEndCapture(b->stream, &g);
         if (r) {

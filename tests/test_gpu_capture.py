@@ -112,7 +112,12 @@ def test_captured_ensemble_step(env, prec):
             X.set_state(i, smooth_state(n, seed=82 + i))
         X.step_auto(0.5)
     graph = capture(torch, side, lambda: C.step_auto(0.5))
-    for k in range(3):
+    for k in range(4):
+        if k == 2:                                # another state, after more steps of each kind
+            for X in (C, E):
+                X.run(2, 0.5)
+                X.set_state(1, smooth_state(dims[1], seed=86))
+                X.step_auto(0.5)
         replay(torch, side, graph)
         E.step_auto(0.5)
         for i in range(len(dims)):
