@@ -42,11 +42,10 @@ struct mhd_batch {
     int* flag;                    // nbox x FLAG_COUNT
     // work lists of the single operators [0] and of the fused pairs and the
     // middle along y, z [1] (x: [0] for both): items of the row and march
-    // kernels, and tile items of the boxes whose pencils run in tiles
+    // kernels, or tiles of whole pencils (tiled)
     int2* d_items[2][3];
     int nitems[2][3];
-    int2* d_titems[2][3];
-    int ntitems[2][3];
+    bool tiled[2][3];
     int2* d_cfl_items;
     int n_cfl_items;
     int* d_item_first;
@@ -91,8 +90,7 @@ static void free_lists(mhd_batch* b)
     for (int p = 0; p < 2; ++p)
         for (int d = 0; d < 3; ++d) {
             if (b->d_items[p][d]) { (void)hipFree(b->d_items[p][d]); b->d_items[p][d] = nullptr; }
-            if (b->d_titems[p][d]) { (void)hipFree(b->d_titems[p][d]); b->d_titems[p][d] = nullptr; }
-            b->nitems[p][d] = b->ntitems[p][d] = 0;
+            b->nitems[p][d] = 0;
         }
     if (b->d_boxes) { (void)hipFree(b->d_boxes); b->d_boxes = nullptr; }
 }
@@ -116,23 +114,27 @@ static bool offsets32(const mhd_batch* b)
     return true;
 }
 
-// Box i runs axis d (y, z) in tiles of whole pencils: up to 64 cells where
-// the chunk target (pair: of the fused pairs) leaves the pencil whole, in
-// ensembles with 32-bit offsets.  Lines and reasons as for a single grid (tile_shape): at
-// 64 cells tiles win at any number of pencils.  12 boxes of 16 to 48 cells
-// a side, FP32, us per launch: fluid 39 -> 12.5, magnetic 24 -> 12, pair 52
-// -> 20.6, middle 19.3 in place of M_z and the pair.
-static bool box_tiles(const mhd_batch* b, int i, int d, bool pair)
+// The launches along y or z (pair: of the fused pairs and the middle) run in
+// tiles of whole pencils: up to 64 cells in every box, left whole by the chunk
+// target, in ensembles with 32-bit offsets.  Reasons as for a single grid
+// (tile_shape).  Not for the short boxes beside longer ones: tiles and marches
+// are then two launches, each with its own tail, where one took both (boxes of
+// 32, 64 and 96 cells twice, FP32: 474 us a step against 429; 16, 24, 32 and
+// 96: 405 / 357; 32, 64, 96, 128 four times: 1654 / 1552).  And past the lines
+// on the total of cells the marches fill the card, with longer loads (FP32, us
+// a step, tiles / marches: 64^3 4 M cells 424 / 489, 8 M 1060 / 954, 32 M 4060
+// / 3550; 48^3 2.1 M 249 / 322, 4.2 M 483 / 533, 8.4 M 1133 / 1039; FP64 64^3
+// 2 M 574 / 867, 4 M 1230 / 1312, 8 M 2420 / 2353; 40^3 4 M 1366 / 1338), but for
+// pencils of up to 32 cells, whose marches are mostly warm-up (FP32 32^3 8 M
+// 936 / 976, 16 M 1836 / 1980; FP64 8 M 2320 / 2353, 16 M 4600 / 4728).
+static bool axis_tiles(const mhd_batch* b, int d, bool pair)
 {
-    const BoxDesc& bd = b->boxes[i];
+    if (d == 0 || !offsets32(b)) return false;
     const int target = pair ? b->pair_chunk_target : b->chunk_target;
-    return d > 0 && bd.n[d] <= BATCH_TILE_CELLS && bd.n[d] <= target && offsets32(b);
-}
-
-// every box runs the pairs along d in tiles
-static bool all_tiles(const mhd_batch* b, int d)
-{
-    return b->ntitems[1][d] > 0 && b->nitems[1][d] == 0;
+    int longest = 0;
+    for (const BoxDesc& bd : b->boxes) longest = std::max(longest, bd.n[d]);
+    const size_t line = b->prec == MHD_F32 ? (size_t)9 << 19 : (size_t)3 << 20;     // cells
+    return longest <= target && (longest <= 32 || (longest <= BATCH_TILE_CELLS && b->total / 8 <= line));
 }
 
 // (re)build box shapes and the work lists of the three directions
@@ -140,7 +142,9 @@ static int build_lists(mhd_batch* b)
 {
     free_lists(b);
     drop_graph(b);
-    std::vector<int2> items[2][3], titems[2][3];
+    std::vector<int2> items[2][3];
+    for (int p = 0; p < 2; ++p)
+        for (int d = 0; d < 3; ++d) b->tiled[p][d] = axis_tiles(b, d, p == 1);
     for (int i = 0; i < b->nbox; ++i) {
         BoxDesc& bd = b->boxes[i];
         bd.chunk[0] = bd.pchunk[0] = 0;
@@ -160,27 +164,25 @@ static int build_lists(mhd_batch* b)
         for (int p = 0; p < 2; ++p)
             for (int d = 1; d < 3; ++d) {
                 const long npencil = (long)bd.n[0] * (d == 1 ? bd.n[2] : bd.n[1]);
-                const bool tiled = box_tiles(b, i, d, p == 1);
-                const long per = tiled ? batch_tile_pencils(bd.n[d]) : 256;
+                const bool tiled = b->tiled[p][d];
+                const long per = tiled ? batch_tile_pencils(bd.n[d], b->prec == MHD_F32) : 256;
                 const long lanes = tiled ? npencil : npencil * (bd.n[d] / (p ? bd.pchunk[d] : bd.chunk[d]));
                 const int nt = (int)((lanes + per - 1) / per);
                 if (p == 0) bd.ntile[d] = nt;
-                for (int t = 0; t < nt; ++t) (tiled ? titems : items)[p][d].push_back(make_int2(i, t));
+                for (int t = 0; t < nt; ++t) items[p][d].push_back(make_int2(i, t));
             }
     }
     HIP_TRY(b, hipMalloc(&b->d_boxes, sizeof(BoxDesc) * b->nbox));
     HIP_TRY(b, hipMemcpy(b->d_boxes, b->boxes.data(), sizeof(BoxDesc) * b->nbox,
                          hipMemcpyHostToDevice));
     for (int p = 0; p < 2; ++p)
-        for (int d = 0; d < 3; ++d)
-            for (int t = 0; t < 2; ++t) {
-                const std::vector<int2>& v = t ? titems[p][d] : items[p][d];
-                int2*& dst = t ? b->d_titems[p][d] : b->d_items[p][d];
-                (t ? b->ntitems : b->nitems)[p][d] = (int)v.size();
-                if (v.empty()) continue;
-                HIP_TRY(b, hipMalloc(&dst, sizeof(int2) * v.size()));
-                HIP_TRY(b, hipMemcpy(dst, v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice));
-            }
+        for (int d = 0; d < 3; ++d) {
+            const std::vector<int2>& v = items[p][d];
+            b->nitems[p][d] = (int)v.size();
+            if (v.empty()) continue;
+            HIP_TRY(b, hipMalloc(&b->d_items[p][d], sizeof(int2) * v.size()));
+            HIP_TRY(b, hipMemcpy(b->d_items[p][d], v.data(), sizeof(int2) * v.size(), hipMemcpyHostToDevice));
+        }
     return MHD_OK;
 }
 
@@ -240,8 +242,9 @@ extern "C" mhd_batch* mhd_batch_create(int nbox, const int* dims, double gamma, 
     b->d_boxes = nullptr;
     for (int d = 0; d < 3; ++d) {
         for (int p = 0; p < 2; ++p) {
-            b->d_items[p][d] = b->d_titems[p][d] = nullptr;
-            b->nitems[p][d] = b->ntitems[p][d] = 0;
+            b->d_items[p][d] = nullptr;
+            b->nitems[p][d] = 0;
+            b->tiled[p][d] = false;
         }
         b->grid[d] = 1024;
     }
@@ -445,14 +448,12 @@ static bool batch_mid_fused(const mhd_batch* b)
     return b->mid_mode == 1;
 }
 
-// what a step runs: the reports above are the marches' choice; where every
-// box runs the pairs in tiles and the choice is the library's, the pairs, and
-// in FP32 with van Leer's limiter the middle, are one launch each (the
-// launches of a step flip the fields' buffers, so one choice holds for all
-// boxes)
+// what a step runs: the reports above are the marches' choice; where the
+// pairs run in tiles and the choice is the library's, the pairs, and in FP32
+// with van Leer's limiter the middle, are one launch each
 static bool run_pairs_fused(const mhd_batch* b)
 {
-    return batch_pairs_fused(b) || (b->rev_mode == 0 && all_tiles(b, 1) && all_tiles(b, 2));
+    return batch_pairs_fused(b) || (b->rev_mode == 0 && b->tiled[1][1] && b->tiled[1][2]);
 }
 // (in place of two launches, so not once a caller has captured a step: the two
 // leave every field in the buffer that it started in, which replays of that
@@ -465,7 +466,7 @@ static bool run_mid_fused(const mhd_batch* b)
 {
     if (batch_mid_fused(b)) return true;
     return b->mid_mode == 0 && !b->captured && batch_pairs_fused(b) && b->prec == MHD_F32 &&
-           b->limiter == MHD_LIMITER_VANLEER && all_tiles(b, 2) && b->nitems[0][2] == 0;
+           b->limiter == MHD_LIMITER_VANLEER && b->tiled[1][2] && b->tiled[0][2];
 }
 
 template <typename T>
@@ -512,14 +513,11 @@ static int enqueue_batch_step(mhd_batch* b, double cfl)
         // the last launch (F_x or the x pair) also finds the next step's CFL
         P.cfl_acc = k == nops - 1 ? b->cfl_acc : nullptr;
         P.gamma64 = b->gamma;
-        for (int t = 0; t < 2; ++t) {
-            P.items = t ? b->d_titems[pl][d] : b->d_items[pl][d];
-            P.nitems = t ? b->ntitems[pl][d] : b->nitems[pl][d];
-            if (!P.nitems) continue;
-            const int grid = std::max(8, std::min(b->grid[d], (P.nitems + 7) / 8 * 8));
-            HIP_TRY(b, t ? launch_batch_tile_op<T>(P, op, d, grid, b->stream)
-                         : launch_batch_op<T>(P, op, d, grid, b->stream));
-        }
+        P.items = b->d_items[pl][d];
+        P.nitems = b->nitems[pl][d];
+        const int grid = std::max(8, std::min(b->grid[d], (P.nitems + 7) / 8 * 8));
+        HIP_TRY(b, b->tiled[pl][d] ? launch_batch_tile_op<T>(P, op, d, grid, b->stream)
+                                   : launch_batch_op<T>(P, op, d, grid, b->stream));
         if (op != 1)
             for (int q = 0; q < 5; ++q) b->cur[q] = 1 - b->cur[q];
         if (op != 0)

@@ -2168,7 +2168,7 @@ constexpr int batch_waves(int d)
 
 // The tile kernels' form for the boxes of a work list whose pencils along y
 // or z are short and whole (32-bit offsets): bd.n[D] / 4 threads per pencil,
-// as many pencils as 256 threads hold.  The tile functions leave LDS to the
+// batch_tile_pencils of them.  The tile functions leave LDS to the
 // next item as they leave it between two operators of one item: every
 // region is rewritten only after a barrier that follows its last read.
 template <typename T, int OP, int D, int LIM>
@@ -2185,7 +2185,7 @@ __global__ void __launch_bounds__(256, (sizeof(T) == 4 ? 3 : 2)) batch_tile_kern
         const BoxDesc bd = B.boxes[it.x];
         const SweepParams<T> P = box_params(B, it.x, bd);
         const int tg = bd.n[D] / 4;
-        sweep_tile<T, OP, D, LIM>(P, it.y, batch_tile_pencils(bd.n[D]), tg, reinterpret_cast<T*>(smem_raw));
+        sweep_tile<T, OP, D, LIM>(P, it.y, batch_tile_pencils(bd.n[D], sizeof(T) == 4), tg, reinterpret_cast<T*>(smem_raw));
     }
 }
 
