@@ -1851,18 +1851,55 @@ inline bool offsets32(const SweepParams<T>& P, const LaunchTuning& tune)
 //   16^3     F 5.1 / 10.8   M 4.7 / 7.5   pair 6.6 / 20   middle 7.4 / 31
 //   64^3     F 8.1 / 17     M 6.8 / 11    pair 10.5 / 29  middle 11.7 / 38
 //   128^3    F 25.5 / 27    M 17.8 / 16.5 pair 33 / 42    middle 46.6 / 57
-//   256x64x256 (y)  F 40 / 48    M 28 / 30   pair 54 / 68
-//   256x128x256 (y) F 112 / 107  M 52 / 47   pair 155 / 136
 // A march costs (chunk + warm-up) positions of latency, so it loses wherever
-// its waves do not fill the SIMDs; past 64 cells per pencil the tile's
-// workgroup is so large that few are resident on a CU, and on grids that
-// stream from HBM that costs more than the march's warm-up.  FP64 windows
-// and tiles hold half the waves per SIMD: the same at 64 cells (F 11.6 / 23,
-// M 8.3 / 15.5, pair 16.5 / 37 at 64^3), 8 pencils (64 bytes) per tile above
-// (128^3: pair 94 / 97, F 55 / 58, M 37 / 37).
+// its waves do not fill the SIMDs.  Where they do, its loads are longer (64
+// lanes along x, a tile 16) and a tile's workgroup, the larger the longer its
+// pencils, leaves part of a CU's wave slots empty, so by length there is a
+// size of grid past which the march is faster (tile_line).
 struct TileShape {
     int tx, tg, threads, grid;
 };
+
+// Most cells (in units of 2^17) at which pencils of nd cells along d run
+// operator op in tiles.  The lines lie between measured sizes (0.5, 1, 1.5, 2,
+// 2.5, 3.2, 4.4, 9, 16 M cells, both axes, tile / march), the least of which
+// on the far side are:
+//   FP32  nd <= 32: F y 0.88 - 0.90 at 16 M, z 1.06 at 32 M (z planes of 1024^2:
+//                   a tile's rows are megabytes apart); pair, middle < 0.85
+//         36:       M 1.1 at 2 M, pair 1.1 at 4.4 M (27 of a tile's 36 lanes)
+//         40 - 64:  F 1.03 - 1.17, M 1.3, pair 0.93 - 1.06 (z planes of 512^2:
+//                   1.14) at 9 M; middle 0.73 - 0.89 at 9 M, 1.1 - 1.5 at 24 M
+//         68, 72:   F 1.14 at 1 M, pair 1.08 and middle 1.2 at 2 M
+//         76 - 84:  F 1.14 at 1 M, pair 1.13 and middle 1.5 at 4.4 M
+//         88 - 96:  F 1.05 - 1.1 at 2 M, pair 1.03 - 1.12 at 4.4 M, middle 1.15
+//                   at 2.5 M
+//         100 - 116: F 1.0 at 2.5 M, pair 1.01 and middle 1.1 at 3.2 M
+//         120, 128: F 0.91 at 2.5 M (past it within 0.05), pair and middle
+//                   0.86 - 1.1 at 4.4 M
+//         (M past 64 cells: 0.9 - 1.1 at 1 M and more)
+//   FP64  nd <= 32: 0.67 - 0.97 at 16 M, F z 1.03 at 32 M
+//         36 - 60:  F 1.05 - 1.1 at 3 M, pair y 1.01 - 1.13 from 9 M, z 1.1 at 3 M
+//                   after M_z's march, as a step runs it
+//         64:       y 0.95, z 1.27 at 16 M
+//         68 - 84:  pair 1.06 at 2.3 M; to 128: 1.03 - 1.07 at 2.5 M
+inline int tile_line(bool f32, int op, int d, int nd)
+{
+    constexpr int ANY = 1 << 14;                     // (a field is at most 2^32 bytes here)
+    if (nd <= 32) return op == 1 ? 16 : op == 0 && d == 2 ? 144 : ANY;
+    if (!f32) {
+        if (nd <= 60) return op == 1 ? 16 : op == 0 || d == 2 ? 18 : 36;
+        if (nd <= 64) return op == 1 ? 16 : d == 1 ? 160 : 80;
+        return op < 2 || nd > 128 ? 0 : nd <= 84 ? 16 : 18;
+    }
+    static constexpr struct { int nd, line[4]; } bands[] = {
+        { 36, { 36, 8, 24, 80 } },  { 64, { 36, 16, 36, 80 } }, { 72, { 5, 0, 13, 13 } },   { 84, { 5, 0, 26, 26 } },
+        { 96, { 10, 0, 26, 18 } },  { 116, { 16, 0, 24, 20 } }, { 128, { 20, 0, 36, 36 } },
+    };
+    for (const auto& b : bands)
+        if (nd <= b.nd) return b.line[op];
+    return 0;
+}
+
 template <typename T>
 inline bool tile_shape(const int n[3], int op, int d, const LaunchTuning& tune, TileShape& ts)
 {
@@ -1871,19 +1908,29 @@ inline bool tile_shape(const int n[3], int op, int d, const LaunchTuning& tune, 
     if (d == 0 || set[d] || tune.wide || cells * sizeof(T) > (1ull << 32)) return false;
     const int nd = n[d], npencil = n[0] * n[3 - d];
     constexpr unsigned long long M = 1ull << 20;
-    const bool f32 = sizeof(T) == 4;
-    const bool use = op == 0 ? nd <= 64 || (f32 && nd <= 128 && cells <= 5 * M / 2)
-                   : op == 1 ? nd <= 64 && cells <= 2 * M
-                             : nd <= 64 || (nd <= 128 && cells <= (f32 ? 9 * M / 2 : 9 * M / 4));
-    if (!use) return false;
+    constexpr bool f32 = sizeof(T) == 4;
+    const bool below = cells <= (unsigned long long)tile_line(f32, op, d, nd) << 17;
+    // along y, where a tile's rows lie one after another, a workgroup of 512
+    // threads holds 32 pencils of 64 cells, 128 bytes of x per load, and stays
+    // ahead at any size (against the march: 9 M cells F 110.6 / 110, pair 157 /
+    // 176; 16 M 178 / 230, 254 / 301; 64 M 688 / 777, 1014 / 1075; 60 cells, 480
+    // threads: F 1.07 of the march at 9 M)
+    const bool wide = f32 && d == 1 && nd == 64 && (op == 0 || op == 2) && !below;
+    if (!below && !wide) return false;
     ts.tg = nd / 4;
     // 64 bytes of consecutive x per load: 16 pencils (FP64 pencils over 64
     // cells: 8), more for short pencils so that a workgroup has a full wave,
     // and 256 threads where a million cells leave enough workgroups (M_y of
-    // 256x32x256: 15.6 us with 32 pencils, 17.8 with 16; 48^3 the other way)
-    ts.tx = !f32 && nd > 64 ? 8 : 16;
+    // 256x32x256: 15.6 us with 32 pencils, 17.8 with 16; 48^3 the other way);
+    // in FP32 then whole 64-byte pieces (512x48x384: pair 193 us with 21
+    // pencils, 165 with 16, march 154; 832x24x840 0.97 of the march with 42,
+    // 0.79 with 32; in FP64 the threads this idles cost more)
+    ts.tx = !f32 && nd > 64 ? 8 : wide ? 32 : 16;
     const int least = cells >= M ? 256 : 64;
-    if (ts.tx * ts.tg < least) ts.tx = least / ts.tg;
+    if (ts.tx * ts.tg < least) {
+        ts.tx = least / ts.tg;
+        if (f32 && cells >= M) ts.tx = ts.tx / 16 * 16;
+    }
     ts.threads = ts.tx * ts.tg;
     ts.grid = (npencil + ts.tx - 1) / ts.tx;
     return ts.threads <= TILE_THREADS;
