@@ -138,9 +138,15 @@ static void current_fields(mhd_ctx* h, const T* f[8])
 // 29.7, pair 65 from 102, middle 98 from 119; 192^3 magnetic 41.5 from 48,
 // pair 124 from 143, middle 163 from 224; 256^3 fluid 198 from 218 (z 173
 // from 206), magnetic 131 from 136; 512^3 fluid 1435 from 1537.
-static int march_chunk(int nd, long npencil, int warm, int unroll, int resident)
+// even: rather than one workgroup per CU two of half as many positions where
+// the estimate is the same, for the single operators (128^3 magnetic 16.0 us
+// at 16 cells, 17.5 at 32; 128x100x128 z 14.5 / 17.0; 160x68x144 y, 17 and 34
+// cells: fluid 24.5 / 28.5); other ties keep the longer (160x88x148: magnetic
+// 17.1 us at 22 cells, 18.0 at 11), and the pairs' differ within 7% either way.
+static int march_chunk(int nd, long npencil, int warm, int unroll, int resident, bool even)
 {
     int best = nd;
+    long best_m = 0;
     double least = 0.0;
     for (int ch = nd; ch >= 8; --ch) {
         if (nd % ch) continue;
@@ -148,7 +154,7 @@ static int march_chunk(int nd, long npencil, int warm, int unroll, int resident)
         const long m = (wgs + 255) / 256, rounds = (m + resident - 1) / resident;
         const int pos = (ch + warm + unroll - 1) / unroll * unroll;
         const double cost = pos * ((double)m + 0.5 * (double)rounds);
-        if (ch == nd || cost < least) { best = ch; least = cost; }
+        if (ch == nd || cost < least || (even && cost == least && best_m == 1)) { best = ch; best_m = m; least = cost; }
     }
     return best;
 }
@@ -164,9 +170,9 @@ static void default_tuning(mhd_ctx* h)
     const bool f32 = h->prec == MHD_F32;
     for (int d = 1; d < 3; ++d) {
         const long npencil = (long)h->n[0] * h->n[3 - d];
-        h->tune.chunk[d] = march_chunk(h->n[d], npencil, 6, f32 ? 4 : 2, f32 ? 3 : 2);
-        h->tune.pair_chunk[d] = march_chunk(h->n[d], npencil, 13, f32 ? 4 : 2, f32 ? 2 : 1);
-        h->tune.triple_chunk[d] = march_chunk(h->n[d], npencil, 19, f32 ? 6 : 2, 1);
+        h->tune.chunk[d] = march_chunk(h->n[d], npencil, 6, f32 ? 4 : 2, f32 ? 3 : 2, true);
+        h->tune.pair_chunk[d] = march_chunk(h->n[d], npencil, 13, f32 ? 4 : 2, f32 ? 2 : 1, false);
+        h->tune.triple_chunk[d] = march_chunk(h->n[d], npencil, 19, f32 ? 6 : 2, 1, false);
     }
 }
 

@@ -84,3 +84,14 @@ def test_other_tiles_are_the_marches(env, n, prec):
         outs.append(S.get_state())
         S.close()
     assert np.array_equal(*outs)
+
+
+@pytest.mark.parametrize("n,d,chunk,pair", [((128, 128, 128), 1, 16, 32), ((128, 100, 128), 2, 16, 32),
+                                            ((160, 68, 144), 1, 17, 34), ((160, 160, 160), 2, 32, 32), ((160, 88, 148), 1, 22, 44),
+                                            ((64, 64, 1024), 2, 32, 64)])
+def test_march_chunks_of_equal_estimate(env, n, d, chunk, pair):
+    M, _ = env
+    S = M.Solver(n)
+    say(f"case: chunks n={n} axis {d}: {S.chunk(d)} {S.pair_chunk(d)}")
+    assert (S.chunk(d), S.pair_chunk(d)) == (chunk, pair)
+    S.close()
