@@ -7,9 +7,9 @@
 namespace mhd {
 
 enum {
-    EPI_BIAS_RELU = 0,   // y = relu(acc + bias) -> bf16
+    EPI_BIAS_RELU = 0,   // y = relu(acc + bias) -> bf16 (32 output channels)
     EPI_BIAS_F32 = 1,    // y = acc + bias -> fp32
-    EPI_MASK = 2,        // y = acc * (mask > 0) -> bf16
+    EPI_MASK = 2,        // y = acc * (mask > 0) -> bf16 (32 output channels)
     EPI_F32 = 3,         // y = acc -> fp32
     EPI_CLOSURE = 4      // y = (acc + bias) gate -> fp32, and its channel sums (32 -> 8 channels)
 };

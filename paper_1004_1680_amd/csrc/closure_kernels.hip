@@ -221,7 +221,8 @@ __global__ void __launch_bounds__((ConvShape<CIN, COUT>::THREADS), (ConvShape<CI
     // 32 output channels in bf16 leave through LDS (two buffers, so that the
     // barrier of a tile is enough): 4 chunks of 16 bytes per cell, chunk q of
     // cell c at q ^ ((c >> 2) & 3), which spreads 16 cells over the banks
-    constexpr bool STAGED = COUT == 32 && (EPI == EPI_BIAS_RELU || EPI == EPI_MASK);
+    constexpr bool STAGED = EPI == EPI_BIAS_RELU || EPI == EPI_MASK;
+    static_assert(!STAGED || COUT == 32, "the layers with 8 output channels leave in FP32");
     constexpr int OUT = STAGED ? CT_X * CT_Y * S::TZ * COUT : 8;
     constexpr int CHUNKS = STAGED ? OUT / 8 / THREADS : 1;
     __shared__ __align__(16) uint16_t tiles[2 * S::LDS];
@@ -375,24 +376,12 @@ __global__ void __launch_bounds__((ConvShape<CIN, COUT>::THREADS), (ConvShape<CI
             }
             if (EPI == EPI_BIAS_RELU) v[e] = fmaxf(v[e], 0.0f);
         }
-        if (EPI == EPI_MASK && !STAGED) {
-            const uint2 mk = *reinterpret_cast<const uint2*>(A.mask + (size_t)c * COUT + co0);
-            const uint16_t mm[4] = { (uint16_t)(mk.x & 0xffff), (uint16_t)(mk.x >> 16),
-                                     (uint16_t)(mk.y & 0xffff), (uint16_t)(mk.y >> 16) };
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (!(bf2f(mm[e]) > 0.0f)) v[e] = 0.0f;
-        }
-        if (EPI == EPI_BIAS_F32 || EPI == EPI_F32 || EPI == EPI_CLOSURE) {
-            *reinterpret_cast<float4*>(A.yf + (size_t)c * COUT + co0) = make_float4(v[0], v[1], v[2], v[3]);
+        if constexpr (STAGED) {
+            const int cl = (plane_of(u) * CT_Y + row(u)) * CT_X + r, q = co0 >> 3;
+            *reinterpret_cast<uint2*>(st + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)) + (co0 & 4)) =
+                make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
         } else {
-            const uint2 w = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
-            if constexpr (STAGED) {
-                const int cl = (plane_of(u) * CT_Y + row(u)) * CT_X + r, q = co0 >> 3;
-                *reinterpret_cast<uint2*>(st + cl * COUT + 8 * (q ^ ((cl >> 2) & 3)) + (co0 & 4)) = w;
-            } else {
-                *reinterpret_cast<uint2*>(A.yb + (size_t)c * COUT + co0) = w;
-            }
+            *reinterpret_cast<float4*>(A.yf + (size_t)c * COUT + co0) = make_float4(v[0], v[1], v[2], v[3]);
         }
     };
     auto load_gate = [&]() INLINE {
@@ -708,9 +697,12 @@ static hipError_t conv_launch(const ConvArgs& A, hipStream_t s)
     using S = ConvShape<CIN, COUT>;
     const dim3 grid((unsigned)conv_grid<CIN, COUT>(A.n)), block(S::THREADS);
     const unsigned long long pieces = (unsigned long long)S::PARTS * A.n[0] * A.n[1] * A.n[2];
-    // offsets in 32 bits up to 2^30 cells of 32 channels (64 GiB)
+    // offsets in 32 bits up to 2^30 cells of 32 channels (64 GiB); past that
+    // only the single-layer calls get (a closure's buffers take 400 GiB there)
     if (pieces < 1ull << 32) hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI, unsigned>), grid, block, 0, s, A);
-    else hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI, unsigned long long>), grid, block, 0, s, A);
+    else if constexpr (EPI == EPI_BIAS_F32 || EPI == EPI_F32)
+        hipLaunchKernelGGL((conv3d_kernel<CIN, COUT, EPI, unsigned long long>), grid, block, 0, s, A);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
@@ -718,9 +710,13 @@ template <int CIN, int COUT>
 static hipError_t conv_dispatch_epi(const ConvArgs& A, int epi, hipStream_t s)
 {
     switch (epi) {
-    case EPI_BIAS_RELU: return conv_launch<CIN, COUT, EPI_BIAS_RELU>(A, s);
+    case EPI_BIAS_RELU:
+        if constexpr (COUT == 32) return conv_launch<CIN, COUT, EPI_BIAS_RELU>(A, s);
+        return hipErrorInvalidValue;
     case EPI_BIAS_F32: return conv_launch<CIN, COUT, EPI_BIAS_F32>(A, s);
-    case EPI_MASK: return conv_launch<CIN, COUT, EPI_MASK>(A, s);
+    case EPI_MASK:
+        if constexpr (COUT == 32) return conv_launch<CIN, COUT, EPI_MASK>(A, s);
+        return hipErrorInvalidValue;
     case EPI_F32: return conv_launch<CIN, COUT, EPI_F32>(A, s);
     case EPI_CLOSURE:
         if constexpr (CIN == 32 && COUT == 8) return conv_launch<CIN, COUT, EPI_CLOSURE>(A, s);
