@@ -3,8 +3,9 @@
 A step is one full update of the method: the FP64 CFL max-reduction on the
 device and the 12 operators F_x M_x F_y M_y F_z M_z M_z F_z M_y F_y M_x F_x
 (dt kept on the device, as mhd_step_auto enqueues it).  In FP32 each
-reverse-half pair (M_d F_d) runs as one fused kernel, so a step is 9
-launches, and the CFL maximum of the next step is found by the last one.  The default
+reverse-half pair (M_d F_d) runs as one fused kernel, and at these sizes M_z
+M_z F_z as one, so a step is 8 launches (FP64: the x pair, 11); the CFL
+maximum of the next step is found by the last one.  The default
 workload is the 512^3 FP32 run of the 3D Orszag-Tang-type state (the size at
 which the HBM-roofline target is stated); ot1024, turb256 (seeded
 random-phase solenoidal turbulence, P(k) ~ k^-4, 1 <= k <= 8, rms Mach 1,
@@ -310,9 +311,16 @@ def time_components(S, n, prec, stream, reps, torch, mhd):
     return out
 
 
+def x_pair_fused(esize, fused, w32, lim):
+    """whether the reverse x pair is one launch: with fused pairs, and in FP64
+    by itself (32-bit offsets, any limiter but superbee)"""
+    return fused or (esize == 8 and w32 == "true" and lim != 3)
+
+
 def step_launches(S, n, esize, fused, w32, lim=0, middle=False):
     """(kernel name, grid threads) of every sweep launch of one step of an
-    n^3 grid, in the profiler's naming: the template arguments as the
+    n^3 grid whose pencils are too long for the tile kernels (n > 128), in the
+    profiler's naming: the template arguments as the
     demangled names print them (the slope limiter; the fluid kernels' freezing
     speed, 0 for the step's; the 32-bit offsets flag of the x kernels last)"""
     t = "double" if esize == 8 else "float"
@@ -341,7 +349,10 @@ def step_launches(S, n, esize, fused, w32, lim=0, middle=False):
                 (f"magfluid_march_kernel<{t}, 2, {w32}, {lim}>", march(S.pair_chunk(2))),
                 (f"magfluid_march_kernel<{t}, 1, {w32}, {lim}>", march(S.pair_chunk(1))),
                 (f"magfluid_x_kernel<{t}, true, {lim}, {w32}>", xgrid)]
-    return [fx, mx, fy, my, fz, mz, mz, fz, my, fy, mx, (f"fluid_x_kernel<{t}, true, {lim}, 0, {w32}>", xgrid)]
+    yz = [fx, mx, fy, my, fz, mz, mz, fz, my, fy]
+    if x_pair_fused(esize, fused, w32, lim):
+        return yz + [(f"magfluid_x_kernel<{t}, true, {lim}, {w32}>", xgrid)]
+    return yz + [mx, (f"fluid_x_kernel<{t}, true, {lim}, 0, {w32}>", xgrid)]
 
 
 def cpu_baseline(wl, reps=3):
@@ -950,22 +961,26 @@ def main():
     kern = {}
     fused = S.reverse() == 1
     middle = S.launch(mhd.MHD_TUNE_MIDDLE) == 1
-    ops = ("fluid", "magnetic", "pair") if fused else ("fluid", "magnetic")
-    for op in ops:
-        for d in range(3):
-            if op == "pair" and d == 0:
-                # the x pair runs once a step, as the last launch, with the
-                # fused CFL epilogue (sweep code 6)
-                S.set_state_tensor(saved)
-                dt = S.cfl_dt(args.cfl) * 0.25
-                ms = time_operator(S, "pair+cfl", 0, dt, args.kernel_reps, stream, torch)
-                gbs = ALG_WORDS["pair"] * esize * ncell / (ms * 1e-3) / 1e9
-                kern["pair_x+cfl"] = {"ms": round(ms, 5), "alg_GBs": round(gbs, 1)}
+    # march and x kernels carry their addressing (32-bit byte offsets when a
+    # field is at most 4 GiB) as a template argument
+    w32 = "true" if ncell * esize <= 2 ** 32 else "false"
+    xpair = x_pair_fused(esize, fused, w32, lim)
+    ops = [(op, d) for op in ("fluid", "magnetic") for d in range(3)]
+    ops += [("pair", d) for d in range(3) if fused or (xpair and d == 0)]
+    for op, d in ops:
+        if op == "pair" and d == 0:
+            # the x pair runs once a step, as the last launch, with the
+            # fused CFL epilogue (sweep code 6)
             S.set_state_tensor(saved)
             dt = S.cfl_dt(args.cfl) * 0.25
-            ms = time_operator(S, op, d, dt, args.kernel_reps, stream, torch)
-            gbs = ALG_WORDS[op] * esize * ncell / (ms * 1e-3) / 1e9
-            kern[f"{op}_{'xyz'[d]}"] = {"ms": round(ms, 5), "alg_GBs": round(gbs, 1)}
+            ms = time_operator(S, "pair+cfl", 0, dt, args.kernel_reps, stream, torch)
+            gbs = ALG_WORDS["pair"] * esize * ncell / (ms * 1e-3) / 1e9
+            kern["pair_x+cfl"] = {"ms": round(ms, 5), "alg_GBs": round(gbs, 1)}
+        S.set_state_tensor(saved)
+        dt = S.cfl_dt(args.cfl) * 0.25
+        ms = time_operator(S, op, d, dt, args.kernel_reps, stream, torch)
+        gbs = ALG_WORDS[op] * esize * ncell / (ms * 1e-3) / 1e9
+        kern[f"{op}_{'xyz'[d]}"] = {"ms": round(ms, 5), "alg_GBs": round(gbs, 1)}
     if middle:
         # M_z M_z F_z in one launch (sweep code 7), run once a step in place of
         # M_z and the z pair
@@ -992,7 +1007,7 @@ def main():
     energy = energy_window(S, args.cfl, ncell, torch)
     # dominant kernel: largest time per step (with fused reverse pairs every
     # kernel runs once a step, otherwise each operator runs twice)
-    skip = {"cfl(sync)"} | ({"pair_x"} if fused else set()) | ({"magnetic_z", "pair_z"} if middle else set())
+    skip = {"cfl(sync)", "pair_x"} | ({"magnetic_z", "pair_z"} if middle else set())
     dom = max((k for k in kern if k not in skip), key=lambda k: kern[k]["ms"])
     op = dom.split("_")[0]
     bytes_per_launch = ALG_WORDS[op] * esize * ncell
@@ -1006,9 +1021,6 @@ def main():
     from paper_1004_1680_amd.profile_summary import read_traffic
     tmap = read_traffic(tpath)
     kname = {"fluid": "fluid", "magnetic": "mag", "pair": "magfluid", "middle": "magmagfluid"}[op]
-    # march kernels carry their addressing (32-bit byte offsets when a field
-    # is under 4 GiB) as a third template argument
-    w32 = "true" if ncell * esize <= 2 ** 32 else "false"
     axis = dom.split("_")[1][0]
     cfl_x = dom.endswith("+cfl")
     # the profiler's names (as in step_launches): the slope limiter, the
@@ -1056,7 +1068,9 @@ def main():
                             + ("8 launches: M_z M_z F_z in one, the reverse pairs M_y F_y, M_x F_x "
                                "fused, CFL in the last" if middle else
                                "9 launches: each reverse pair M_d F_d fused, CFL in the last"
-                               if fused else "12 launches")),
+                               if fused else
+                               "11 launches: the reverse pair M_x F_x fused, CFL in it"
+                               if xpair else "12 launches")),
                    "limiter": args.limiter,
                    "march_chunks": [S.chunk(1), S.chunk(2)],
                    "pair_chunks": [S.pair_chunk(1), S.pair_chunk(2)] if fused else None,
