@@ -220,29 +220,30 @@ int mhd_restrict(mhd_ctx *fine, mhd_ctx *coarse);
  * along the sweep axis in chunks of `value` cells (value must divide the
  * axis length and be >= 8; 0 restores the built-in choice).  key: MHD_TUNE_
  * CHUNK_Y or MHD_TUNE_CHUNK_Z for the single operators, MHD_TUNE_PAIR_
- * CHUNK_Y or MHD_TUNE_PAIR_CHUNK_Z for the fused reverse-half pairs.  The
- * built-in choice takes kernels that hold tiles of whole pencils instead of
- * walking them where pencils are short (up to 64 cells, up to 128 on grids
- * of a few million cells); a value that is set selects the walk (along z, below
- * 128^3 cells, also for the middle of a step, which then runs as M_z and the
- * pair).
- * mhd_get_launch reports the walk's chunk and, for the next two keys, what
- * is chosen for the walking kernels: with tiles, MHD_TUNE_REVERSE 0 and
- * MHD_TUNE_MIDDLE 0 run the reverse pairs, and in FP32 with van Leer's
- * limiter the middle, as one launch each.
+ * CHUNK_Y or MHD_TUNE_PAIR_CHUNK_Z for the fused reverse-half pairs.  Where
+ * pencils are short (up to 128 cells; which length up to which size of grid
+ * depends on the operator, the tier and the axis) the built-in choice takes
+ * kernels that hold tiles of whole pencils instead of walking them; a value
+ * that is set selects the walk (along z, below 128^3 cells, also for the
+ * middle of a step, which then runs as M_z and the pair).
+ * mhd_get_launch reports the chunks, and for the next two keys the choice, of
+ * the walking kernels (y and z).  With 0 and 0 set, launches that other
+ * kernels run may be fewer: the pairs that tiles run and, in FP64 (any limiter
+ * but superbee, 32-bit offsets), the x pair are one launch each, and the
+ * middle is where tiles run it in FP32 with van Leer's limiter.
  * key MHD_TUNE_REVERSE: how the reverse-half pairs M_d F_d of a step and of
  * mhd_sweep(3..5) run: 1 = one fused launch per pair (the new faces stay
- * in registers; 9 launches per step), 2 = the two operators in turn (12
- * launches), 0 = the built-in choice (1 in FP32 with the van Leer or
- * minmod limiter, 2 otherwise: the fused MC and superbee kernels spill
- * registers); mhd_get_launch reports the resolved 1 or 2.
+ * in registers), 2 = the two operators in turn (12 launches per step), 0 =
+ * the built-in choice (for the walking kernels 1 in FP32 with the van Leer or
+ * minmod limiter, 2 otherwise: the others spill registers or come to one wave
+ * per SIMD); mhd_get_launch reports 1 or 2.
  * key MHD_TUNE_MIDDLE: how the middle of a step, M_z M_z F_z (the last
  * forward operator and the first reverse pair), runs: 1 = one launch (the
  * second magnetic window takes the first one's new faces and edge
  * velocities from registers; 8 launches per step), 2 = M_z and the reverse
- * pair (9), 0 = the built-in choice (1 for grids of 128^3 cells and more,
- * 2 below); mhd_get_launch reports 1 or 2.  It takes effect in FP32 with
- * fused reverse pairs and van Leer's limiter only.
+ * pair (9), 0 = the built-in choice (for the walking kernels 1 for grids of
+ * 128^3 cells and more, 2 below); mhd_get_launch reports 1 or 2.  It takes
+ * effect in FP32 with fused reverse pairs and van Leer's limiter only.
  * MHD_TUNE_MIDDLE_CHUNK: its march chunk along z (rules of the chunks above).
  * key MHD_TUNE_ROW_GROUP: the x sweeps visit their row tiles in groups of
  * consecutive rows along y, one group per z in turn, so that the rows z +- 1
@@ -265,9 +266,10 @@ int mhd_get_launch(const mhd_ctx *h, int key, int *value);
 /* ------------------------------------------------------------------------
  * Batched ensembles of uneven periodic boxes.  Each box is an independent
  * grid advanced by the same method (section II) with its own CFL time step
- * and relaxation speed; a step is the per-box CFL (FP64, on the device) and
- * the 12 operators, each operator ONE persistent launch over the work items
- * (box, tile) of all boxes, then the per-box time advance.  A box evolves
+ * and relaxation speed; a step is the per-box CFL (FP64, on the device),
+ * which also advances the boxes' times, and the 12 operators, each ONE
+ * persistent launch over the work items (box, tile) of all boxes (a fused pair
+ * or middle likewise).  A box evolves
  * bit for bit as it would in a single-grid handle.  Box dims follow the
  * single-grid rules.  Not thread-safe.
  * ------------------------------------------------------------------------ */
@@ -313,12 +315,15 @@ int mhd_batch_time(mhd_batch *b, double *times);
  * as MHD_TUNE_WIDE_OFFSETS, and MHD_BATCH_MIDDLE as MHD_TUNE_MIDDLE (1: M_z
  * M_z F_z in one launch, on the fused pairs' work list; 2: M_z and the z
  * pair; 0: built-in, 1 where the boxes hold 128^3 cells or more on average,
- * in FP32 with fused pairs and van Leer's limiter).  Boxes whose pencils
- * along y or z have at most 64 cells, and are not cut by the chunk target,
- * run in tiles of whole pencils instead of walking them; where every box's
- * pairs do, the built-in choices run the pairs, and in FP32 with van Leer's
- * limiter the middle, as one launch each (the reports are those of the
- * walking kernels, as for a single grid).
+ * in FP32 with fused pairs and van Leer's limiter).  Where every box's
+ * pencils along y or z have at most 64 cells, left whole by the chunk target,
+ * and the ensemble at most 4.5 * 2^20 cells in FP32, 3 * 2^20 in FP64 (any
+ * number with pencils of at most 32), that axis runs in tiles of whole pencils
+ * instead of walks, and the built-in choices run its pairs, and in FP32 with
+ * van Leer's limiter the middle, as one launch each; the reports are those of
+ * the walking kernels, as for a single grid.  (Once a caller has captured a
+ * step, the middle in tiles is two launches, so that replays and other steps
+ * mix.)
  * Launch-shape parameters, not part of the method. */
 enum { MHD_BATCH_GRID_X = 10, MHD_BATCH_GRID_Y = 11, MHD_BATCH_GRID_Z = 12,
        MHD_BATCH_CHUNK = 13, MHD_BATCH_REVERSE = 14, MHD_BATCH_WIDE_OFFSETS = 15,

@@ -2,9 +2,10 @@
 //
 // All boxes live in one pair of device buffers; box b holds its 8 fields
 // contiguously at an element offset.  A step is the per-box CFL (segmented
-// FP64 max-reduction, each box its own dt and relaxation speed) followed by
-// the 12 operators, each ONE persistent launch over the (box, tile) work
-// items of its direction, and the per-box time advance.  Every field is
+// FP64 max-reduction, each box its own dt and relaxation speed, or the maxima
+// that the step before left), which also advances each box's time, and the 12
+// operators, each ONE persistent launch over the (box, tile) work items of its
+// direction, pairs and the middle fused where chosen.  Every field is
 // written 6 times per step, so after a full step the state is back in the
 // buffer it started in, and the captured HIP graph of one step can be
 // replayed for any number of steps.  With the middle M_z M_z F_z in one

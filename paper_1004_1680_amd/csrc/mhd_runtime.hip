@@ -720,8 +720,8 @@ static bool tiles(const mhd_ctx* h, int o, int d)
 
 // the reverse pair along axis d runs as one launch: as pairs_fused says for
 // the marches, and, where the choice is the library's, wherever the tile
-// kernels run it (they spill with no limiter and in neither tier; FP64 64^3:
-// 16.5 us against 11.6 + 8.3 for the two operators), and along x in FP64,
+// kernels run it (none of them spills, whatever the limiter and the tier; FP64
+// 64^3: 16.5 us against 11.6 + 8.3 for the two operators), and along x in FP64,
 // whose row kernel holds the pair at the 2 waves per SIMD of F_x alone (with
 // the CFL, against the two operators: 96^3 48.0 us / 54.8, 160^3 193.3 /
 // 194.9, 256^3 714 / 746; superbee's drops to 1 wave with the CFL, and so do

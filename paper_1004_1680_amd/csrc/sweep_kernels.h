@@ -2,7 +2,7 @@
 // & Perrone, arXiv:1004.1680): the relaxing-TVD fluid operator F_d and the
 // constrained-transport magnetic operator M_d along each axis d.
 //
-// Memory is structure of arrays with x fastest.  Two thread mappings keep
+// Memory is structure of arrays with x fastest.  Three thread mappings keep
 // every global access coalesced without a global transpose:
 //  * x sweeps ("row" kernels): a row of the grid is contiguous; each thread
 //    owns 4 consecutive cells of a row and loads them with one vector load
@@ -14,6 +14,9 @@
 //    stencil in a register window (the two-stage scheme needs 3 cells of
 //    look-ahead), so each input value is read once from memory.  A pencil
 //    may be cut into chunks along d; each chunk re-reads a 6-cell warm-up.
+//  * y and z sweeps of short pencils ("tile" kernels): the row kernels' scheme
+//    on a tile of whole pencils, 16 or more consecutive x by all of d, so that
+//    every cell of a pencil is in flight at once (tile_shape says where).
 // Neighbour pencils needed by the transverse field averages and by the
 // edge velocities of constrained transport are read directly; they are the
 // own data of adjacent lanes or adjacent workgroups and are served by the
@@ -484,7 +487,8 @@ __device__ __forceinline__ void fluid_x_tile(const SweepParams<T>& P, int tile, 
                 vec4<T>::store(RA::at(P.out[f], base + i0), v);
             }
         // the record (1 non-physical, 2 zero signal speed) carries over to
-        // the CFL that follows, as the separate reduction would find it
+        // the device-dt step that follows; the host's CFL call reduces the
+        // state itself where it meets one
         if constexpr (CFL)
             if (threadIdx.x == 0) atomicOr(P.cfl_acc + CFL_ACC_SLOTS, (unsigned long long)*P.flag);
         return;
@@ -542,9 +546,8 @@ __global__ void __launch_bounds__(256) fluid_x_kernel(SweepParams<T> P, int tpr,
 // Two parts, so that a second operator over the same velocity field can
 // take the first one's edge velocities and new faces:
 //
-// mag_cells_load: the edge velocities a(k+1/2) of the chains, their fields q
-// at the thread's 4 cells and (q4) the next one, b_n of the 4 cells.  pb:
-// offsets of pencils P, P-t1, P+t1, P-t2, P+t2.  own (optional): rho and m_n
+// mag_cells_load: the edge velocities a(k+1/2) of the chains and their fields
+// q at the thread's 4 cells and (q4) the next one.  pb: offsets of pencils P, P-t1, P+t1, P-t2, P+t2.  own (optional): rho and m_n
 // of the thread's 4 cells as loaded.  A: LDS of 9 values per thread.
 template <typename T, int D, bool W32, typename Thread>
 __device__ __forceinline__ void mag_cells_load(const SweepParams<T>& P, const Thread& R,
@@ -777,7 +780,8 @@ __device__ __forceinline__ void magfluid_x_tile(const SweepParams<T>& P, int til
                 vec4<T>::store(RA::at(P.out[f], base + R.i0), v);
             }
         // the record (1 non-physical, 2 zero signal speed) carries over to
-        // the CFL that follows, as the separate reduction would find it
+        // the device-dt step that follows; the host's CFL call reduces the
+        // state itself where it meets one
         if constexpr (CFL)
             if (threadIdx.x == 0) atomicOr(P.cfl_acc + CFL_ACC_SLOTS, (unsigned long long)*P.flag);
         return;
