@@ -605,79 +605,83 @@ __global__ void __launch_bounds__((ConvShape<CIN, COUT>::THREADS), (ConvShape<CI
 #pragma unroll
         for (int i = 0; i < CHUNKS; ++i) store_staged(load_staged(stage + buf * OUT, i), i);
     }
-    if constexpr (FOLD) {
-        // In the folded form a row that only one of the two output rows may
-        // see meets zero weights in the other's MFMA rows, and zero times an
-        // infinity or a NaN is a NaN, outside its stencil.  So where a
-        // workgroup finds a NaN (EPI_CLOSURE: in its sums) it takes all its
-        // tiles again, the two output rows one after the other, each with its
-        // own input rows and its weights in all 16 MFMA rows.  (Tested for and
-        // mended tile by tile, between the products and the barrier, this cost
-        // 2.5 us of the 62 at 128^3.)
-        if (EPI == EPI_CLOSURE)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) nan = nan || isnan(sum[e]);
-        if (__syncthreads_or(nan)) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sum[e] = 0.0;
-            o = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-            at = conv_visit(o, tx, tz);
+    // In the folded form a row that only one of the two output rows may see
+    // meets zero weights in the other's MFMA rows, and zero times an infinity
+    // or a NaN is a NaN, outside its stencil.  So where a workgroup finds a NaN
+    // (EPI_CLOSURE: in its sums) it takes all its tiles again, the two output
+    // rows one after the other, each with its own input rows and its weights in
+    // all 16 MFMA rows.  (Tested for and mended tile by tile, between the
+    // products and the barrier, this cost 2.5 us of the 62 at 128^3; by a
+    // reduction of its own at the end, 2 us of 70 at 96 x 64 x 64.)
+    auto apart = [&]() INLINE {
+        o = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+        at = conv_visit(o, tx, tz);
 #pragma unroll 1
-            for (; o < end; o += stride, at = conv_next(at, hop, tx, tz)) {
-                c_old = aim(at);
+        for (; o < end; o += stride, at = conv_next(at, hop, tx, tz)) {
+            c_old = aim(at);
 #pragma unroll
-                for (int f = 0; f < FILL; ++f) load(f);
+            for (int f = 0; f < FILL; ++f) load(f);
 #pragma unroll
-                for (int f = 0; f < FILL; ++f) fill(tiles, f);
-                __syncthreads();
-                const uint16_t* const base = tiles + wz * (CH_Y * CL_X * CIN);
+            for (int f = 0; f < FILL; ++f) fill(tiles, f);
+            __syncthreads();
+            const uint16_t* const base = tiles + wz * (CH_Y * CL_X * CIN);
 #pragma unroll 1
-                for (int half = 0; half < 2; ++half) {
-                    f4 one[NA];
+            for (int half = 0; half < 2; ++half) {
+                f4 one[NA];
 #pragma unroll
-                    for (int u = 0; u < NA; ++u) one[u] = f4{ 0.f, 0.f, 0.f, 0.f };
+                for (int u = 0; u < NA; ++u) one[u] = f4{ 0.f, 0.f, 0.f, 0.f };
 #pragma unroll 1
-                    for (int k = 0; k < S::PHASES; ++k) {
-                        const int p = k / CH_Y, in = k % CH_Y;
-                        const bf16x8 left = as_bf8(*reinterpret_cast<const uint4*>(base + (k * CL_X + r) * CIN + 8 * conv_chunk<CIN>(k * CL_X + r, g)));
-                        const bf16x8 right = as_bf8(*reinterpret_cast<const uint4*>(base + (k * CL_X + r + 2) * CIN + 8 * conv_chunk<CIN>(k * CL_X + r + 2, g)));
-                        const bf16x8 b[3] = { left, between(left, right), right };
+                for (int k = 0; k < S::PHASES; ++k) {
+                    const int p = k / CH_Y, in = k % CH_Y;
+                    const bf16x8 left = as_bf8(*reinterpret_cast<const uint4*>(base + (k * CL_X + r) * CIN + 8 * conv_chunk<CIN>(k * CL_X + r, g)));
+                    const bf16x8 right = as_bf8(*reinterpret_cast<const uint4*>(base + (k * CL_X + r + 2) * CIN + 8 * conv_chunk<CIN>(k * CL_X + r + 2, g)));
+                    const bf16x8 b[3] = { left, between(left, right), right };
 #pragma unroll
-                        for (int u = 0; u < NA; ++u) {
-                            const int dz = p - u / NB, dy = in - 2 * (u % NB) - half;
-                            if (dz < 0 || dz > 2 || dy < 0 || dy > 2) continue;
+                    for (int u = 0; u < NA; ++u) {
+                        const int dz = p - u / NB, dy = in - 2 * (u % NB) - half;
+                        if (dz < 0 || dz > 2 || dy < 0 || dy > 2) continue;
 #pragma unroll
-                            for (int dx = 0; dx < 3; ++dx)
-                                one[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                    as_bf8(wp[(dz * 9 + dy * 3 + dx) * 64 + (lane & ~8)]), b[dx], one[u], 0, 0, 0);
-                        }
+                        for (int dx = 0; dx < 3; ++dx)
+                            one[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                as_bf8(wp[(dz * 9 + dy * 3 + dx) * 64 + (lane & ~8)]), b[dx], one[u], 0, 0, 0);
                     }
-#pragma unroll
-                    for (int u = 0; u < NA; ++u)
-                        if (half == g >> 1) acc_old[u] = one[u];
                 }
-                load_gate();
 #pragma unroll
-                for (int u = 0; u < NA; ++u) epilogue(u, nullptr);
-                __syncthreads();                            // the tile's buffer is free again
+                for (int u = 0; u < NA; ++u)
+                    if (half == g >> 1) acc_old[u] = one[u];
             }
+            load_gate();
+#pragma unroll
+            for (int u = 0; u < NA; ++u) epilogue(u, nullptr);
+            __syncthreads();                            // the tile's buffer is free again
         }
-    }
+    };
     if constexpr (EPI == EPI_CLOSURE) {
         // the workgroup's channel sums: 16 lanes of a channel, then the waves
+        // (every thread has the total of channel threadIdx.x % 8)
+        auto totals = [&]() INLINE {
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int st = FOLD ? 32 : 8; st > 0; st >>= st == 32 ? 2 : 1) sum[e] += __shfl_xor(sum[e], st, 64);
-        if (r == 0 && g < 2)
+                for (int st = FOLD ? 32 : 8; st > 0; st >>= st == 32 ? 2 : 1) sum[e] += __shfl_xor(sum[e], st, 64);
+            if (r == 0 && g < 2)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) wave_sum[wave][4 * g + e] = sum[e];
-        __syncthreads();
-        if (threadIdx.x < 8) {
+                for (int e = 0; e < 4; ++e) wave_sum[wave][4 * g + e] = sum[e];
+            __syncthreads();
             double v = 0.0;
-            for (int w = 0; w < S::WAVES; ++w) v += wave_sum[w][threadIdx.x];
-            A.sums[(size_t)blockIdx.x * 8 + threadIdx.x] = v;
+            for (int w = 0; w < S::WAVES; ++w) v += wave_sum[w][threadIdx.x & 7];
+            return v;
+        };
+        double v = totals();
+        if (__any(isnan(v))) {                              // (the same in every wave)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] = 0.0;
+            apart();
+            v = totals();
         }
+        if (threadIdx.x < 8) A.sums[(size_t)blockIdx.x * 8 + threadIdx.x] = v;
+    } else if constexpr (FOLD) {
+        if (__syncthreads_or(nan)) apart();
     }
 }
 #undef INLINE
