@@ -1866,8 +1866,8 @@ struct TileShape {
 
 // Most cells (in units of 2^17) at which pencils of nd cells along d run
 // operator op in tiles.  The lines lie between measured sizes (0.5, 1, 1.5, 2,
-// 2.5, 3.2, 4.4, 9, 16 M cells, both axes, tile / march), the least of which
-// on the far side are:
+// 2.5, 3.2, 4.4, 9, 16 M cells, both axes; 480 random grids in whole steps),
+// tile / march on the far side:
 //   FP32  nd <= 32: F y 0.88 - 0.90 at 16 M, z 1.06 at 32 M (z planes of 1024^2:
 //                   a tile's rows are megabytes apart); pair, middle < 0.85
 //         36:       M 1.1 at 2 M, pair 1.1 at 4.4 M (27 of a tile's 36 lanes)
@@ -1875,9 +1875,9 @@ struct TileShape {
 //                   1.14) at 9 M; middle 0.73 - 0.89 at 9 M, 1.1 - 1.5 at 24 M
 //         68, 72:   F 1.14 at 1 M, pair 1.08 and middle 1.2 at 2 M
 //         76 - 84:  F 1.14 at 1 M, pair 1.13 and middle 1.5 at 4.4 M
-//         88 - 96:  F 1.05 - 1.1 at 2 M, pair 1.03 - 1.12 at 4.4 M, middle 1.15
-//                   at 2.5 M
-//         100 - 116: F 1.0 at 2.5 M, pair 1.01 and middle 1.1 at 3.2 M
+//         88 - 96:  F 1.05 - 1.1 at 2 M, pair 1.03 - 1.14 and middle 1.2 - 1.4 at
+//                   4.4 M (middle of 88 1.15 at 2.5 M, 0.90 at 3.2 M)
+//         100 - 116: F 1.0 at 2.5 M, pair 1.02 - 1.14 and middle 1.0 - 1.1 at 4.4 M
 //         120, 128: F 0.91 at 2.5 M (past it within 0.05), pair and middle
 //                   0.86 - 1.1 at 4.4 M
 //         (M past 64 cells: 0.9 - 1.1 at 1 M and more)
@@ -1896,8 +1896,8 @@ inline int tile_line(bool f32, int op, int d, int nd)
         return op < 2 || nd > 128 ? 0 : nd <= 84 ? 16 : 18;
     }
     static constexpr struct { int nd, line[4]; } bands[] = {
-        { 36, { 36, 8, 24, 80 } },  { 64, { 36, 16, 36, 80 } }, { 72, { 5, 0, 13, 13 } },   { 84, { 5, 0, 26, 26 } },
-        { 96, { 10, 0, 26, 18 } },  { 116, { 16, 0, 24, 20 } }, { 128, { 20, 0, 36, 36 } },
+        { 36, { 36, 8, 24, 80 } },  { 64, { 36, 16, 36, 80 } }, { 72, { 7, 0, 13, 13 } },   { 84, { 7, 0, 26, 26 } },
+        { 96, { 13, 0, 28, 28 } },  { 116, { 18, 0, 33, 28 } }, { 128, { 20, 0, 36, 36 } },
     };
     for (const auto& b : bands)
         if (nd <= b.nd) return b.line[op];

@@ -29,8 +29,8 @@ def say(*a):
 
 # grid, tier, axis, operators (F, M, P pair, Z middle) that run in tiles
 ROUTES = [((128, 128, 128), "f32", 1, "FP"), ((128, 128, 128), "f32", 2, "FPZ"), ((160, 128, 128), "f32", 2, "FPZ"),
-          ((256, 128, 128), "f32", 2, "PZ"), ((128, 72, 256), "f32", 1, ""), ((80, 72, 64), "f32", 1, "FP"),
-          ((128, 72, 128), "f32", 1, "P"), ((160, 80, 208), "f32", 1, "P"), ((128, 96, 96), "f32", 1, "FP"), ((128, 96, 128), "f32", 1, "P"),
+          ((256, 128, 128), "f32", 2, "PZ"), ((128, 72, 256), "f32", 1, ""), ((80, 72, 64), "f32", 1, "FP"), ((124, 84, 64), "f32", 1, "FP"), ((148, 84, 76), "f32", 1, "P"),
+          ((128, 72, 128), "f32", 1, "P"), ((160, 80, 208), "f32", 1, "P"), ((128, 96, 96), "f32", 1, "FP"), ((128, 96, 128), "f32", 1, "FP"), ((128, 96, 148), "f32", 1, "P"),
           ((128, 112, 128), "f32", 2, "FPZ"), ((192, 112, 128), "f32", 1, "P"), ((128, 64, 128), "f32", 1, "FMP"),
           ((256, 64, 256), "f32", 1, "FP"), ((384, 64, 256), "f32", 1, "FP"), ((256, 384, 64), "f32", 2, "Z"),
           ((384, 48, 256), "f32", 1, "FP"), ((384, 48, 260), "f32", 1, ""), ((384, 260, 48), "f32", 2, "Z"),
