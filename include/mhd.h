@@ -287,7 +287,11 @@ int mhd_batch_info(const mhd_batch *b, int *nbox, long long *ncell);
 int mhd_batch_set_state(mhd_batch *b, int box, const double *host, size_t n);
 int mhd_batch_get_state(mhd_batch *b, int box, double *host, size_t n);
 
-/* One step of every box with its own dt = cfl h / vmax (asynchronous). */
+/* One step of every box with its own dt = cfl h / vmax (asynchronous).
+ * Captured in a caller's graph as the first step after mhd_batch_set_state it
+ * reduces, on every replay, the states that it finds (replay it before the
+ * next eager step).  Captured after a step it takes the maxima that the step
+ * before each replay left: step once between a new state and a replay. */
 int mhd_batch_step_auto(mhd_batch *b, double cfl);
 
 /* nsteps steps; use_graph != 0 captures one step in a HIP graph (once per
